@@ -1,0 +1,49 @@
+"""GPU kernels at the sizes where their tiling can go wrong: edges of tiles,
+remainders, the smallest and largest of a dispatch range, against the FP64
+oracle (or exact integer results)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.helpers import clustered_msa
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+@pytest.fixture(scope="module")
+def plm():
+    import paper_1401_4832_amd as p
+    return p
+
+
+def _to(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+# rows around the 64- and 128-row tiles and the switch between them (8192 rows); columns below one
+# 32-column word, at its edges, across a chunk of four words, and with an odd row pitch
+@pytest.mark.parametrize("B,N,q,theta", [(2, 2, 2, 0.5), (64, 31, 21, 0.8), (129, 32, 21, 0.8), (257, 33, 5, 0.6),
+                                         (4097, 129, 21, 0.8), (8191, 45, 21, 0.75), (8192, 160, 21, 0.8),
+                                         (8321, 35, 21, 1.0), (8200, 257, 21, 0.8), (300, 513, 21, 0.0)])
+def test_reweight_tiles_bit_exact(plm, B, N, q, theta):
+    print(f"reweight tiles B={B} N={N} q={q} theta={theta}", flush=True)
+    msa = clustered_msa(seed=3 * B + N, B=B, N=N, n_anc=max(1, B // 30), p_mut=0.08, q=q)
+    m, w, beff = plm.reweight(_to(msa), theta=theta, q=q)
+    plm.sync(DEV)
+    m_o, w_o, beff_o = oracle.reweight(msa, theta=theta)
+    assert np.array_equal(m.cpu().numpy(), m_o)
+    assert np.array_equal(w.cpu().numpy(), w_o)
+    assert beff.item() == beff_o
+
+
+@pytest.mark.parametrize("B,N,row,col", [(200, 40, 199, 39), (9000, 33, 8999, 0), (9000, 300, 0, 299)])
+def test_reweight_reports_every_bad_symbol(plm, B, N, row, col):
+    print(f"reweight bad symbol B={B} N={N}", flush=True)
+    msa = clustered_msa(seed=5, B=B, N=N, n_anc=50, p_mut=0.9)
+    for v in (21, 32, 200):
+        msa[row, col] = v
+        plm.reweight(_to(msa), theta=0.8)
+        with pytest.raises(plm.PlmError):
+            plm.sync(DEV)
