@@ -1,6 +1,6 @@
 // k_score.hip -- coupling scores of asymmetric plmDCA (sec. 3.4 steps 4-6).
 //
-// One wave per pair (i, j), i < j: both estimates of the pair as q x q
+// For every pair (i, j), i < j: both estimates of the pair as q x q
 // matrices indexed (state of i, state of j) -- the site-i estimate is
 // J[i][j][k][s] read with s the state of i, the site-j estimate J[j][i][k][s]
 // with s the state of j, i.e. transposed -- each moved to the Ising gauge by
@@ -16,136 +16,242 @@
 
 namespace plm {
 
-// One wave per pair (i < j): both estimates to the Ising gauge, combined
-// (average, elementwise min or max), reduced by the chosen norm over all
-// states or over the non-gap states 0..q-2: Frobenius, l_p (sum of |J|^p to
-// the power 1/p), or the Burkoff divergence sum P ln(P / (f_i f_j)) with
-// P proportional to f_i(k) f_j(l) exp(J(k,l)) (computed with the largest
+// Each wave scores a run of `per` consecutive pairs (i < j, ordered by i, then
+// j): both estimates to the Ising gauge, combined (average, elementwise min or
+// max), reduced by the chosen norm over all states or over the non-gap states
+// 0..q-2: Frobenius, l_p (sum of |J|^p to
+// the power 1/p), or the Burkoff divergence sum P ln(P / (f_i f_j)) with P
+// proportional to f_i(k) f_j(l) exp(J(k,l)) (computed with the largest
 // exponent factored out).
-__global__ __launch_bounds__(64) void pair_score_kernel(const float* __restrict__ J, int32_t N,
-                                                        int32_t q, ScoreOpts o,
-                                                        const double* __restrict__ freq,
-                                                        double* __restrict__ raw) {
-  __shared__ double A[kQMax * kQMax], Bm[kQMax * kQMax];
-  __shared__ double rA[kQMax], cA[kQMax], rB[kQMax], cB[kQMax];
-  const int i = blockIdx.y, j = blockIdx.x;
-  if (j <= i) {
-    if (j == i && threadIdx.x == 0) raw[(size_t)i * N + i] = 0.0;
-    return;
+// Lane 21 h + a holds the elements (state a of i, states 7 h + k of j),
+// k = 0..6, in registers: the site-i block is read straight into them (q
+// contiguous floats at a time), the site-j block through LDS (transposed);
+// the sums over j's states are seven adds and a sum over three lanes, those
+// over i's states the same on the matrix written to LDS and read with the
+// states exchanged.  Every wave uses its own LDS, so nothing waits for the
+// block; the next pair's loads are in flight while the current one is scored.  AVG: the gauge shift is linear, so the average is shifted once; the
+// other combinations shift both estimates.
+// Bound: HBM, the couplings read once (441 MB at N = 500, 92 us at the copy
+// rate); measured there 277 -> 124 us (one wave per block, transposed
+// global reads, every sum q serial LDS reads before).
+constexpr int kScWaves = 4;
+constexpr int kScPer = 7;           // states of j per lane
+constexpr int kScPitch = kQMax + 2;  // row pitch of the FP64 matrix in LDS (odd)
+static_assert(3 * kScPer == kQMax, "three lanes cover the states of j");
+
+// orders a wave's LDS accesses (they execute in program order; this keeps the compiler's order)
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <bool AVG, int NORM>
+__global__ __launch_bounds__(64 * kScWaves) void pair_score_kernel(const float* __restrict__ J, int32_t N, int32_t q,
+                                                                   int32_t npairs, int32_t per, ScoreOpts o,
+                                                                   const double* __restrict__ freq,
+                                                                   double* __restrict__ raw) {
+  constexpr int NM = AVG ? 1 : 2;  // matrices moved to the Ising gauge
+  __shared__ float T[kScWaves][kQMax * kQMax];
+  __shared__ double M[kScWaves][kQMax * kScPitch];
+  __shared__ double mean[kScWaves][kQMax];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < N; k += gridDim.x * blockDim.x) raw[(size_t)k * N + k] = 0.0;
+  const int p0 = (blockIdx.x * kScWaves + wid) * per, p1 = min(npairs, p0 + per);
+  if (p0 >= p1) return;
+  // row i of pair p0: the last i whose first pair i (2 N - 1 - i) / 2 is <= p0
+  int i, j;
+  {
+    const double b = 2.0 * N - 1.0;
+    i = (int)(0.5 * (b - sqrt(b * b - 8.0 * (double)p0)));
+    auto first = [&](int r) { return (int)((int64_t)r * (2 * (int64_t)N - 1 - r) / 2); };
+    while (first(i) > p0) --i;
+    while (first(i + 1) <= p0) ++i;
+    j = i + 1 + (p0 - first(i));
+    i = __builtin_amdgcn_readfirstlane(i);
+    j = __builtin_amdgcn_readfirstlane(j);
   }
-  const int lane = threadIdx.x, qq = q * q;
-  const size_t bij = ((size_t)i * N + j) * qq, bji = ((size_t)j * N + i) * qq;
-  for (int e = lane; e < qq; e += 64) {
-    const int a = e / q, c = e - a * q;  // a: state of i, c: state of j
-    A[e] = (double)J[bij + (size_t)c * q + a];
-    Bm[e] = (double)J[bji + (size_t)a * q + c];
-  }
-  __syncthreads();
-  if (lane < q) {
-    double s1 = 0.0, s2 = 0.0, s3 = 0.0, s4 = 0.0;
-    for (int c = 0; c < q; ++c) { s1 += A[lane * q + c]; s3 += Bm[lane * q + c]; }
-    for (int a = 0; a < q; ++a) { s2 += A[a * q + lane]; s4 += Bm[a * q + lane]; }
-    rA[lane] = s1 / q;
-    cA[lane] = s2 / q;
-    rB[lane] = s3 / q;
-    cB[lane] = s4 / q;
-  }
-  __syncthreads();
-  double gA = 0.0, gB = 0.0;
-  for (int a = 0; a < q; ++a) { gA += rA[a]; gB += rB[a]; }
-  gA /= q;
-  gB /= q;
-  const int qs = o.exclude_gap ? q - 1 : q;  // states summed over
-  auto combined = [&](int e) {
-    const int a = e / q, c = e - a * q;
-    const double ga = A[e] - cA[c] - rA[a] + gA;
-    const double gb = Bm[e] - cB[c] - rB[a] + gB;
-    return o.combine == PLM_COMBINE_MIN ? fmin(ga, gb) : o.combine == PLM_COMBINE_MAX ? fmax(ga, gb)
-                                                                                         : 0.5 * (ga + gb);
-  };
-  auto included = [&](int e) {
-    const int a = e / q, c = e - a * q;
-    return a < qs && c < qs;
-  };
-  double out = 0.0;
-  if (o.norm == PLM_NORM_BURKOFF) {
-    double mx = -INFINITY;
-    for (int e = lane; e < qq; e += 64)
-      if (included(e)) mx = fmax(mx, combined(e));
-    for (int d = 32; d > 0; d >>= 1) mx = fmax(mx, __shfl_xor(mx, d, 64));
-    double z = 0.0, zv = 0.0;
-    for (int e = lane; e < qq; e += 64)
-      if (included(e)) {
-        const int a = e / q, c = e - a * q;
-        const double v = combined(e);
-        const double t = freq[(size_t)i * q + a] * freq[(size_t)j * q + c] * exp(v - mx);
-        z += t;
-        zv += t * v;
-      }
-    for (int d = 32; d > 0; d >>= 1) {
-      z += __shfl_xor(z, d, 64);
-      zv += __shfl_xor(zv, d, 64);
+  const int qq = q * q, qs = o.exclude_gap ? q - 1 : q;  // states summed over
+  const int h = lane / kQMax, a = lane - h * kQMax, c0 = kScPer * h;
+  const bool act = h < 3 && a < q;
+  // the other two lanes of this state
+  const int l1 = h < 3 ? (h + 1) % 3 * kQMax + a : lane, l2 = h < 3 ? (h + 2) % 3 * kQMax + a : lane;
+  auto sum3 = [&](double v) { return v + (__shfl(v, l1, 64) + __shfl(v, l2, 64)); };
+  const double dq = (double)q;
+  float xi[kScPer], t[kScPer];
+  auto load = [&](int ii, int jj) {
+    const float* Jij = J + ((size_t)ii * N + jj) * qq;
+    const float* Jji = J + ((size_t)jj * N + ii) * qq;
+#pragma unroll
+    for (int k = 0; k < kScPer; ++k) {
+      xi[k] = act && c0 + k < q ? Jij[(c0 + k) * q + a] : 0.f;
+      t[k] = lane + 64 * k < qq ? Jji[lane + 64 * k] : 0.f;
     }
-    out = z > 0.0 ? zv / z - mx - log(z) : 0.0;
-  } else {
-    const bool lp = o.norm == PLM_NORM_LP;
-    double ss = 0.0;
-    for (int e = lane; e < qq; e += 64)
-      if (included(e)) {
-        const double v = combined(e);
-        ss += lp ? pow(fabs(v), o.p) : v * v;
+  };
+  load(i, j);
+  for (int p = p0; p < p1; ++p) {
+    const int ci = i, cj = j;
+    float xc[kScPer];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < kScPer; ++k) {
+      xc[k] = xi[k];
+      if (lane + 64 * k < qq) T[wid][lane + 64 * k] = t[k];
+    }
+    if (++j == N) {
+      ++i;
+      j = i + 1;
+    }
+    if (p + 1 < p1) load(i, j);
+    wave_sync();
+    double x[NM][kScPer];
+#pragma unroll
+    for (int k = 0; k < kScPer; ++k) {
+      const double y = act && c0 + k < q ? (double)T[wid][a * q + c0 + k] : 0.0;
+      x[0][k] = AVG ? 0.5 * ((double)xc[k] + y) : (double)xc[k];
+      if (!AVG) x[NM - 1][k] = y;
+    }
+#pragma unroll
+    for (int z = 0; z < NM; ++z) {
+      double r = 0.0, s = 0.0, g = 0.0, cm[kScPer];
+      if (z) wave_sync();
+#pragma unroll
+      for (int k = 0; k < kScPer; ++k) {
+        r += x[z][k];
+        if (act && c0 + k < q) M[wid][(c0 + k) * kScPitch + a] = x[z][k];
       }
-    for (int d = 32; d > 0; d >>= 1) ss += __shfl_xor(ss, d, 64);
-    out = lp ? pow(ss, 1.0 / o.p) : sqrt(ss);
-  }
-  if (lane == 0) {
-    raw[(size_t)i * N + j] = out;
-    raw[(size_t)j * N + i] = out;
+      r = sum3(r) / dq;
+      wave_sync();
+      // here a is the state of j, c0 + k the states of i
+#pragma unroll
+      for (int k = 0; k < kScPer; ++k)
+        if (act && c0 + k < q) s += M[wid][a * kScPitch + c0 + k];
+      s = sum3(s) / dq;
+      if (act && h == 0) mean[wid][a] = s;
+      wave_sync();
+#pragma unroll
+      for (int k = 0; k < kScPer; ++k) {
+        cm[k] = c0 + k < q && h < 3 ? mean[wid][c0 + k] : 0.0;
+        g += cm[k];
+      }
+      g = sum3(g) / dq;
+#pragma unroll
+      for (int k = 0; k < kScPer; ++k) x[z][k] = x[z][k] - cm[k] - r + g;
+    }
+    double v[kScPer];
+    bool in[kScPer];
+#pragma unroll
+    for (int k = 0; k < kScPer; ++k) {
+      v[k] = AVG ? x[0][k]
+                 : o.combine == PLM_COMBINE_MIN ? fmin(x[0][k], x[NM - 1][k]) : fmax(x[0][k], x[NM - 1][k]);
+      in[k] = act && a < qs && c0 + k < qs;
+    }
+    double out = 0.0;
+    if constexpr (NORM == PLM_NORM_BURKOFF) {
+      double mx = -INFINITY;
+#pragma unroll
+      for (int k = 0; k < kScPer; ++k)
+        if (in[k]) mx = fmax(mx, v[k]);
+      for (int d = 32; d > 0; d >>= 1) mx = fmax(mx, __shfl_xor(mx, d, 64));
+      double z = 0.0, zv = 0.0;
+      const double fi = act ? freq[(size_t)ci * q + a] : 0.0;
+#pragma unroll
+      for (int k = 0; k < kScPer; ++k)
+        if (in[k]) {
+          const double w = fi * freq[(size_t)cj * q + c0 + k] * exp(v[k] - mx);
+          z += w;
+          zv += w * v[k];
+        }
+      for (int d = 32; d > 0; d >>= 1) {
+        z += __shfl_xor(z, d, 64);
+        zv += __shfl_xor(zv, d, 64);
+      }
+      out = z > 0.0 ? zv / z - mx - log(z) : 0.0;
+    } else {
+      constexpr bool lp = NORM == PLM_NORM_LP;
+      double ss = 0.0;
+#pragma unroll
+      for (int k = 0; k < kScPer; ++k)
+        if (in[k]) ss += lp ? pow(fabs(v[k]), o.p) : v[k] * v[k];
+      for (int d = 32; d > 0; d >>= 1) ss += __shfl_xor(ss, d, 64);
+      out = lp ? pow(ss, 1.0 / o.p) : sqrt(ss);
+    }
+    if (lane == 0) {
+      raw[(size_t)ci * N + cj] = out;
+      raw[(size_t)cj * N + ci] = out;
+    }
   }
 }
 
-// row sums of the raw scores, parked on the diagonal of the output until the last pass
-__global__ void rowsum_kernel(const double* __restrict__ fn, int32_t N, double* __restrict__ cfn) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
+// row sums of the raw scores, one wave per row, parked on the diagonal of the
+// output until the correction has read them
+__global__ __launch_bounds__(64) void rowsum_kernel(const double* __restrict__ fn, int32_t N,
+                                                    double* __restrict__ cfn) {
+  const int i = blockIdx.x;
+  const double* row = fn + (size_t)i * N;
   double s = 0.0;
-  for (int j = 0; j < N; ++j) s += fn[(size_t)i * N + j];
-  cfn[(size_t)i * N + i] = s;
+#pragma unroll 4
+  for (int j = threadIdx.x; j < N; j += 64) s += row[j];
+  for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+  if (threadIdx.x == 0) cfn[(size_t)i * N + i] = s;
 }
 
 // Correction of the symmetric raw scores with means over all N positions:
-// average product (eq. corr_norm2), average sum (eq. corr_normsum) or none;
-// zero diagonal.
-__global__ __launch_bounds__(1024) void correct_kernel(const double* __restrict__ fn, int32_t N,
-                                                       int32_t mode, double* __restrict__ cfn) {
-  __shared__ double all_s;
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int i = 0; i < N; ++i) t += cfn[(size_t)i * N + i];
-    all_s = t / ((double)N * (double)N);
+// average product (eq. corr_norm2), average sum (eq. corr_normsum) or none.
+// kCorRows rows per block; every block adds the row sums parked on the
+// diagonal in the same order, and leaves the diagonal alone (other blocks
+// still read it: diag_zero_kernel clears it).  Measured at N = 500: 333 -> 8 us
+// (one block for all pairs before), the row sums 105 -> 5 us (one thread a row).
+constexpr int kCorRows = 4;
+__global__ __launch_bounds__(256) void correct_kernel(const double* __restrict__ fn, int32_t N, int32_t mode,
+                                                      double* __restrict__ cfn) {
+  __shared__ double red[4];
+  double t = 0.0;
+  for (int k = threadIdx.x; k < N; k += blockDim.x) t += cfn[(size_t)k * N + k];
+  const double all = block_sum_f64(t, red) / ((double)N * (double)N);
+  const int i0 = blockIdx.x * kCorRows, i1 = min(N, i0 + kCorRows);
+  for (int j = threadIdx.x; j < N; j += blockDim.x) {
+    const double rj = cfn[(size_t)j * N + j] / (double)N;
+    for (int i = i0; i < i1; ++i) {
+      if (i == j) continue;
+      const size_t e = (size_t)i * N + j;
+      const double ri = cfn[(size_t)i * N + i] / (double)N;
+      cfn[e] = mode == PLM_CORR_NONE ? fn[e]
+               : mode == PLM_CORR_ASC ? fn[e] - ri - rj + all
+               : all == 0.0           ? 0.0
+                                      : fn[e] - ri * rj / all;
+    }
   }
-  __syncthreads();
-  const double all = all_s;
-  const size_t NN = (size_t)N * N;
-  for (size_t e = threadIdx.x; e < NN; e += blockDim.x) {
-    const int i = (int)(e / N), j = (int)(e - (size_t)i * N);
-    if (i == j) continue;
-    const double ri = cfn[(size_t)i * N + i] / (double)N, rj = cfn[(size_t)j * N + j] / (double)N;
-    double v;
-    if (mode == PLM_CORR_NONE) v = fn[e];
-    else if (mode == PLM_CORR_ASC) v = fn[e] - ri - rj + all;
-    else v = all == 0.0 ? 0.0 : fn[e] - ri * rj / all;
-    cfn[e] = v;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < N; i += blockDim.x) cfn[(size_t)i * N + i] = 0.0;
 }
+
+__global__ void diag_zero_kernel(double* cfn, int32_t N) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < N) cfn[(size_t)i * N + i] = 0.0;
+}
+
+constexpr int kScResident = 256 * 6 * kScWaves;  // waves: six blocks (LDS) on each CU
 
 hipError_t launch_score_ex(const float* J, int32_t N, int32_t q, const ScoreOpts& o,
                            const double* freq, double* raw, double* cor, hipStream_t st) {
-  hipLaunchKernelGGL(pair_score_kernel, dim3(N, N), dim3(64), 0, st, J, N, q, o, freq, raw);
-  hipLaunchKernelGGL(rowsum_kernel, dim3((N + 255) / 256), dim3(256), 0, st, raw, N, cor);
-  hipLaunchKernelGGL(correct_kernel, dim3(1), dim3(1024), 0, st, raw, N, o.correction, cor);
+  // runs of pairs for as many waves as stay resident: a block per four pairs
+  // spent as long being dispatched as scoring (198 us at N = 500)
+  const int64_t npairs = (int64_t)N * (N - 1) / 2;
+  if (npairs > 0x7fffffff - 64) return hipErrorInvalidValue;
+  const int64_t per = (npairs + kScResident - 1) / kScResident;
+  const dim3 grid((unsigned)((npairs + kScWaves * per - 1) / (kScWaves * per))), block(64 * kScWaves);
+  auto launch = [&](auto avg, auto norm) {
+    hipLaunchKernelGGL((pair_score_kernel<decltype(avg)::value, decltype(norm)::value>), grid, block, 0, st, J, N, q,
+                       (int32_t)npairs, (int32_t)per, o, freq, raw);
+  };
+  auto launch_norm = [&](auto avg) {
+    if (o.norm == PLM_NORM_BURKOFF) launch(avg, std::integral_constant<int, PLM_NORM_BURKOFF>{});
+    else if (o.norm == PLM_NORM_LP) launch(avg, std::integral_constant<int, PLM_NORM_LP>{});
+    else launch(avg, std::integral_constant<int, PLM_NORM_FROB>{});
+  };
+  if (o.combine == PLM_COMBINE_AVG) launch_norm(std::true_type{});
+  else launch_norm(std::false_type{});
+  hipLaunchKernelGGL(rowsum_kernel, dim3(N), dim3(64), 0, st, raw, N, cor);
+  hipLaunchKernelGGL(correct_kernel, dim3((N + kCorRows - 1) / kCorRows), dim3(256), 0, st, raw, N, o.correction, cor);
+  hipLaunchKernelGGL(diag_zero_kernel, dim3((N + 255) / 256), dim3(256), 0, st, cor, N);
   return hipGetLastError();
 }
 
@@ -161,8 +267,10 @@ hipError_t launch_score(const float* J, int32_t N, int32_t q, double* fn, double
 }
 
 // Reweighted single-site frequencies f_i(k) = sum_b w_b [sigma_i^b = k] / B_eff:
-// one block per column; per-thread FP64 counters in LDS, then a fixed-order
-// sum over the threads.
+// one block per column; per-thread FP64 counters in LDS (eight rows' loads in
+// flight per thread), then a fixed-order sum over the threads, eight lanes per
+// state.  Bound: load latency (N = 200, B = 10 000: 29 -> 16 us; one row in
+// flight per thread and 256 serial adds per state before).
 __global__ __launch_bounds__(256) void freq_kernel(const uint8_t* __restrict__ msa, int32_t B,
                                                    int32_t N, int32_t q,
                                                    const double* __restrict__ w,
@@ -171,15 +279,28 @@ __global__ __launch_bounds__(256) void freq_kernel(const uint8_t* __restrict__ m
   __shared__ double cnt[256 * kQMax];
   const int i = blockIdx.x, t = threadIdx.x;
   for (int k = 0; k < kQMax; ++k) cnt[t * kQMax + k] = 0.0;
-  for (int b = t; b < B; b += 256) {
-    const int k = msa[(size_t)b * N + i];
-    if (k < q) cnt[t * kQMax + k] += w[b];
+  constexpr int U = 8;
+  for (int b0 = t; b0 < B; b0 += 256 * U) {
+    int s[U];
+    double wv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b = b0 + 256 * u;
+      s[u] = b < B ? msa[(size_t)b * N + i] : 255;
+      wv[u] = b < B ? w[b] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s[u] < q) cnt[t * kQMax + s[u]] += wv[u];
   }
   __syncthreads();
-  if (t < q) {
+  const int k = t >> 3, p = t & 7;
+  if (k < q) {
     double s = 0.0;
-    for (int u = 0; u < 256; ++u) s += cnt[u * kQMax + t];
-    f[(size_t)i * q + t] = s / *beff;
+#pragma unroll 8
+    for (int u = 0; u < 32; ++u) s += cnt[(8 * u + p) * kQMax + k];
+    for (int d = 4; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+    if (p == 0) f[(size_t)i * q + k] = s / *beff;
   }
 }
 

@@ -47,3 +47,28 @@ def test_reweight_reports_every_bad_symbol(plm, B, N, row, col):
         plm.reweight(_to(msa), theta=0.8)
         with pytest.raises(plm.PlmError):
             plm.sync(DEV)
+
+
+# pairs around the four per block, the smallest alphabet, rows longer than the correction's block
+@pytest.mark.parametrize("N,q", [(2, 2), (4, 21), (5, 3), (66, 21), (259, 4)])
+@pytest.mark.parametrize("combine,corr", [("avg", "apc"), ("min", "asc"), ("max", "none")])
+def test_score_tiles(plm, N, q, combine, corr):
+    from oracle import score_variants as sv
+    print(f"score tiles N={N} q={q} {combine} {corr}", flush=True)
+    J = (0.4 * np.random.default_rng(N + q).standard_normal((N, N, q, q))).astype(np.float32)
+    raw, cor = plm.score(_to(J), combine=combine, correction=corr)
+    raw_o = sv.raw_scores(J.astype(np.float64), combine, "frob", 2.0, False, None)
+    # FP64 sums of the same values in another order
+    np.testing.assert_allclose(raw.cpu().numpy(), raw_o, rtol=1e-9, atol=1e-12)
+    np.testing.assert_allclose(cor.cpu().numpy(), sv.correct(raw_o, corr), rtol=1e-9, atol=1e-11)
+
+
+@pytest.mark.parametrize("B,N,q", [(1, 2, 2), (255, 3, 21), (2048, 5, 21), (2049, 17, 21), (5001, 4, 11)])
+def test_frequencies_sizes(plm, B, N, q):
+    from oracle import score_variants as sv
+    print(f"frequencies B={B} N={N} q={q}", flush=True)
+    rng = np.random.default_rng(B)
+    msa = rng.integers(0, q, size=(B, N), dtype=np.uint8)
+    w = rng.uniform(0.01, 1.0, size=B)
+    f = plm.frequencies(_to(msa), _to(w), _to(np.array([w.sum()])), q)
+    np.testing.assert_allclose(f.cpu().numpy(), sv.frequencies(msa, w, float(w.sum()), q), rtol=1e-12, atol=1e-15)
