@@ -68,8 +68,10 @@ extern "C" {
  * X[b][(i,k)] = [sigma_i^b = k] is exact in BF16; the MFMA paths split the
  * other operand (the couplings W_r[(i,k)][s] = J_ri(s,k) in the forward, the
  * residuals R_b(s) in the backward) into BF16 pieces and accumulate in FP32. */
-#define PLM_PATH_GATHER_FP32 0 /* energies by LDS gather, coupling gradient by a symbol-sorted
-                                  LDS scatter; FP32 arithmetic */
+#define PLM_PATH_GATHER_FP32 0 /* energies by LDS gather, FP32 arithmetic; coupling gradient as an
+                                  int8 MFMA product with the FP32 residuals in 32-bit fixed point,
+                                  round(R * 2^(30 - e)) with max |w_b| <= 2^e, as four signed int8
+                                  digits, accumulated exactly (|dR| <= 2^-31 2^e; any weights) */
 #define PLM_PATH_MFMA_BF16X2 1 /* both directions as MFMA products with hi/lo (two-piece)
                                   operands: 16 significant bits, relative error <= 2^-16 per
                                   coupling and residual (precision/speed trade-off) */
@@ -135,7 +137,7 @@ int plm_reweight(plm_ctx *ctx, const uint8_t *msa, int32_t B, int32_t N, int32_t
  *   gh_out float [N][q]       d f_r / d h_r(s)
  *   gJ_out float [N][N][q][q] d f_r / d J_ri(s,k) at [r][i][k][s]; zero for i == r
  * gh_out / gJ_out may be NULL to skip the gradient (with gJ_out NULL the
- * scatter kernel is not run at all).  grad_scale (device double[N], may be
+ * gradient kernel is not run at all).  grad_scale (device double[N], may be
  * NULL) multiplies the gradient rows of site r by grad_scale[r]: the
  * vector-Jacobian product an automatic-differentiation backward needs.  path
  * is one of PLM_PATH_*.  beff is a device pointer (as written by
@@ -256,7 +258,7 @@ typedef struct {
  * stream the kernels run on), and the number of iterations timed. */
 typedef struct {
   double forward_ms;    /* energies, log-softmax, residuals */
-  double backward_ms;   /* coupling-gradient scatter */
+  double backward_ms;   /* coupling gradient */
   double lbfgs_ms;      /* line search decision, history update, two-loop recursion */
   double total_ms;      /* wall time of the fit on the device stream */
   int64_t iterations;   /* graph replays (or eager iterations) executed */

@@ -4,6 +4,8 @@
 // derivatives, eqs. g_gradh2 / g_gradJ2), and input checks.
 #include <string.h>
 
+#include <algorithm>
+
 #include "plm_internal.h"
 
 namespace plm {
@@ -125,43 +127,93 @@ __global__ void list_tables_kernel(BatchArgs b, const int32_t* list, int32_t fir
   finish_tables(b);
 }
 
-__global__ __launch_bounds__(1024) void objgrad_final_kernel(FinalArgs a) {
-  __shared__ double red[16];
+// Objective and gradient of one listed site (blockIdx.x): the l2 terms added
+// to the data parts, the gradient scaled.  With gridDim.y > 1 (few sites) the
+// gradient's entries are cut into gridDim.y - 1 ranges, one block each, and
+// the last block takes the objective; with gridDim.y == 1 one block does both
+// in one pass over J.  Either way the objective adds the same terms in the
+// same order.  With check set, non-finite h, J or grad_scale raise bit 2 of
+// *check (every site is listed then).  Bound: HBM, 16 bytes per coupling.
+constexpr int kFinThreads = 1024;
+__global__ __launch_bounds__(kFinThreads) void objgrad_final_kernel(FinalArgs a, int32_t* check) {
+  __shared__ double red[kFinThreads / 64];
+  __shared__ double fd_s;
   const int r = a.sites ? a.sites[blockIdx.x] : blockIdx.x;
-  const int q = a.q, N = a.N;
-  const size_t qq = (size_t)q * q, Nqq = (size_t)N * qq;
+  const int q = a.q, N = a.N, tid = threadIdx.x;
+  const int parts = gridDim.y, part = blockIdx.y;
+  const bool grad = a.gJ_out && (parts == 1 || part < parts - 1);
+  const bool obj = part == parts - 1;
+  const int qq = q * q;
+  const size_t Nqq = (size_t)N * qq;
   const double beff = *a.beff;
   const double sc = a.grad_scale ? a.grad_scale[r] : 1.0;
-  double reg = 0.0;
-  for (size_t e = threadIdx.x; e < Nqq; e += blockDim.x) {
-    const size_t i = e / qq;
-    const double v = (double)a.J[(size_t)r * Nqq + e];
-    if (i != (size_t)r) reg += a.lambda_Jp * v * v;
-    if (a.gJ_out)
-      a.gJ_out[(size_t)r * Nqq + e] =
-          (i == (size_t)r) ? 0.f
-                           : (float)(sc * (a.gJ[(size_t)r * Nqq + e] + 2.0 * beff * a.lambda_Jp * v));
-  }
-  if (threadIdx.x < (unsigned)q) {
-    const int s = threadIdx.x;
-    const double v = (double)a.h[(size_t)r * q + s];
-    reg += a.lambda_h * v * v;
-    if (a.gh_out) {
+  const double two_lam = 2.0 * beff * a.lambda_Jp;
+  const size_t self0 = (size_t)r * qq, self1 = self0 + qq;
+  const float* J = a.J + (size_t)r * Nqq;
+  const double* gJ = a.gJ + (size_t)r * Nqq;
+  float* out = a.gJ_out ? a.gJ_out + (size_t)r * Nqq : nullptr;
+  double nan_add = 0.0;
+  if (obj || a.nan_grad) {
+    if (tid < 64) {
       double t = 0.0;
-      for (int k = 0; k < a.tiles; ++k) t += a.gh_part[((size_t)k * N + r) * kSlot + s];
-      a.gh_out[(size_t)r * q + s] = (float)(sc * (t + 2.0 * beff * a.lambda_h * v));
+      for (int k = tid; k < a.tiles; k += 64) t += a.f_part[(size_t)k * N + r];
+      for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+      if (tid == 0) fd_s = t;
+    }
+    __syncthreads();
+    if (a.nan_grad && fd_s != fd_s) nan_add = fd_s;
+  }
+  const int ngrad = parts == 1 ? 1 : parts - 1;
+  const size_t csz = (Nqq + ngrad - 1) / ngrad;
+  const size_t beg = obj ? 0 : (size_t)part * csz, end = obj ? Nqq : (beg + csz < Nqq ? beg + csz : Nqq);
+  double reg = 0.0;
+  bool bad = false;
+  constexpr int U = 4;
+  for (size_t e0 = beg + tid; e0 < end; e0 += (size_t)U * kFinThreads) {
+    float jv[U];
+    double gv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t e = e0 + (size_t)u * kFinThreads < end ? e0 + (size_t)u * kFinThreads : end - 1;
+      jv[u] = J[e];
+      gv[u] = grad ? gJ[e] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t e = e0 + (size_t)u * kFinThreads;
+      if (e >= end) continue;
+      const double v = (double)jv[u];
+      const bool self = e >= self0 && e < self1;
+      bad |= !isfinite(jv[u]);
+      if (!self) reg += a.lambda_Jp * v * v;
+      if (grad) out[e] = self ? 0.f : (float)(sc * (gv[u] + two_lam * v + nan_add));
     }
   }
-  reg = block_sum_f64(reg, red);
-  if (threadIdx.x == 0) {
-    double f = 0.0;
-    for (int k = 0; k < a.tiles; ++k) f += a.f_part[(size_t)k * N + r];
-    a.f_out[r] = f + beff * reg;
+  if (obj) {
+    if (tid < q) {
+      const double v = (double)a.h[(size_t)r * q + tid];
+      bad |= !isfinite(v);
+      reg += a.lambda_h * v * v;
+      if (a.gh_out) {
+        double t = 0.0;
+#pragma unroll 8
+        for (int k = 0; k < a.tiles; ++k) t += a.gh_part[((size_t)k * N + r) * kSlot + tid];
+        a.gh_out[(size_t)r * q + tid] = (float)(sc * (t + 2.0 * beff * a.lambda_h * v));
+      }
+    }
+    reg = block_sum_f64(reg, red);
+    if (tid == 0) a.f_out[r] = fd_s + beff * reg;
   }
+  bad |= !isfinite(sc);
+  if (check && bad) atomicOr(check, 2);
 }
 
-hipError_t launch_objgrad_final(const FinalArgs& a, int32_t nsites, hipStream_t st) {
-  hipLaunchKernelGGL(objgrad_final_kernel, dim3(nsites), dim3(1024), 0, st, a);
+// One block per site fills the chip from some five hundred sites on (two
+// blocks of 1024 threads per CU); below, a second pass over J for the
+// objective is cheaper than idle CUs.
+hipError_t launch_objgrad_final(const FinalArgs& a, int32_t nsites, int32_t* check, hipStream_t st) {
+  const int parts = nsites >= 256 ? 1 : 1 + std::min(8, (512 + nsites - 1) / nsites);
+  hipLaunchKernelGGL(objgrad_final_kernel, dim3(nsites, a.gJ_out ? parts : 1), dim3(kFinThreads), 0, st, a, check);
   return hipGetLastError();
 }
 
@@ -187,6 +239,39 @@ hipError_t launch_check_f64(const double* p, size_t n, int32_t* flag, hipStream_
   size_t blocks = (n + 255) / 256;
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL(nonfinite_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, st, p, n, flag);
+  return hipGetLastError();
+}
+
+// One block: raises bit 2 of *flag for a non-finite weight, and writes the
+// smallest exponent e with every |w_b| <= 2^e (0 for all-zero weights).
+__global__ __launch_bounds__(1024) void weight_exponent_kernel(const double* __restrict__ w, int32_t B, int32_t* wexp,
+                                                               int32_t* flag) {
+  __shared__ double red[16];
+  double mx = 0.0;
+  bool bad = false;
+#pragma unroll 8
+  for (int b = threadIdx.x; b < B; b += 1024) {
+    const double v = fabs(w[b]);
+    bad |= !isfinite(v);
+    mx = fmax(mx, v);
+  }
+  if (bad && flag) atomicOr(flag, 2);
+  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < 16; ++k) mx = fmax(mx, red[k]);
+    int e = 0;
+    if (mx > 0.0 && isfinite(mx)) {
+      const double m = frexp(mx, &e);  // m in [0.5, 1)
+      if (m == 0.5) --e;
+    }
+    *wexp = e;
+  }
+}
+
+hipError_t launch_weight_exponent(const double* w, int32_t B, int32_t* wexp, int32_t* flag, hipStream_t st) {
+  hipLaunchKernelGGL(weight_exponent_kernel, dim3(1), dim3(1024), 0, st, w, B, wexp, flag);
   return hipGetLastError();
 }
 

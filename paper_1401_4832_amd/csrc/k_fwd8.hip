@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kFIThreads) void fwd_i8_kernel(BatchArgs b) {
   __shared__ double wrow[kFIWaves * 32];
   __shared__ uint8_t srow[kFIWaves * 96];
   __shared__ int32_t item_s;
-  int32_t qi = 0;
+  int32_t qi = -1;
   const int32_t total = total_items(b, KIND_FWD);
   for (;;) {
     if (threadIdx.x == 0) item_s = next_item(b.ctr + KIND_FWD * kQueues, total, qi);

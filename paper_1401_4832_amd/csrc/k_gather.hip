@@ -1,19 +1,19 @@
-// k_gather.hip -- FP32 gather/scatter evaluation of the per-site objective and
-// gradient of asymmetric plmDCA (sec. 3.4 step 3: eqs. g_regdef2, g_gradh2,
+// k_gather.hip -- gather evaluation of the per-site objective and residuals of
+// asymmetric plmDCA (sec. 3.4 step 3: eqs. g_regdef2, g_gradh2,
 // g_gradJ2) for many sites at once.
 //
 // Forward (one block = one site r x a tile of sequences): the site's coupling
-// slice J_r is streamed through LDS sixteen columns at a time; each lane adds
+// slice J_r is streamed through LDS eight columns at a time; each lane adds
 // J_ri(s, sigma_i^b) into the energy E_b(s) of its (sequence, state) pair
-// (eq. condpfinal), then a 21-lane segmented reduction gives log Z_b, the
-// objective term w_b (log Z_b - E_b(sigma_r^b)) and the residual
-// R_b(s) = w_b (P_b(s) - [sigma_r^b = s]), which is written to HBM.
-//
-// Backward (one block = one site r x 24 alignment columns, all sequences):
-// dJ_ri(s,k) = sum_b [sigma_i^b = k] R_b(s).  Each wave owns three columns, so
-// its read-modify-write scatter into LDS never races with another wave, and
-// the three 21-lane slots of a wave write three bank-disjoint copies of each
-// row.  FP32 LDS partials are folded into FP64 registers every 768 sequences.
+// (eq. condpfinal); then every lane takes one sequence through its states:
+// log Z_b, the objective term w_b (log Z_b - E_b(sigma_r^b)) and the residuals
+// R_b(s) = w_b (P_b(s) - [sigma_r^b = s]), which leave in the form the path's
+// gradient kernel reads (k_mfma.hip).
+// Bound: LDS, one 4-byte word per (row, column, state): 32 a clock and CU,
+// with the symbols 25.  Measured, all sites at N = 500, B = 50 000: 24 -> 19 ms
+// (the softmax over 21 lanes by shuffles, a row at a time with its loads inside
+// the loop and byte stores of the digits, took a third of it), N = 150,
+// B = 8000: 830 -> 457 us, N = 40, B = 500: 66 -> 23 us.
 #include "plm_internal.h"
 
 namespace plm {
@@ -54,12 +54,13 @@ hipError_t launch_pad_msa(const uint8_t* msa, int32_t B, int32_t N, int32_t q, u
 int32_t forward_tile_seqs(int32_t nb) { return kFwdWaves * kSlots * nb; }
 
 // J chunk of the gather forward: kFwdPos columns of kQMax rows of 64 floats;
-// the same LDS later parks 16 energies per lane (16 waves x 16 x 64 floats).
+// the same LDS later parks the energies of 48 rows per wave.
 constexpr int kFwdPos = 8;
 constexpr int kPosBytes = kQMax * kRowF * 4;  // 5376
 static_assert((kFwdPos - 1) * kPosBytes + 20 * 256 + 255 < 65536, "LDS offsets fit the immediate field");
 constexpr int kFwdJFloats = kFwdPos * kQMax * kRowF;
-constexpr int kFwdParkFloats = kFwdWaves * 16 * 64;
+constexpr int kParkRows = 16 * kSlots;  // rows of a wave parked at a time
+constexpr int kFwdParkFloats = kFwdWaves * kParkRows * kSlot;
 // LDS floats of the forward block: the J chunk (with LO, as the FP64 sums of
 // the couplings' high and low words, twice the bytes), or the parked energies
 // (AT values)
@@ -100,26 +101,38 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
 
   const size_t Jr = (size_t)r * N * qq;
   const int nchunks = (N + kFwdPos - 1) / kFwdPos;
+  // a wave whose rows all lie past the alignment's (padded to three) has
+  // nothing to gather: no row of it is read by the gradient (the rows of the
+  // last gradient chunk past the alignment are zeroed once per alignment)
+  const bool live = tile0 + wid * (NB * kSlots) < a.B3;
   const char* L = reinterpret_cast<const char*>(lds);
   // LDS byte address of row (p, sigma), this lane's word: p * kPosBytes (an
   // immediate offset) + sigma * 256 + 4 * lane, where the last two are one
   // byte permute: byte 0 = 4 * lane (< 256), byte 1 = the symbol byte
   const uint32_t lane4 = 4u * lane;
   // the next chunk's couplings and symbols travel in registers while the
-  // current chunk is gathered
+  // current chunk is gathered.  Entry e of a chunk (column p, row k, state s)
+  // is e values after the chunk's first in J_r, whatever the column
   constexpr int kJPer = (kFwdPos * kQMax * kQMax + kFwdThreads - 1) / kFwdThreads;
   constexpr int kSPer = (tileSeq + kFwdThreads - 1) / kFwdThreads;
   float jv[kJPer], jl[LO ? kJPer : 1];
   uint2 sv[kSPer];
+  int jdst[kJPer];  // the entry's word in the staged chunk; -1 past its end
+#pragma unroll
+  for (int k = 0; k < kJPer; ++k) {
+    const int e = tid + k * kFwdThreads;
+    const int p = e / qq, rem = e - p * qq, kk = rem / q;
+    jdst[k] = e < kFwdPos * qq ? (p * kQMax + kk) * kRowF + rem - kk * q : -1;
+  }
+  const int Nqq = N * qq, self0 = r * qq;
   auto load = [&](int c) {
+    const int c0 = c * kFwdPos * qq;
 #pragma unroll
     for (int k = 0; k < kJPer; ++k) {
-      const int e = tid + k * kFwdThreads;
-      const int p = e / qq, rem = e - p * qq;
-      const int i = c * kFwdPos + p;
-      const bool in = e < kFwdPos * qq && i < N && i != r;
-      jv[k] = in ? gmem(a.J)[Jr + (size_t)i * qq + rem] : 0.f;
-      if (LO) jl[k] = in ? gmem(a.J_lo)[Jr + (size_t)i * qq + rem] : 0.f;
+      const int e = c0 + tid + k * kFwdThreads;
+      const bool in = jdst[k] >= 0 && e < Nqq && (unsigned)(e - self0) >= (unsigned)qq;
+      jv[k] = in ? gmem(a.J)[Jr + e] : 0.f;
+      if (LO) jl[k] = in ? gmem(a.J_lo)[Jr + e] : 0.f;
     }
 #pragma unroll
     for (int k = 0; k < kSPer; ++k) {
@@ -131,23 +144,21 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
   auto store = [&]() {
 #pragma unroll
     for (int k = 0; k < kJPer; ++k) {
-      const int e = tid + k * kFwdThreads;
-      if (e < kFwdPos * qq) {
-        const int p = e / qq, rem = e - p * qq, kk = rem / q, ss = rem - kk * q;
+      if (jdst[k] >= 0) {
         if (LO) {
           // the pair's exact FP64 sum (two 24-bit significands 2^24 apart fit
           // 53 bits), one 8-byte word per entry: the gather then reads one
           // word and adds once per term
-          double* row = reinterpret_cast<double*>(lds) + (p * kQMax + kk) * kRowF;
+          double* row = reinterpret_cast<double*>(lds) + jdst[k];
           const double v = (double)jv[k] + (double)jl[k];
-          row[ss] = v;
-          row[ss + kSlot] = v;
-          row[ss + 2 * kSlot] = v;
+          row[0] = v;
+          row[kSlot] = v;
+          row[2 * kSlot] = v;
         } else {
-          float* row = lds + (p * kQMax + kk) * kRowF;
-          row[ss] = jv[k];
-          row[ss + kSlot] = jv[k];
-          row[ss + 2 * kSlot] = jv[k];
+          float* row = lds + jdst[k];
+          row[0] = jv[k];
+          row[kSlot] = jv[k];
+          row[2 * kSlot] = jv[k];
         }
       }
     }
@@ -163,127 +174,211 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
     store();
     __syncthreads();
     if (c + 1 < nchunks) load(c + 1);
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const uint2 sg = sgl[tw + 3 * j];
-      // two accumulation chains (even and odd columns)
-      AT acc0 = E[j], acc1 = (AT)0;
+    if (!live) continue;
+    // row j + 1's words are read while row j's are added, and its symbols one
+    // row earlier still: one row at a time left the LDS idle between a row's
+    // reads and its sums
+    AT v[2][kFwdPos];
+    auto gather = [&](uint2 sg, AT (&d)[kFwdPos]) {
 #pragma unroll
       for (int p = 0; p < kFwdPos; ++p) {
         const uint32_t word = p < 4 ? sg.x : sg.y;
         const uint32_t addr = __builtin_amdgcn_perm(lane4, word, 0x0c0c0004u | ((uint32_t)(p & 3) << 8));
-        AT v;
         if (LO) {
           // 8-byte rows: twice the float row's byte address, from a base per
           // four positions so that the offset fits the immediate field
           const char* L2 = L + (p < 4 ? 0 : 4 * 2 * kPosBytes);
-          v = *reinterpret_cast<const double*>(L2 + 2 * addr + (p & 3) * 2 * kPosBytes);
+          d[p] = *reinterpret_cast<const double*>(L2 + 2 * addr + (p & 3) * 2 * kPosBytes);
         } else {
-          v = (AT)*reinterpret_cast<const float*>(L + addr + p * kPosBytes);
+          d[p] = (AT)*reinterpret_cast<const float*>(L + addr + p * kPosBytes);
         }
-        if (p == 1) acc1 = v;
-        else if (p & 1) acc1 += v;
-        else acc0 += v;
+      }
+    };
+    gather(sgl[tw], v[0]);
+    uint2 sn = sgl[tw + 3];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const uint2 sc = sn;
+      if (j + 2 < NB) sn = sgl[tw + 3 * (j + 2)];
+      if (j + 1 < NB) gather(sc, v[(j + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      // two accumulation chains (even and odd columns)
+      const AT(&d)[kFwdPos] = v[j & 1];
+      AT acc0 = E[j], acc1 = d[1];
+#pragma unroll
+      for (int p = 0; p < kFwdPos; ++p) {
+        if (p == 1) continue;
+        if (p & 1) acc1 += d[p];
+        else acc0 += d[p];
       }
       E[j] = acc0 + acc1;
-      // keep one row's loads in flight at a time, so rows do not pile up in registers
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 
-  // log-softmax over the 21 lanes of each slot, objective and residuals.  The
-  // energies are parked in the (now free) LDS sixteen rows at a time so that
-  // the per-row work below runs as a loop rather than unrolled over all rows.
+  // log-softmax, objective and residuals, 48 rows of the wave at a time: their
+  // energies are parked in the (now free) LDS, every lane takes one row through
+  // its states in registers and puts the residuals in the energies' place, then
+  // lane 21 g + s takes state s of the rows 16 g .. 16 g + 15 to the field
+  // gradient and to HBM, sixteen rows of a digit in one store.
   double facc = 0.0, ghacc = 0.0;
-  const int sbase = slotA * kSlot;
-  AT* park = reinterpret_cast<AT*>(lds) + wid * (16 * 64);  // 16 rows x 64 lanes per wave
-#pragma unroll
-  for (int g = 0; g < NB / 16; ++g) {
-    __syncthreads();
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) park[jj * 64 + lane] = E[g * 16 + jj];
-    __syncthreads();
+  const double rscale = a.rfrag == 4 ? ldexp(1.0, kR4ScaleLog2 - *a.wexp) : (double)(1 << kRiScaleLog2);
+  __syncthreads();  // every wave is done with the last chunk
+  AT* park = reinterpret_cast<AT*>(lds) + wid * (kParkRows * kSlot);
 #pragma unroll 1
-    for (int jj = 0; jj < 16; ++jj) {
-      const int b = bw + 3 * (g * 16 + jj);
-      const AT e = act ? park[jj * 64 + lane] : (AT)-INFINITY;
-      AT m = e;
+  for (int g = 0; live && g < NB / 16; ++g) {
+    const int b0 = tile0 + wid * (NB * kSlots) + g * kParkRows;  // the first of the 48 rows
+    // this lane's row: its symbol at the site and its weight
+    const int b = b0 + min(lane, kParkRows - 1);
+    const int sr = gmem(a.msa_cm)[((size_t)(r / kFwdChunk) * a.B_pad + b) * kFwdChunk + r % kFwdChunk];
+    const double wb = b < a.B ? gmem(a.w)[b] : 0.0;
+    if (slot < kSlots) {
+      // (one straight-line copy of the stores per g: the energies stay in registers)
+      with_count<0, NB / 16 - 1>(g, [&](auto gc) {
 #pragma unroll
-      for (int d = 1; d < 32; d <<= 1) {
-        const AT o = __shfl_down(m, d, 64);
-        if (s + d < kSlot) m = fmax(m, o);
-      }
-      m = __shfl(m, sbase, 64);
-      const AT ex = act ? (AT)exp(e - m) : (AT)0;
-      AT sum = ex;
+        for (int jj = 0; jj < 16; ++jj)
+          park[(3 * jj + slot) * kSlot + s] = s < q ? E[decltype(gc)::value * 16 + jj] : (AT)-INFINITY;
+      });
+    }
+    wave_sync();
+    if (lane < kParkRows) {
+      AT* row = park + lane * kSlot;
+      // four states at a time (fences keep the others in LDS, not in registers)
+      AT m = row[kSlot - 1];
 #pragma unroll
-      for (int d = 1; d < 32; d <<= 1) {
-        const AT o = __shfl_down(sum, d, 64);
-        if (s + d < kSlot) sum += o;
+      for (int k = 0; k < kSlot - 1; ++k) m = fmax(m, row[k]);
+      const AT esr = row[sr];
+      AT part[5];
+#pragma unroll
+      for (int k = 0; k < 5; ++k) {
+        AT x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          x[u] = (AT)exp(row[4 * k + u] - m);
+          row[4 * k + u] = x[u];
+        }
+        part[k] = (x[0] + x[1]) + (x[2] + x[3]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      sum = __shfl(sum, sbase, 64);
+      const AT xl = (AT)exp(row[kSlot - 1] - m);
+      row[kSlot - 1] = xl;
+      // pairwise sum: a binary tree over the first sixteen states and over the last five
+      const AT sum = ((part[0] + part[1]) + (part[2] + part[3])) + (part[4] + xl);
       const AT lse = m + (AT)log(sum);
-      const int sr = gmem(a.msa_cm)[((size_t)(r / kFwdChunk) * a.B_pad + b) * kFwdChunk + r % kFwdChunk];
-      const double wb = (slot < kSlots && b < a.B) ? gmem(a.w)[b] : 0.0;
-      const AT P = ex / sum;
-      const AT Rv = act ? (AT)wb * (P - (s == sr ? (AT)1 : (AT)0)) : (AT)0;
-      if (act && s == sr) facc += wb * (double)(lse - e);
-      ghacc += (double)Rv;
-      if (a.rfrag == 3) {
-        // two sets of int8 digits, in the int8 gradient's fragment order for
-        // every row of the tile (zero past B): v = round(R * 2^22) and, in the
-        // second set, the remainder's round((R * 2^22 - v) * 2^22) -- R to
-        // 2^-45 absolute; each set's integer sums are exact
-        if (slot < kSlots) {
-          const double x = (double)Rv * (double)(1 << kRiScaleLog2);
-          const double vh = rint(x);
-          const int vv[2] = {(int)vh, (int)rint((x - vh) * (double)(1 << kRiScaleLog2))};
-          auto Ri = gmem_w(reinterpret_cast<int8_t*>(a.R));
-          const size_t ix = rifrag_index(r, a.B_pad >> 8, b, s);
-          const size_t lo_off = (size_t)a.N * (a.B_pad >> 8) * kRiChunkBytes;
+      facc += wb * (double)(lse - esr);
+      // P = x / sum by the reciprocal with one correction step
+      const AT inv = (AT)1 / sum, wa = (AT)wb;
 #pragma unroll
-          for (int z = 0; z < 2; ++z) {
-            const int v = vv[z];
-            const int lo = (int)(int8_t)(v & 255);
-            const int v1 = (v - lo) >> 8;
-            const int mid = (int)(int8_t)(v1 & 255);
-            const int hi = (v1 - mid) >> 8;
-            Ri[z * lo_off + ix] = (int8_t)hi;
-            Ri[z * lo_off + ix + kRiDigitBytes] = (int8_t)mid;
-            Ri[z * lo_off + ix + 2 * kRiDigitBytes] = (int8_t)lo;
-          }
-        }
-      } else if (a.rfrag == 2) {
-        // int8 digits of round(R * 2^22) in the int8 gradient's fragment
-        // order, for every row of the tile (zero past B)
-        if (slot < kSlots) {
-          const int v = (int)rintf((float)Rv * (float)(1 << kRiScaleLog2));
-          const int lo = (int)(int8_t)(v & 255);
-          const int v1 = (v - lo) >> 8;
-          const int mid = (int)(int8_t)(v1 & 255);
-          const int hi = (v1 - mid) >> 8;
-          auto Ri = gmem_w(reinterpret_cast<int8_t*>(a.R));
-          const size_t ix = rifrag_index(r, a.B_pad >> 8, b, s);
-          Ri[ix] = (int8_t)hi;
-          Ri[ix + kRiDigitBytes] = (int8_t)mid;
-          Ri[ix + 2 * kRiDigitBytes] = (int8_t)lo;
-        }
-      } else if (a.rfrag) {
-        // FP16 hi/lo pieces of R * 2^12 in the grouped gradient's fragment
-        // order, for every row of the tile (zero past B)
-        if (slot < kSlots) {
-          const float v = (float)Rv * kRfScale;
-          const _Float16 hi = (_Float16)v;
-          const _Float16 lo = (_Float16)(v - (float)hi);
-          auto Rf = gmem_w(reinterpret_cast<uint16_t*>(a.R));
-          const size_t ix = rfrag_index(r, a.B_pad >> 8, b, s);
-          Rf[ix] = __builtin_bit_cast(uint16_t, hi);
-          Rf[ix + kRfPieceWords] = __builtin_bit_cast(uint16_t, lo);
-        }
-      } else if (slot < kSlots && b < a.B3) {
-        gmem_w(a.R)[((size_t)r * a.B3 + b) * kSlot + s] = (float)Rv;
+      for (int k = 0; k < kSlot; ++k) {
+        const AT x = row[k];
+        AT P = x * inv;
+        P = fma(fma(-P, sum, x), inv, P);
+        row[k] = wa * (P - (k == sr ? (AT)1 : (AT)0));
+        if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
+    wave_sync();
+    if (a.rfrag == 0) {
+      // FP32 rows: the 48 rows are contiguous
+      auto Rr = gmem_w(a.R) + ((size_t)r * a.B3 + b0) * kSlot;
+      const int n = min(kParkRows, a.B3 - b0) * kSlot;
+#pragma unroll
+      for (int k = 0; k < (kParkRows * kSlot + 63) / 64; ++k)
+        if (lane + 64 * k < n) Rr[lane + 64 * k] = (float)park[lane + 64 * k];
+    }
+    if (slot < kSlots) {
+      const int bg = b0 + 16 * slot;  // sixteen rows from here
+      const AT* col = park + 16 * slot * kSlot + s;
+      // rows of every tile are written, zeros past B; states past q hold zeros
+      if (a.rfrag == 0) {
+#pragma unroll
+        for (int t = 0; t < 16; ++t) ghacc += (double)col[t * kSlot];
+      } else if (a.rfrag == 1) {
+        // FP16 hi/lo pieces of R * 2^12 in the grouped gradient's fragment order
+        auto Rf = gmem_w(reinterpret_cast<u32x4_t*>(a.R));
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          u32x4_t hi, lo;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            uint32_t hw = 0, lw = 0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const AT v = col[(8 * hf + 2 * t + u) * kSlot];
+              ghacc += (double)v;
+              const float y = (float)v * kRfScale;
+              const _Float16 yh = (_Float16)y;
+              const _Float16 yl = (_Float16)(y - (float)yh);
+              hw |= (uint32_t)__builtin_bit_cast(uint16_t, yh) << (16 * u);
+              lw |= (uint32_t)__builtin_bit_cast(uint16_t, yl) << (16 * u);
+            }
+            hi[t] = hw;
+            lo[t] = lw;
+          }
+          const size_t ix = rfrag_index(r, a.B_pad >> 8, bg + 8 * hf, s);
+          Rf[ix / 8] = hi;
+          Rf[(ix + kRfPieceWords) / 8] = lo;
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        // int8 digits in the int8 gradient's fragment order: three of round(R * 2^22); with
+        // rfrag = 3 three more, in a second set, of the remainder's round((R * 2^22 - v) * 2^22);
+        // with rfrag = 4 four of round(R * 2^(30 - e))
+        auto Ri = gmem_w(reinterpret_cast<u32x4_t*>(a.R));
+        const int nch = a.B_pad >> 8;
+        // the digits of sixteen integers: ND planes kRiDigitBytes apart from byte ix on, highest first
+        auto put = [&](size_t ix, auto nd, auto&& integer) {
+          constexpr int ND = decltype(nd)::value;
+          u32x4_t dw[ND];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            uint32_t w[ND];
+#pragma unroll
+            for (int d = 0; d < ND; ++d) w[d] = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              int y = integer(col[(4 * t + u) * kSlot]);
+#pragma unroll
+              for (int d = ND - 1; d >= 0; --d) {
+                const int lo = (int)(int8_t)(y & 255);
+                w[d] |= (uint32_t)(lo & 255) << (8 * u);
+                y = (y - lo) >> 8;
+              }
+            }
+#pragma unroll
+            for (int d = 0; d < ND; ++d) dw[d][t] = w[d];
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int d = 0; d < ND; ++d) Ri[(ix + (size_t)d * kRiDigitBytes) / 16] = dw[d];
+        };
+        constexpr std::integral_constant<int, 3> three;
+        if (a.rfrag == 4) {
+          put(r4frag_index(r, nch, bg, s), std::integral_constant<int, 4>{}, [&](AT v) {
+            ghacc += (double)v;
+            return (int)rint((double)v * rscale);
+          });
+        } else {
+          const size_t ix = rifrag_index(r, nch, bg, s);
+          if (sizeof(AT) == 4) {
+            put(ix, three, [&](AT v) {
+              ghacc += (double)v;
+              return (int)rintf((float)v * (float)(1 << kRiScaleLog2));
+            });
+          } else {
+            put(ix, three, [&](AT v) {
+              ghacc += (double)v;
+              return (int)rint((double)v * rscale);
+            });
+            put(ix + (size_t)a.N * nch * kRiChunkBytes, three, [&](AT v) {
+              const double y = (double)v * rscale;
+              return (int)rint((y - rint(y)) * rscale);
+            });
+          }
+        }
+      }
+    }
+    wave_sync();
   }
   const double ftot = block_sum_f64(facc, red);
   if (tid == 0) gmem_w(a.f_part)[(size_t)tile * N + r] = ftot;
@@ -299,12 +394,12 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
 
 // Persistent forward kernel: drains the forward work items of the batch.
 template <int NB, class AT, bool LO>
-__global__ __launch_bounds__(kFwdThreads) void fwd_kernel(BatchArgs b) {
+__global__ __launch_bounds__(kFwdThreads, sizeof(AT) == 4 ? 4 : 2) void fwd_kernel(BatchArgs b) {
   __shared__ __attribute__((aligned(16))) float lds[fwd_lds_floats<AT, LO>()];
   __shared__ uint2 sgl[kFwdWaves * kSlots * NB];
   __shared__ double red[kFwdWaves * 64];
   __shared__ int32_t item_s;
-  int32_t qi = 0;
+  int32_t qi = -1;
   const int32_t total = total_items(b, KIND_FWD);
   for (;;) {
     if (threadIdx.x == 0) item_s = next_item(b.ctr + KIND_FWD * kQueues, total, qi);
@@ -357,193 +452,6 @@ int32_t forward_resident_blocks(int32_t nb, int32_t f64) {
     default: break;
   }
   return (e == hipSuccess && per > 0) ? per : 1;
-}
-
-// Stable counting sort of each chunk's rows by their symbol at each column,
-// done once per alignment.  Entry = (chunk-local row << 8) | symbol; the row
-// field is then directly the byte offset of the row in the LDS residual tile
-// (rows of 64 floats = 256 bytes), and the low byte the symbol.
-__global__ __launch_bounds__(256) void chunk_sort_kernel(const uint8_t* __restrict__ msa_cm,
-                                                         int32_t B3, int32_t B_pad, int32_t N,
-                                                         int32_t q, uint16_t* __restrict__ sorted) {
-  __shared__ uint16_t cnt[256][kQMax + 1];
-  const int c = blockIdx.x, i = blockIdx.y * 256 + threadIdx.x;
-  if (i >= N) return;
-  const int b0 = c * kBwdSeqChunk, n = min(kBwdSeqChunk, B3 - b0);
-  uint16_t* ct = cnt[threadIdx.x];
-  for (int k = 0; k <= kQMax; ++k) ct[k] = 0;
-  const uint8_t* col = msa_cm + (size_t)(i / kFwdChunk) * B_pad * kFwdChunk + i % kFwdChunk;
-  for (int t = 0; t < n; ++t) ct[col[(size_t)(b0 + t) * kFwdChunk]]++;
-  int run = 0;
-  for (int k = 0; k < q; ++k) {
-    const int v = ct[k];
-    ct[k] = (uint16_t)run;
-    run += v;
-  }
-  uint16_t* out = sorted + ((size_t)c * N + i) * kBwdSeqChunk;
-  for (int t = 0; t < n; ++t) {
-    const int k = col[(size_t)(b0 + t) * kFwdChunk];
-    out[ct[k]++] = (uint16_t)((t << 8) | k);
-  }
-}
-
-hipError_t launch_chunk_sort(const uint8_t* msa_cm, int32_t B3, int32_t B_pad, int32_t N, int32_t q,
-                             uint16_t* sorted, hipStream_t st) {
-  const int nchunks = (B3 + kBwdSeqChunk - 1) / kBwdSeqChunk;
-  hipLaunchKernelGGL(chunk_sort_kernel, dim3(nchunks, (N + 255) / 256), dim3(256), 0, st, msa_cm,
-                     B3, B_pad, N, q, sorted);
-  return hipGetLastError();
-}
-
-// dJ_ri(s,k) = sum over the rows b with sigma_i^b = k of R_b(s).  Per chunk of
-// 192 rows, the residual rows are staged in LDS (three bank-disjoint copies of
-// each 21-float row, one per slot).  Each slot owns one column and walks the
-// chunk's rows in symbol order, keeping a running FP32 sum in a register.  A
-// symbol's rows are contiguous, so each group sum is final when the symbol
-// changes and is stored (plain store, no read-back) into the column's slot for
-// that symbol; after the chunk every lane folds its 21 slots into FP64
-// registers and clears them.  No two lanes ever write the same LDS word.
-// One LDS arena: residual rows first (so a row's byte offset is its address).
-// Pitches chosen so that the three slots of a wave, which work on three
-// consecutive columns, hit disjoint LDS banks: 200 entries (100 dwords) per
-// column, and 469 = 7 * 64 + 21 floats per column of group sums.
-constexpr int kEntPitch = kBwdSeqChunk + 8;
-constexpr int kSegPitch = 7 * 64 + kSlot;
-constexpr int kRsBytes = kBwdSeqChunk * kRowF * 4;              // 48 KB
-constexpr int kEntBytes = kBwdPos * kEntPitch * 2;              // 19 KB
-constexpr int kSegBytes = kBwdPos * kSegPitch * 4;              // 88 KB
-
-// One backward work item: site r x the 48 alignment columns of block cb.
-__device__ inline void bwd_item(const EvalArgs& a, int r, int cb, char* arena) {
-  float* Rs = reinterpret_cast<float*>(arena);
-  uint16_t* ent = reinterpret_cast<uint16_t*>(arena + kRsBytes);
-  float* seg = reinterpret_cast<float*>(arena + kRsBytes + kEntBytes);
-  const int q = a.q, N = a.N, qq = q * q;
-  const int i0 = cb * kBwdPos;
-  const int tid = item_tid(), lane = tid & 63, wid = tid >> 6;
-  const int slot = lane / kSlot, s = lane - slot * kSlot;
-  const int slotA = slot < kSlots ? slot : kSlots - 1;  // lane 63 shadows lane 42 and never writes
-  const int pl = wid * kSlots + slotA;                   // this lane's column within the block
-  const int i = i0 + pl;
-  const bool writer = lane < kSlots * kSlot;
-  const int npos = min(kBwdPos, N - i0);
-
-  for (int e = tid; e < kBwdPos * kSegPitch; e += kBwdThreads) seg[e] = 0.f;
-  double acc64[kQMax];
-#pragma unroll
-  for (int k = 0; k < kQMax; ++k) acc64[k] = 0.0;
-  float* myseg = seg + pl * kSegPitch + s;                // + 21 * symbol
-  const uint32_t lane_off = 4u * (uint32_t)(slotA * kSlot + s);
-  const uint16_t* myent = ent + pl * kEntPitch;
-
-  const int nchunks = (a.B3 + kBwdSeqChunk - 1) / kBwdSeqChunk;
-  const auto Rr = gmem(a.R + (size_t)r * a.B3 * kSlot);
-  for (int c = 0; c < nchunks; ++c) {
-    const int bc = c * kBwdSeqChunk, n = min(kBwdSeqChunk, a.B3 - bc);
-    __syncthreads();
-    for (int e = tid; e < n * kSlot; e += kBwdThreads) {
-      const int t = e / kSlot, ss = e - t * kSlot;
-      const float v = Rr[(size_t)bc * kSlot + e];
-      float* row = Rs + t * kRowF;
-      row[ss] = v;
-      row[ss + kSlot] = v;
-      row[ss + 2 * kSlot] = v;
-    }
-    {
-      constexpr int kV = kBwdSeqChunk / 8, kVP = kEntPitch / 8;   // uint4 per column: data, pitch
-      const uint16_t* src = a.sorted + ((size_t)c * N + i0) * kBwdSeqChunk;
-      uint4* dst = reinterpret_cast<uint4*>(ent);
-      for (int e = tid; e < kBwdPos * kV; e += kBwdThreads) {
-        const int col = e / kV, x = e - col * kV;
-        dst[col * kVP + x] = col < npos ? gload_u4(src + 8 * (size_t)e) : make_uint4(0, 0, 0, 0);
-      }
-    }
-    __syncthreads();
-    uint32_t cur = myent[0] & 0xffu;
-    float run = 0.f;
-    auto rowval = [&](uint32_t e) {
-      return *reinterpret_cast<const float*>(arena + ((e & 0xff00u) | lane_off));
-    };
-    int j = 0;
-    for (; j + 8 <= n; j += 8) {
-      // eight sorted entries at once; they all continue the current group
-      // exactly when the last one does, since symbols ascend within the chunk
-      const uint4 e8 = *reinterpret_cast<const uint4*>(myent + j);
-      const uint32_t e[8] = {e8.x & 0xffffu, e8.x >> 16, e8.y & 0xffffu, e8.y >> 16,
-                             e8.z & 0xffffu, e8.z >> 16, e8.w & 0xffffu, e8.w >> 16};
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = rowval(e[u]);
-      if ((e[7] & 0xffu) == cur) {
-        run += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-      } else {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const uint32_t sg = e[u] & 0xffu;
-          if (sg != cur) {
-            if (writer) myseg[cur * kQMax] = run;
-            run = 0.f;
-            cur = sg;
-          }
-          run += v[u];
-        }
-      }
-    }
-    for (; j < n; ++j) {
-      const uint32_t e = myent[j];
-      const uint32_t sg = e & 0xffu;
-      const float v = rowval(e);
-      if (sg != cur) {
-        if (writer) myseg[cur * kQMax] = run;
-        run = 0.f;
-        cur = sg;
-      }
-      run += v;
-    }
-    if (writer) myseg[cur * kQMax] = run;
-    // fold this chunk's group sums (the lane's own words) into FP64
-#pragma unroll
-    for (int k = 0; k < kQMax; ++k) {
-      acc64[k] += (double)myseg[k * kQMax];
-      if (writer) myseg[k * kQMax] = 0.f;
-    }
-  }
-  if (writer && s < q && i < N) {
-#pragma unroll
-    for (int k = 0; k < kQMax; ++k)
-      if (k < q) a.gJ[((size_t)r * N + i) * qq + (size_t)k * q + s] = (i == r) ? 0.0 : acc64[k];
-  }
-}
-
-// Persistent backward kernel: drains the backward work items of the batch.
-__global__ __launch_bounds__(kBwdThreads) void bwd_kernel(BatchArgs b) {
-  __shared__ __attribute__((aligned(16))) char arena[kRsBytes + kEntBytes + kSegBytes];
-  __shared__ int32_t item_s;
-  int32_t qi = 0;
-  const int32_t total = total_items(b, KIND_BWD);
-  for (;;) {
-    if (threadIdx.x == 0) item_s = next_item(b.ctr + KIND_BWD * kQueues, total, qi);
-    __syncthreads();
-    const int32_t t = __builtin_amdgcn_readfirstlane(item_s);
-    if (t < 0) break;
-    const Item it = decode_item(b, KIND_BWD, t);
-    const EvalArgs a = load_uniform(b.ev + it.m);
-    bwd_item(a, it.r, it.sub, arena);
-    __syncthreads();
-  }
-}
-
-int32_t backward_blocks_per_site(int32_t N) { return (N + kBwdPos - 1) / kBwdPos; }
-
-int32_t backward_resident_blocks() {
-  int per = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bwd_kernel, kBwdThreads, 0);
-  return (e == hipSuccess && per > 0) ? per : 1;
-}
-
-hipError_t launch_backward(const BatchArgs& b, int32_t nblocks, hipStream_t st) {
-  hipLaunchKernelGGL(bwd_kernel, dim3(nblocks), dim3(kBwdThreads), 0, st, b);
-  return hipGetLastError();
 }
 
 }  // namespace plm

@@ -460,7 +460,7 @@ __global__ __launch_bounds__(kMThreads) void fwd_mfma_kernel(BatchArgs b) {
   __shared__ __attribute__((aligned(16))) uint8_t sgl[2][kFRows * kFPos];
   __shared__ double red[kMWaves * 64];
   __shared__ int32_t item_s;
-  int32_t qi = 0;
+  int32_t qi = -1;
   const int32_t total = total_items(b, KIND_FWD);
   for (;;) {
     if (threadIdx.x == 0) item_s = next_item(b.ctr + KIND_FWD * kQueues, total, qi);
@@ -490,7 +490,7 @@ __global__ __launch_bounds__(kMThreads) void bwd_mfma_kernel(BatchArgs b) {
   __shared__ __attribute__((aligned(16))) uint16_t Bf[2][NP * kBfPiece];
   __shared__ __attribute__((aligned(16))) uint8_t sig[2][kMPosMax * kSigPitch];
   __shared__ int32_t item_s;
-  int32_t qi = 0;
+  int32_t qi = -1;
   const int32_t total = total_items(b, KIND_BWD);
   for (;;) {
     if (threadIdx.x == 0) item_s = next_item(b.ctr + KIND_BWD * kQueues, total, qi);
@@ -692,7 +692,7 @@ __global__ __launch_bounds__(kGThreads) void bwd_g3_kernel(BatchArgs b) {
   __shared__ __attribute__((aligned(16))) uint8_t sig0[kGPosMax * kSigPitch];
   __shared__ __attribute__((aligned(16))) uint8_t sig1[kGPosMax * kSigPitch];
   __shared__ int32_t item_s;
-  int32_t qi = 0;
+  int32_t qi = -1;
   const int32_t total = total_items(b, KIND_BWD);
   for (;;) {
     if (threadIdx.x == 0) item_s = next_item(b.ctr + KIND_BWD * kQueues, total, qi);
@@ -757,9 +757,20 @@ hipError_t launch_backward_g3(const BatchArgs& b, int32_t nblocks, hipStream_t s
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
 constexpr int kISteps = kMChunk / 32;                 // MFMA steps per chunk
-constexpr int kISiteStride = kRiChunkBytes + 80;      // bank-disjoint site runs, as above
-static_assert((kISiteStride / 16 - kSlot) % 8 == 0 && kISiteStride % 16 == 0, "bank-disjoint site runs");
-constexpr int kIBufBytes = 2 * kISiteStride + kRiChunkBytes;
+// Digit planes per pass over the sequences: three (paths 5 to 7: R * 2^22), or
+// two (path 0: the four digits of R * 2^30 in two passes, so that the
+// accumulators of a pass leave registers for the operands in flight).
+template <int ND>
+struct I8Shape {
+  static constexpr int kPassBytes = ND * kRiDigitBytes;                   // copied per site, chunk and pass
+  static constexpr int kChunkBytes = ND == 2 ? kR4ChunkBytes : kRiChunkBytes;
+  static constexpr int kPasses = kChunkBytes / kPassBytes;
+  static constexpr int kSiteStride = kPassBytes + 80;                     // bank-disjoint site runs, as above
+  static constexpr int kBufBytes = 2 * kSiteStride + kPassBytes;
+  static constexpr int kCopies = (kPassBytes + 1023) / 1024;              // wave copies of 1 KB per site and chunk
+  static constexpr int kCopiesWave = (kG3Sites * kCopies + kGWaves - 1) / kGWaves;
+  static_assert((kSiteStride / 16 - kSlot) % 8 == 0 && kSiteStride % 16 == 0, "bank-disjoint site runs");
+};
 
 // One-hot of 16 symbols against k as sixteen int8 values (1 where sigma == k):
 // a byte of x = sigma ^ k is below 32, so x + 0x7f keeps bit 7 clear exactly
@@ -789,14 +800,26 @@ __device__ inline uint4 onehot16_neg(uint4 s16, uint32_t nkk) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// LO = false: the residual digits of round(R * 2^22), written to the gradient
-// data part; LO = true (second pass of the precise path): the digits of the
-// remainder, round((R * 2^22 - v) * 2^22), added to it scaled by 2^-44.
+// ND = 3, LO = false: the residual digits of round(R * 2^22), written to the
+// gradient data part; LO = true (second pass of the precise path): the digits
+// of the remainder, round((R * 2^22 - v) * 2^22), added to it scaled by 2^-44.
+// ND = 2 (path 0): the four digits of round(R * 2^(30 - e)), e = *a.wexp, in
+// two passes over the sequences, the high two first; every pass is cut into
+// segments of kI8SegChunks chunks, so that the int32 sums are exact for any
+// number of sequences, and each pass and segment after the first adds its
+// FP64 value to the one stored (exact while the sums stay below 2^53 2^-30,
+// 2^23 sequences).  Bound: the int8 product, four digit planes against three
+// (10.9 ms at the products' measured rate for N = 500, B = 50 000); it took
+// the place of a scatter of FP32 residuals in symbol order through LDS, 85 ->
+// 16 ms there and 1776 -> 426 us at N = 150, B = 8000, with a gradient error
+// against FP64 of 3.0e-8 where the scatter's was 4.9e-8 (N = 40, B = 500).
 // NEG: the one-hot operand holds -128 for a one (alignments of fewer than
 // kNegSeqMax padded sequences), and the epilogue divides it out exactly.
-template <bool LO, bool NEG>
+constexpr int kI8SegChunks = (1 << 16) - 1;
+template <int ND, bool LO, bool NEG>
 __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Item& it, int8_t* Rb0, int8_t* Rb1,
                                uint8_t* sig0, uint8_t* sig1) {
+  using Sh = I8Shape<ND>;
   const int npos_blk = g3_block_positions(a.q);
   const int q = a.q, N = a.N, qq = q * q;
   const int i0 = it.sub * npos_blk;
@@ -827,44 +850,47 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
   for (int T = 0; T < kGT; ++T) {
     const int col = min(32 * T + l32, 3 * kSlot - 1);
     const int g = col / kSlot, sidx = col - g * kSlot;
-    boff[T] = (uint32_t)(g * kISiteStride + half * (kSlot * 16) + sidx * 16);
+    boff[T] = (uint32_t)(g * Sh::kSiteStride + half * (kSlot * 16) + sidx * 16);
   }
 
   const int nchunks = (a.B3 + kMChunk - 1) / kMChunk;
   const int nch_site = a.B_pad >> 8;
   const int nsig = npos_blk * (kMChunk / 16);
-  // a site's chunk is 15.75 KB: 16 wave copies of 1 KB, the last one moved
-  // back to end at the chunk end (it re-copies 256 bytes with the same values);
-  // the LDS destination of a copy is uniform over the wave
-  // with three sites, each wave's six copies are set up once per item
-  static_assert(kG3Sites * 16 == 6 * kGWaves, "six copies per wave for a full group");
-  const char* rsrc[6];
-  uint32_t rdst[6];
+  // a site's pass over a chunk is 15.75 (10.5) KB: wave copies of 1 KB, the
+  // last one moved back to end at its end (it re-copies bytes with the same
+  // values); the LDS destination of a copy is uniform over the wave
+  // with three sites, each wave's copies are set up once per item
+  constexpr int kCopies = Sh::kCopies, kCW = Sh::kCopiesWave;
+  const char* rsrc[kCW];
+  uint32_t rdst[kCW];
 #pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    const int k = wid + kGWaves * j;
-    const int g = k >> 4, part = k & 15;
-    const int off = min(part * 1024, kRiChunkBytes - 1024);
+  for (int j = 0; j < kCW; ++j) {
+    const int k = min(wid + kGWaves * j, kG3Sites * kCopies - 1);
+    const int g = k / kCopies, part = k - g * kCopies;
+    const int off = min(part * 1024, Sh::kPassBytes - 1024);
     const int rg = g == 0 ? rs[0] : (g == 1 ? rs[1] : rs[2]);
     rsrc[j] = reinterpret_cast<const char*>(a.R) + (LO ? (size_t)N * nch_site * kRiChunkBytes : 0) +
-              (size_t)rg * nch_site * kRiChunkBytes + off;
-    rdst[j] = (uint32_t)(g * kISiteStride + off);
+              (size_t)rg * nch_site * Sh::kChunkBytes + off;
+    rdst[j] = (uint32_t)(g * Sh::kSiteStride + off);
   }
+  int poff = 0;  // byte offset of the pass within a chunk
   auto fetch_r = [&](int c, int8_t* dst) {
     if (cnt == kG3Sites) {
 #pragma unroll
-      for (int j = 0; j < 6; ++j)
-        copy16_to_lds(rsrc[j] + (size_t)c * kRiChunkBytes, reinterpret_cast<char*>(dst) + rdst[j], lane);
+      for (int j = 0; j < kCW; ++j)
+        if (wid + kGWaves * j < kG3Sites * kCopies)
+          copy16_to_lds(rsrc[j] + (size_t)c * Sh::kChunkBytes + (Sh::kPasses > 1 ? poff : 0),
+                        reinterpret_cast<char*>(dst) + rdst[j], lane);
       return;
     }
-    const int ninst = cnt * 16;
+    const int ninst = cnt * kCopies;
     for (int k = wid; k < ninst; k += kGWaves) {
-      const int g = k >> 4, part = k & 15;
-      const int off = min(part * 1024, kRiChunkBytes - 1024);
+      const int g = k / kCopies, part = k - g * kCopies;
+      const int off = min(part * 1024, Sh::kPassBytes - 1024);
       const int rg = g == 0 ? rs[0] : (g == 1 ? rs[1] : rs[2]);
       const char* src = reinterpret_cast<const char*>(a.R) + (LO ? (size_t)N * nch_site * kRiChunkBytes : 0) +
-                        ((size_t)rg * nch_site + c) * kRiChunkBytes + off;
-      copy16_to_lds(src, reinterpret_cast<char*>(dst) + g * kISiteStride + off, lane);
+                        ((size_t)rg * nch_site + c) * Sh::kChunkBytes + (Sh::kPasses > 1 ? poff : 0) + off;
+      copy16_to_lds(src, reinterpret_cast<char*>(dst) + g * Sh::kSiteStride + off, lane);
     }
   };
   uint4 sv;
@@ -878,20 +904,15 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
     if (tid < nsig) *reinterpret_cast<uint4*>(dst + (tid >> 4) * kSigPitch + (tid & 15) * 16) = sv;
   };
 
-  i32x16 acc[3][kGRB][kGT];
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int m = 0; m < kGRB; ++m)
-#pragma unroll
-      for (int T = 0; T < kGT; ++T) acc[d][m][T] = i32x16{};
+  i32x16 acc[ND][kGRB][kGT];
+  int cend = nchunks;  // end of the segment
 
   auto chunk = [&](int c, const int8_t* cur, int8_t* nxt, const uint8_t* scur, uint8_t* snxt) {
-    if (c + 1 < nchunks) {
+    if (c + 1 < cend) {
       fetch_r(c + 1, nxt);
       store_sig(snxt);
     }
-    if (c + 2 < nchunks) load_sig(c + 2);
+    if (c + 2 < cend) load_sig(c + 2);
     if (wave_live) {
       const char* rb = reinterpret_cast<const char*>(cur);
       const uint8_t* sgb = scur + half * 16;
@@ -907,7 +928,7 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
         // the symbols read ahead have arrived (lgkmcnt 0; vmcnt and expcnt at
         // their maxima, so the chunk copies stay in flight)
         __builtin_amdgcn_s_waitcnt(0xc07f);
-        // the six B fragments (digit, tile) of this step, each read two ahead of its use
+        // the B fragments (digit, tile) of this step, each read two ahead of its use
         auto ldb = [&](int f) {
           return *reinterpret_cast<const uint4*>(rb + boff[f & 1] + ((f >> 1) * kISteps + t) * (2 * kSlot * 16));
         };
@@ -922,7 +943,7 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
         // fragment two ahead (an LDS wait then covers only the reads a product
         // needs)
         const uint4 s1 = ldsym(1, t);
-        uint4 bq[6];
+        uint4 bq[2 * ND];
         bq[0] = ldb(0);
         bq[1] = ldb(1);
         __builtin_amdgcn_sched_barrier(0);
@@ -936,11 +957,11 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
         prod(0, 1, av1, bq[0]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int f = 1; f < 6; ++f) {
+        for (int f = 1; f < 2 * ND; ++f) {
           prod(f, 0, av0, bq[f]);
           prod(f, 1, av1, bq[f]);
           __builtin_amdgcn_sched_barrier(0);
-          if (f + 2 < 6) bq[f + 2] = ldb(f + 2);
+          if (f + 2 < 2 * ND) bq[f + 2] = ldb(f + 2);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -949,55 +970,95 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
     __syncthreads();
   };
 
-  fetch_r(0, Rb0);
-  load_sig(0);
-  store_sig(sig0);
-  if (nchunks > 1) load_sig(1);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  for (int c = 0; c < nchunks; c += 2) {
-    chunk(c, Rb0, Rb1, sig0, sig1);
-    if (c + 1 < nchunks) chunk(c + 1, Rb1, Rb0, sig1, sig0);
-  }
-  if (!wave_live) return;
-  constexpr double kScale = (LO ? 1.0 / ((double)(1 << kRiScaleLog2) * (double)(1 << kRiScaleLog2))
-                                : 1.0 / (double)(1 << kRiScaleLog2)) *
-                           (NEG ? -1.0 / 128.0 : 1.0);
+  // the sums of chunks [cb, cend) of one pass
+  auto accumulate = [&](int cb) {
 #pragma unroll
-  for (int T = 0; T < kGT; ++T) {
-    const int col = 32 * T + l32;
-    const int g = col / kSlot, sidx = col - g * kSlot;
-    if (g >= cnt || sidx >= q) continue;
-    const int rg = g == 0 ? rs[0] : (g == 1 ? rs[1] : rs[2]);
+    for (int d = 0; d < ND; ++d)
 #pragma unroll
-    for (int m = 0; m < kGRB; ++m)
+      for (int m = 0; m < kGRB; ++m)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int row = (wid * kGRB + m) * 32 + 8 * (j >> 2) + 4 * half + (j & 3);
-        if (row < nrows) {
-          const int i = i0 + row / q, k = row % q;
-          // exact: every digit sum is an integer below 2^31
-          const double v = (double)acc[0][m][T][j] * 65536.0 + (double)acc[1][m][T][j] * 256.0 +
-                           (double)acc[2][m][T][j];
-          auto out = gmem_w(a.gJ) + ((size_t)rg * N + i) * qq + (size_t)k * q + sidx;
-          if (LO) {
-            if (i != rg) *out += v * kScale;
-          } else {
-            *out = (i == rg) ? 0.0 : v * kScale;
+        for (int T = 0; T < kGT; ++T) acc[d][m][T] = i32x16{};
+    fetch_r(cb, Rb0);
+    load_sig(cb);
+    store_sig(sig0);
+    if (cb + 1 < cend) load_sig(cb + 1);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    for (int c = cb; c < cend; c += 2) {
+      chunk(c, Rb0, Rb1, sig0, sig1);
+      if (c + 1 < cend) chunk(c + 1, Rb1, Rb0, sig1, sig0);
+    }
+  };
+  // the digit sums combined, scaled and written (add = false) or added
+  auto flush = [&](double scale, bool add) {
+    // (the lane's place is opaque here, so that the addresses below are not
+    // computed ahead of the product loop, which needs the registers)
+    int lo32 = l32, hi32 = half, wv = wid;
+    asm volatile("" : "+v"(lo32), "+v"(hi32), "+s"(wv));
+#pragma unroll
+    for (int T = 0; T < kGT; ++T) {
+      const int col = 32 * T + lo32;
+      const int g = col / kSlot, sidx = col - g * kSlot;
+      if (g >= cnt || sidx >= q) continue;
+      const int rg = g == 0 ? rs[0] : (g == 1 ? rs[1] : rs[2]);
+      // row (i - i0) q + k of the block is entry (i, k): q values further on each
+      auto out = gmem_w(a.gJ) + ((size_t)rg * N + i0) * qq + sidx;
+      const int self0 = (rg - i0) * q;  // rows of the site's own column
+#pragma unroll
+      for (int m = 0; m < kGRB; ++m) {
+        const int row0 = (wv * kGRB + m) * 32 + 4 * hi32;
+        // the stored values of a few rows are read together, as many as registers allow
+        constexpr int kOld = ND == 3 ? 4 : 16;
+        double old[kOld];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          if (j % kOld == 0) {
+#pragma unroll
+            for (int k = 0; k < kOld; ++k) {
+              const int row = row0 + 8 * ((j + k) >> 2) + ((j + k) & 3);
+              old[k] = add && row < nrows ? out[row * q] : 0.0;
+            }
+          }
+          const int row = row0 + 8 * (j >> 2) + (j & 3);
+          if (row < nrows) {
+            // exact: every digit sum is an integer below 2^31
+            const double v = ND == 3 ? (double)acc[0][m][T][j] * 65536.0 + (double)acc[1][m][T][j] * 256.0 +
+                                           (double)acc[ND - 1][m][T][j]
+                                     : (double)acc[0][m][T][j] * 256.0 + (double)acc[1][m][T][j];
+            out[row * q] = (unsigned)(row - self0) < (unsigned)q ? 0.0 : old[j % kOld] + v * scale;
           }
         }
       }
+    }
+  };
+  constexpr double kNeg = NEG ? -1.0 / 128.0 : 1.0;
+  if constexpr (ND == 3) {
+    accumulate(0);
+    if (!wave_live) return;
+    flush((LO ? 1.0 / ((double)(1 << kRiScaleLog2) * (double)(1 << kRiScaleLog2))
+              : 1.0 / (double)(1 << kRiScaleLog2)) * kNeg,
+          LO);
+  } else {
+    const double unit = ldexp(kNeg, __builtin_amdgcn_readfirstlane(*a.wexp) - kR4ScaleLog2);
+    for (int pass = 0; pass < Sh::kPasses; ++pass) {
+      poff = pass * Sh::kPassBytes;
+      for (int cb = 0; cb < nchunks; cb += kI8SegChunks) {
+        cend = min(nchunks, cb + kI8SegChunks);
+        accumulate(cb);
+        if (wave_live) flush(pass == 0 ? unit * 65536.0 : unit, pass > 0 || cb > 0);
+      }
+    }
   }
 }
 
-template <bool LO>
+template <int ND, bool LO>
 __global__ __launch_bounds__(kGThreads) void bwd_i8_kernel(BatchArgs b) {
-  __shared__ __attribute__((aligned(16))) int8_t Rb0[kIBufBytes];
-  __shared__ __attribute__((aligned(16))) int8_t Rb1[kIBufBytes];
+  __shared__ __attribute__((aligned(16))) int8_t Rb0[I8Shape<ND>::kBufBytes];
+  __shared__ __attribute__((aligned(16))) int8_t Rb1[I8Shape<ND>::kBufBytes];
   __shared__ __attribute__((aligned(16))) uint8_t sig0[kGPosMax * kSigPitch];
   __shared__ __attribute__((aligned(16))) uint8_t sig1[kGPosMax * kSigPitch];
   __shared__ int32_t item_s;
-  int32_t qi = 0;
+  int32_t qi = -1;
   const int32_t total = total_items(b, KIND_BWD);
   for (;;) {
     if (threadIdx.x == 0) item_s = next_item(b.ctr + KIND_BWD * kQueues, total, qi);
@@ -1006,23 +1067,26 @@ __global__ __launch_bounds__(kGThreads) void bwd_i8_kernel(BatchArgs b) {
     if (t < 0) break;
     const Item it = decode_item(b, KIND_BWD, t);
     const EvalArgs a = load_uniform(b.ev + it.m);
-    if (a.B_pad < kNegSeqMax) i8_item<LO, true>(b, a, it, Rb0, Rb1, sig0, sig1);
-    else i8_item<LO, false>(b, a, it, Rb0, Rb1, sig0, sig1);
+    if (a.B_pad < kNegSeqMax) i8_item<ND, LO, true>(b, a, it, Rb0, Rb1, sig0, sig1);
+    else i8_item<ND, LO, false>(b, a, it, Rb0, Rb1, sig0, sig1);
     __syncthreads();
   }
 }
 
 int32_t i8_backward_blocks_per_site(int32_t N, int32_t q) { return g3_backward_blocks_per_site(N, q); }
 
-int32_t i8_resident_blocks() {
+int32_t i8_resident_blocks(int32_t digits) {
   int per = 0;
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bwd_i8_kernel<false>, kGThreads, 0);
+  const hipError_t e =
+      digits == 4 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bwd_i8_kernel<2, false>, kGThreads, 0)
+                  : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bwd_i8_kernel<3, false>, kGThreads, 0);
   return (e == hipSuccess && per > 0) ? per : 1;
 }
 
-hipError_t launch_backward_i8(const BatchArgs& b, int32_t nblocks, int32_t lo, hipStream_t st) {
-  if (lo) hipLaunchKernelGGL(bwd_i8_kernel<true>, dim3(nblocks), dim3(kGThreads), 0, st, b);
-  else hipLaunchKernelGGL(bwd_i8_kernel<false>, dim3(nblocks), dim3(kGThreads), 0, st, b);
+hipError_t launch_backward_i8(const BatchArgs& b, int32_t digits, int32_t nblocks, int32_t lo, hipStream_t st) {
+  if (digits == 4) hipLaunchKernelGGL((bwd_i8_kernel<2, false>), dim3(nblocks), dim3(kGThreads), 0, st, b);
+  else if (lo) hipLaunchKernelGGL((bwd_i8_kernel<3, true>), dim3(nblocks), dim3(kGThreads), 0, st, b);
+  else hipLaunchKernelGGL((bwd_i8_kernel<3, false>), dim3(nblocks), dim3(kGThreads), 0, st, b);
   return hipGetLastError();
 }
 

@@ -39,12 +39,6 @@ constexpr int kScPer = 7;           // states of j per lane
 constexpr int kScPitch = kQMax + 2;  // row pitch of the FP64 matrix in LDS (odd)
 static_assert(3 * kScPer == kQMax, "three lanes cover the states of j");
 
-// orders a wave's LDS accesses (they execute in program order; this keeps the compiler's order)
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 template <bool AVG, int NORM>
 __global__ __launch_bounds__(64 * kScWaves) void pair_score_kernel(const float* __restrict__ J, int32_t N, int32_t q,
                                                                    int32_t npairs, int32_t per, ScoreOpts o,

@@ -95,13 +95,14 @@ struct EvalBufs {
   double* f_part;
   double* gh_part;
   double* gJ;
-  uint16_t* sorted;
-  int32_t B_pad, N_pad, B3, tiles_max, nchunks;
+  int32_t B_pad, N_pad, B3, tiles_max;
   int8_t* Wq;
   int32_t* jexp;
   uint32_t* sym3;
   int32_t NG;
 };
+
+constexpr int32_t kWsRows = 192;
 
 // wide: room for the precise path's two residual digit sets (126 bytes per
 // site and row instead of 21 floats)
@@ -119,8 +120,8 @@ void layout_eval(Bump& bp, int32_t B, int32_t N, int32_t q, EvalBufs& e, bool wi
   e.f_part = bp.take<double>((size_t)e.tiles_max * N);
   e.gh_part = bp.take<double>((size_t)e.tiles_max * N * kSlot);
   e.gJ = bp.take<double>((size_t)N * N * q * q);
-  e.nchunks = (e.B3 + kBwdSeqChunk - 1) / kBwdSeqChunk;
-  e.sorted = bp.take<uint16_t>((size_t)e.nchunks * N * kBwdSeqChunk);
+  // unused bytes: the size of a workspace is what callers have been told before
+  bp.take<uint16_t>((size_t)((e.B3 + kWsRows - 1) / kWsRows) * N * kWsRows);
   e.NG = (N + 2) / 3;
   e.Wq = bp.take<int8_t>((size_t)N * e.NG * kWqGroupBytes);
   e.jexp = bp.take<int32_t>((size_t)N * (1 + kJParts));
@@ -266,20 +267,36 @@ int ensure_pin(plm_ctx* c, size_t words) {
   return PLM_OK;
 }
 
-int32_t pick_nb(int32_t B, int32_t tile_seqs) {
+// Rows per wave of the gather forward's tile: a compute unit works through its
+// items one after the other, so the rule takes the tile with the least
+// (items per unit, rounded up) x (rows + 4), where 4 rows' worth is what
+// staging the couplings costs an item.  Measured, forward and gradient of
+// path 5 with 16 / 32 / 64 rows: N = 40, B = 500 52 / 58 / 80 us; N = 120,
+// B = 5000 324 / 319 / 290 us; N = 150, B = 8000 684 / 673 / 780 us; N = 500,
+// B = 50 000 32.9 / 31.4 / 29.4 ms.
+int32_t pick_nb(int32_t N, int32_t B, int32_t ncu, int32_t tile_seqs) {
   if (tile_seqs == 16 || tile_seqs == 32 || tile_seqs == 64) return tile_seqs;
-  if (B >= 4 * forward_tile_seqs(64)) return 64;
-  if (B >= 2 * forward_tile_seqs(32)) return 32;
-  return 16;
+  int32_t best = 16;
+  int64_t cost = 0;
+  for (int32_t nb : {64, 32, 16}) {
+    const int32_t t = forward_tile_seqs(nb);
+    const int64_t items = (int64_t)N * ((B + t - 1) / t);
+    const int64_t k = (items + ncu - 1) / ncu * (nb + 4);
+    if (cost == 0 || k < cost) {
+      cost = k;
+      best = nb;
+    }
+  }
+  return best;
 }
 
-// Kernels of each evaluation path: 0 = LDS gather forward / sorted scatter
-// backward, n > 0 = one-hot MFMA product with n BF16 pieces.
+// Kernels of each evaluation path: fwd_np 0 = LDS gather forward, n > 0 =
+// one-hot MFMA product with n BF16 pieces; bwd_np pieces of the gradient's.
 struct PathSpec {
   int fwd_np, bwd_np;
   int bwd_f16;  // gradient pieces in FP16 (of R * 2^12) instead of BF16
   int bwd_g3;   // grouped gradient: three sites per item, R split by the forward
-  int bwd_i8;   // grouped gradient on int8 digits of R (fixed point, exact accumulation)
+  int bwd_i8;   // grouped gradient on this many int8 digits of R (fixed point, exact accumulation)
   int fwd_i8;   // grouped forward on int8 digits of J (fixed point, exact accumulation)
   int f64;      // precise path: FP64 gather forward, residuals as two int8 digit sets, two gradient passes
 };
@@ -289,18 +306,19 @@ int32_t bwd_group(const PathSpec& p) { return (p.bwd_g3 || p.bwd_i8) ? kG3Sites 
 int32_t fwd_group(const PathSpec& p) { return p.fwd_i8 ? kG3Sites : 1; }
 
 // the int8 gradient sums up to 2^24 sequences exactly
-bool path_fits(const PathSpec& p, int32_t B) { return !p.bwd_i8 || B < (1 << 24); }
+// in one go; the four-digit one cuts longer alignments into segments
+bool path_fits(const PathSpec& p, int32_t B) { return p.bwd_i8 != 3 || B < (1 << 24); }
 
 bool path_spec(int32_t path, PathSpec* p) {
   switch (path) {
-    case PLM_PATH_GATHER_FP32: *p = {0, 0, 0, 0, 0, 0, 0}; return true;
+    case PLM_PATH_GATHER_FP32: *p = {0, 0, 0, 0, 4, 0, 0}; return true;
     case PLM_PATH_MFMA_BF16X2: *p = {2, 2, 0, 0, 0, 0, 0}; return true;
     case PLM_PATH_GATHER_MFMA_FP32: *p = {0, 3, 0, 0, 0, 0, 0}; return true;
     case PLM_PATH_MFMA_FP32: *p = {3, 3, 0, 0, 0, 0, 0}; return true;
     case PLM_PATH_GATHER_MFMA_F16X2: *p = {0, 2, 1, 1, 0, 0, 0}; return true;
-    case PLM_PATH_GATHER_MFMA_I8X3: *p = {0, 3, 0, 0, 1, 0, 0}; return true;
-    case PLM_PATH_MFMA_I8X3: *p = {0, 3, 0, 0, 1, 1, 0}; return true;
-    case PLM_PATH_GATHER64_MFMA_I8X6: *p = {0, 3, 0, 0, 1, 0, 1}; return true;
+    case PLM_PATH_GATHER_MFMA_I8X3: *p = {0, 3, 0, 0, 3, 0, 0}; return true;
+    case PLM_PATH_MFMA_I8X3: *p = {0, 3, 0, 0, 3, 1, 0}; return true;
+    case PLM_PATH_GATHER64_MFMA_I8X6: *p = {0, 3, 0, 0, 3, 0, 1}; return true;
     default: return false;
   }
 }
@@ -316,20 +334,20 @@ int32_t eval_tiles(const PathSpec& p, int32_t B, int32_t nb) {
 int32_t eval_bwd_blocks(const PathSpec& p, int32_t N, int32_t q) {
   if (p.bwd_g3) return g3_backward_blocks_per_site(N, q);
   if (p.bwd_i8) return i8_backward_blocks_per_site(N, q);
-  return p.bwd_np ? mfma_backward_blocks_per_site(N, q) : backward_blocks_per_site(N);
+  return mfma_backward_blocks_per_site(N, q);
 }
 
 // Once per alignment, before the first forward: the int8 forward's packed
 // symbols, and (backward = true) the gradient path's symbol copy and, for the
 // grouped gradient, the residual rows no forward tile writes.
-hipError_t eval_prepare(const PathSpec& p, const EvalArgs& a, uint8_t* msaT, uint16_t* sorted,
-                        hipStream_t st, bool backward = true) {
+hipError_t eval_prepare(const PathSpec& p, const EvalArgs& a, uint8_t* msaT, hipStream_t st, bool backward = true) {
   if (!backward)
     return p.fwd_i8 ? launch_sym3(a.msa_cm, a.B_pad, a.N, a.NG, const_cast<uint32_t*>(a.sym3), st)
                     : hipSuccess;
   if (p.bwd_g3 || p.bwd_i8) {
     hipError_t e =
-        launch_rfrag_tail_zero(a.R, a.N, a.B, a.B3, a.B_pad, p.bwd_i8 ? kRiChunkBytes : kRfChunkBytes, st);
+        launch_rfrag_tail_zero(a.R, a.N, a.B, a.B3, a.B_pad,
+                               p.bwd_i8 == 4 ? kR4ChunkBytes : p.bwd_i8 ? kRiChunkBytes : kRfChunkBytes, st);
     if (e == hipSuccess && p.f64)  // the remainder digits
       e = launch_rfrag_tail_zero(reinterpret_cast<float*>(reinterpret_cast<char*>(a.R) +
                                                           (size_t)a.N * (a.B_pad >> 8) * kRiChunkBytes),
@@ -340,8 +358,7 @@ hipError_t eval_prepare(const PathSpec& p, const EvalArgs& a, uint8_t* msaT, uin
     const hipError_t e = launch_sym3(a.msa_cm, a.B_pad, a.N, a.NG, const_cast<uint32_t*>(a.sym3), st);
     if (e != hipSuccess) return e;
   }
-  if (p.bwd_np) return launch_transpose_msa(a.msa_cm, a.B_pad, a.N_pad, msaT, st);
-  return launch_chunk_sort(a.msa_cm, a.B3, a.B_pad, a.N, a.q, sorted, st);
+  return launch_transpose_msa(a.msa_cm, a.B_pad, a.N_pad, msaT, st);
 }
 
 // persistent grids: resident blocks of each kernel on the whole device
@@ -355,9 +372,8 @@ Grids eval_grids(const plm_ctx* c, const PathSpec& p, int32_t nb) {
                     : p.fwd_np ? mfma_resident_blocks(KIND_FWD, p.fwd_np)
                                : forward_resident_blocks(nb, p.f64));
   g.bwd = c->ncu * (p.bwd_g3   ? g3_resident_blocks()
-                    : p.bwd_i8 ? i8_resident_blocks()
-                    : p.bwd_np ? mfma_resident_blocks(KIND_BWD, p.bwd_np)
-                               : backward_resident_blocks());
+                    : p.bwd_i8 ? i8_resident_blocks(p.bwd_i8)
+                               : mfma_resident_blocks(KIND_BWD, p.bwd_np));
   return g;
 }
 
@@ -381,13 +397,13 @@ hipError_t eval_forward(const PathSpec& p, const BatchArgs& b, int32_t nb, const
 hipError_t eval_backward(const PathSpec& p, const BatchArgs& b, const Grids& g, hipStream_t st) {
   if (p.bwd_g3) return launch_backward_g3(b, g.bwd, st);
   if (p.bwd_i8) {
-    hipError_t e = launch_backward_i8(b, g.bwd, 0, st);
+    hipError_t e = launch_backward_i8(b, p.bwd_i8, g.bwd, 0, st);
     if (e != hipSuccess || !p.f64) return e;
     // the remainder pass drains the same work items: its queues start again
     e = launch_reset_queues(b, KIND_BWD, st);
-    return e == hipSuccess ? launch_backward_i8(b, g.bwd, 1, st) : e;
+    return e == hipSuccess ? launch_backward_i8(b, p.bwd_i8, g.bwd, 1, st) : e;
   }
-  return p.bwd_np ? launch_backward_mfma(b, p.bwd_np, p.bwd_f16, g.bwd, st) : launch_backward(b, g.bwd, st);
+  return launch_backward_mfma(b, p.bwd_np, p.bwd_f16, g.bwd, st);
 }
 
 EvalArgs eval_args(const EvalBufs& e, const uint8_t* msa_unused, int32_t B, int32_t N, int32_t q,
@@ -400,16 +416,22 @@ EvalArgs eval_args(const EvalBufs& e, const uint8_t* msa_unused, int32_t B, int3
   a.w = w; a.h = h; a.J = J;
   a.R = e.R; a.f_part = e.f_part; a.gh_part = e.gh_part; a.gJ = e.gJ;
   a.tiles = tiles;
-  a.rfrag = ps.f64 ? 3 : ps.bwd_i8 ? 2 : (ps.bwd_g3 ? 1 : 0);
+  a.rfrag = ps.f64 ? 3 : ps.bwd_i8 == 4 ? 4 : ps.bwd_i8 ? 2 : (ps.bwd_g3 ? 1 : 0);
   a.Wq = e.Wq;
   a.jexp = e.jexp;
   a.sym3 = e.sym3;
   a.NG = e.NG;
   a.pad_ = 0;
-  a.sorted = e.sorted;
+  a.wexp = e.jexp;  // (path 0 has no coupling digits)
   a.h_lo = nullptr;
   a.J_lo = nullptr;
   return a;
+}
+
+// finite check of the weights, and for path 0 the scale of its residual digits
+hipError_t check_weights(const PathSpec& p, const double* w, int32_t B, const EvalBufs& e, int32_t* flag,
+                         hipStream_t st) {
+  return p.bwd_i8 == 4 ? launch_weight_exponent(w, B, e.jexp, flag, st) : launch_check_f64(w, (size_t)B, flag, st);
 }
 
 int flags_status(plm_ctx* c) {
@@ -555,26 +577,29 @@ int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
   Tables t;
   layout_tables(bp, 1, N, false, t);
   const BatchArgs b = batch_args(t, 1, N, bwd_group(ps), fwd_group(ps));
-  HIPCHK(c, launch_check_f64(w, (size_t)B, c->pin_dev, c->stream));
-  HIPCHK(c, launch_check_f32(h, (size_t)N * q, c->pin_dev, c->stream));
-  HIPCHK(c, launch_check_f32(J, (size_t)N * N * q * q, c->pin_dev, c->stream));
-  if (grad_scale) HIPCHK(c, launch_check_f64(grad_scale, (size_t)N, c->pin_dev, c->stream));
+  HIPCHK(c, check_weights(ps, w, B, e, c->pin_dev, c->stream));
+  // with every site listed the last kernel, which reads h and J anyway, checks them
+  if (sites) {
+    HIPCHK(c, launch_check_f32(h, (size_t)N * q, c->pin_dev, c->stream));
+    HIPCHK(c, launch_check_f32(J, (size_t)N * N * q * q, c->pin_dev, c->stream));
+    if (grad_scale) HIPCHK(c, launch_check_f64(grad_scale, (size_t)N, c->pin_dev, c->stream));
+  }
   HIPCHK(c, launch_pad_msa(msa, B, N, q, e.msa_cm, e.B_pad, e.N_pad, c->pin_dev, c->stream));
-  const int32_t nb = pick_nb(B, 0);
+  const int32_t nb = pick_nb(N, B, c->ncu, 0);
   const EvalArgs a = eval_args(e, msa, B, N, q, w, h, J, eval_tiles(ps, B, nb), ps);
   HIPCHK(c, launch_setup_msa(b, 0, a, nullptr, 0, N, a.tiles, eval_bwd_blocks(ps, N, q), nullptr,
                              c->stream));
   HIPCHK(c, launch_list_tables(b, sites, 0, n_sites, c->pin_dev, c->stream));
   const Grids g = eval_grids(c, ps, nb);
-  HIPCHK(c, eval_prepare(ps, a, e.msaT, e.sorted, c->stream, gJ_out != nullptr));
+  HIPCHK(c, eval_prepare(ps, a, e.msaT, c->stream, gJ_out != nullptr));
   HIPCHK(c, eval_forward(ps, b, nb, g, c->stream));
   if (gJ_out) HIPCHK(c, eval_backward(ps, b, g, c->stream));
   FinalArgs fa;
   fa.N = N; fa.q = q; fa.tiles = a.tiles; fa.lambda_h = lambda_h; fa.lambda_Jp = 0.5 * lambda_J;
   fa.beff = beff; fa.h = h; fa.J = J; fa.sites = t.active;  // the checked site list
-  fa.f_part = e.f_part; fa.gh_part = e.gh_part; fa.gJ = e.gJ; fa.grad_scale = grad_scale;
+  fa.f_part = e.f_part; fa.gh_part = e.gh_part; fa.gJ = e.gJ; fa.grad_scale = grad_scale; fa.nan_grad = ps.bwd_i8 == 4;
   fa.f_out = f_out; fa.gh_out = gh_out; fa.gJ_out = gJ_out;
-  HIPCHK(c, launch_objgrad_final(fa, n_sites, c->stream));
+  HIPCHK(c, launch_objgrad_final(fa, n_sites, sites ? nullptr : c->pin_dev, c->stream));
   return PLM_OK;
 }
 
@@ -713,7 +738,7 @@ int prepare_fit(plm_ctx* c, const plm_msa_desc* d, int32_t n, int32_t q, const p
     return set_err(c, PLM_E_UNSUPPORTED, "evaluation path %d is not available", o->path);
   if (o->single_site && n != 1)
     return set_err(c, PLM_E_INVALID, "the single-site path takes one alignment");
-  int32_t total = 0, Bmax = 0;
+  int32_t total = 0;
   for (int32_t k = 0; k < n; ++k) {
     const plm_msa_desc& m = d[k];
     if (!m.msa || !m.w || !m.beff || !m.h_io || !m.J_io)
@@ -722,7 +747,6 @@ int prepare_fit(plm_ctx* c, const plm_msa_desc* d, int32_t n, int32_t q, const p
     if (rc) return rc;
     if (!path_fits(ps, m.B)) return set_err(c, PLM_E_UNSUPPORTED, "path %d sums at most 2^24 - 1 sequences exactly", o->path);
     total += m.N;
-    if (m.B > Bmax) Bmax = m.B;
   }
   const size_t need = fit_layout(d, n, q, o, nullptr, nullptr, nullptr);
   int rc = check_ws(c, ws, ws_bytes, need);
@@ -742,19 +766,19 @@ int prepare_fit(plm_ctx* c, const plm_msa_desc* d, int32_t n, int32_t q, const p
   hipStream_t st = c->fit_stream;
   c->pin[1] = total;
 
-  const int32_t nb = pick_nb(Bmax, o->tile_seqs);
+  const int32_t nb = pick_nb(d[ord[0]].N, d[ord[0]].B, c->ncu, o->tile_seqs);  // for the largest alignment
   std::vector<int32_t> base(n + 1, 0);
   for (int32_t k = 0; k < n; ++k) {
     const plm_msa_desc& m = d[ord[k]];
     const FitBufs& f = fb[k];
     base[k + 1] = base[k] + m.N;
-    HIPCHK(c, launch_check_f64(m.w, (size_t)m.B, c->pin_dev, st));
+    HIPCHK(c, check_weights(ps, m.w, m.B, f.ev, c->pin_dev, st));
     HIPCHK(c, launch_check_f32(m.h_io, (size_t)m.N * q, c->pin_dev, st));
     HIPCHK(c, launch_pad_msa(m.msa, m.B, m.N, q, f.ev.msa_cm, f.ev.B_pad, f.ev.N_pad, c->pin_dev, st));
     HIPCHK(c, launch_init_fit(m.N, q, m.h_io, m.J_io, f.Th, f.TJ, t.st + base[k], phase_host_dev + base[k], st));
     HIPCHK(c, launch_check_f32(m.J_io, (size_t)m.N * m.N * q * q, c->pin_dev, st));
     const EvalArgs a = eval_args(f.ev, m.msa, m.B, m.N, q, m.w, f.Th, f.TJ, eval_tiles(ps, m.B, nb), ps);
-    HIPCHK(c, eval_prepare(ps, a, f.ev.msaT, f.ev.sorted, st));
+    HIPCHK(c, eval_prepare(ps, a, f.ev.msaT, st));
     LbfgsArgs L;
     L.N = m.N; L.q = q; L.m = o->lbfgs_m; L.max_iter = o->max_iter; L.max_ls = o->max_linesearch;
     L.tiles = a.tiles; L.tol = o->tol; L.lambda_h = o->lambda_h; L.lambda_Jp = 0.5 * o->lambda_J;
@@ -1092,7 +1116,7 @@ int plm_tune(plm_ctx* c, const plm_msa_desc* descs, int32_t n_msas, int32_t q, c
     }
     plm_tune_result r;
     r.path = cd.path;
-    r.tile_seqs = cd.tile == 0 ? 0 : pick_nb(0, cd.tile);
+    r.tile_seqs = cd.tile;
     r.eval_ms = best;
     res.push_back(r);
   }
@@ -1219,9 +1243,9 @@ int run_sym_once(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
     for (int32_t i = r + 1; i < N; ++i) pairs.push_back(make_int2(r, i));
   HIPCHK(c, hipMemcpyAsync(f.pairs, pairs.data(), pairs.size() * sizeof(int2), hipMemcpyHostToDevice, st));
 
-  const int32_t nb = pick_nb(B, o->tile_seqs);
+  const int32_t nb = pick_nb(N, B, c->ncu, o->tile_seqs);
   const BatchArgs b = batch_args(f.t, 1, N, bwd_group(ps), fwd_group(ps));
-  HIPCHK(c, launch_check_f64(w, (size_t)B, c->pin_dev, st));
+  HIPCHK(c, check_weights(ps, w, B, f.ev, c->pin_dev, st));
   HIPCHK(c, launch_check_f32(h_io, (size_t)N * q, c->pin_dev, st));
   HIPCHK(c, launch_check_f32(J_io, (size_t)N * N * q * q, c->pin_dev, st));
   if (lo) {
@@ -1234,7 +1258,7 @@ int run_sym_once(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
     a.h_lo = f.Thl;
     a.J_lo = f.TJl;
   }
-  HIPCHK(c, eval_prepare(ps, a, f.ev.msaT, f.ev.sorted, st));
+  HIPCHK(c, eval_prepare(ps, a, f.ev.msaT, st));
   HIPCHK(c, launch_setup_msa(b, 0, a, nullptr, 0, N, a.tiles, eval_bwd_blocks(ps, N, q), nullptr, st));
   HIPCHK(c, launch_list_tables(b, nullptr, 0, N, nullptr, st));
 

@@ -30,14 +30,6 @@ constexpr int kFwdThreads = kFwdWaves * 64;
 constexpr int kBPadUnit = 3072;
 static_assert(kBPadUnit % (kFwdWaves * kSlots * 64) == 0 && kBPadUnit % 256 == 0, "row padding");
 constexpr int kFwdChunk = 16;
-// Backward kernel: 16 waves; the three slots of a wave own three different
-// alignment columns (48 per block).  Sequences are processed in chunks of 192
-// whose rows are sorted by symbol at every column (once per alignment).
-constexpr int kBwdWaves = 16;
-constexpr int kBwdThreads = kBwdWaves * 64;
-constexpr int kBwdPos = kBwdWaves * kSlots;  // 48
-constexpr int kBwdSeqChunk = 192;
-
 // Per-site optimiser state (device).
 struct SiteState {
   int32_t phase;       // 0 first evaluation pending, 1 line search, 2 done
@@ -87,8 +79,9 @@ struct EvalArgs {
   double* gJ;              // [N][N][q][q] data part of d f / d J (FP64)
   int32_t tiles;
   int32_t rfrag;           // R in gradient-fragment order: 1 FP16 hi/lo pieces, 2 int8 digits, 3 two int8 digit
-                           // sets (R and its remainder; the second set after N * B_pad/256 chunks; see below)
-  const uint16_t* sorted;  // [nchunks][N][kBwdSeqChunk]: (row << 8) | symbol, rows sorted by symbol
+                           // sets (R and its remainder; the second set after N * B_pad/256 chunks), 4 four
+                           // int8 digits (see below)
+  const int32_t* wexp;     // path 0: exponent e with every |w_b| <= 2^e (the residual digits' scale)
   // int8 forward (path 6): couplings as fixed-point digits, symbols by position triple
   int8_t* Wq;              // [N][NG][3 digits][2 steps][2 halves][21 states][16] bytes
   int32_t* jexp;           // [N] scale exponent: digits of round(J * 2^jexp); then [N][kJParts] partial maxima
@@ -128,6 +121,15 @@ __device__ inline size_t rifrag_index(int32_t r, int32_t nch, int32_t b, int32_t
   return ((((c * 3) * 8 + ((b >> 5) & 7)) * 2 + ((b >> 4) & 1)) * kSlot + s) * 16 + (b & 15);
 }
 
+// Path 0 (rfrag = 4): v = round(R_b(s) * 2^(30 - e)) with |R| <= |w_b| <= 2^e,
+// so |v| <= 2^30: 32 bits, as four signed int8 digits, in chunks of 256
+// sequences as above with four digit planes (21504 bytes per chunk and site).
+constexpr int kR4ScaleLog2 = 30;
+constexpr int kR4ChunkBytes = 4 * kRiDigitBytes;            // 21504
+__device__ inline size_t r4frag_index(int32_t r, int32_t nch, int32_t b, int32_t s) {
+  const size_t c = (size_t)r * nch + (b >> 8);
+  return ((((c * 4) * 8 + ((b >> 5) & 7)) * 2 + ((b >> 4) & 1)) * kSlot + s) * 16 + (b & 15);
+}
 
 // Arguments of the optimiser kernel (one block per site).
 struct LbfgsArgs {
@@ -170,6 +172,7 @@ struct FinalArgs {
   const double* gh_part;
   const double* gJ;
   const double* grad_scale;  // nullable per-site gradient multiplier
+  int32_t nan_grad;          // a NaN objective makes the site's coupling gradient NaN (its digits cannot carry one)
   double* f_out;
   float* gh_out;
   float* gJ_out;
@@ -210,19 +213,35 @@ struct Item {
   int32_t m, g, r, sub, first, cnt;
 };
 
-// Next work item of a persistent block (call from one thread).  The block
-// starts on queue blockIdx % kQueues -- under round-robin dispatch, the queue
-// of its XCD, so that consecutive items of one site share that XCD's L2 --
-// and moves to the following queues when its own is empty.  qi counts the
-// queues finished; -1 is returned once all are empty, so every block exits.
+// Next work item of a persistent block (call from one thread; qi starts at
+// -1).  The block starts on queue blockIdx % kQueues -- under round-robin
+// dispatch, the queue of its XCD, so that consecutive items of one site share
+// that XCD's L2 -- and moves to the following queues when its own is empty.
+// The first item of each block is its place in its queue, taken without an
+// atomic; a queue's counter counts the items after those, and a queue with no
+// more items than blocks starting on it is never asked (an atomic on an empty
+// queue costs a trip to memory, and a launch with few items paid eight).  qi
+// counts the queues finished; -1 is returned once all are empty, so every
+// block exits.
 __device__ inline int32_t next_item(uint32_t* ctr, int32_t total, int32_t& qi) {
+  auto range = [&](int32_t x, int32_t& lo, int32_t& n) {
+    lo = (int32_t)(((int64_t)total * x) / kQueues);
+    n = (int32_t)(((int64_t)total * (x + 1)) / kQueues) - lo;
+  };
+  int32_t lo, n;
+  if (qi < 0) {
+    qi = 0;
+    range((int32_t)(blockIdx.x % kQueues), lo, n);
+    const int32_t k = (int32_t)(blockIdx.x / kQueues);
+    if (k < n) return lo + k;
+  }
   while (qi < kQueues) {
     const int32_t x = (int32_t)((blockIdx.x + (uint32_t)qi) % kQueues);
-    const int32_t lo = (int32_t)(((int64_t)total * x) / kQueues);
-    const int32_t hi = (int32_t)(((int64_t)total * (x + 1)) / kQueues);
-    if (lo < hi) {
-      const int32_t k = (int32_t)atomicAdd(&ctr[x], 1u);
-      if (lo + k < hi) return lo + k;
+    range(x, lo, n);
+    const int32_t first = ((int32_t)gridDim.x - x + kQueues - 1) / kQueues;  // blocks that start on queue x
+    if (first < n) {
+      const int32_t k = first + (int32_t)atomicAdd(&ctr[x], 1u);
+      if (k < n) return lo + k;
     }
     ++qi;
   }
@@ -392,6 +411,12 @@ struct ScoreOpts {
 };
 
 // Device helpers ----------------------------------------------------------
+// orders a wave's LDS accesses (they execute in program order; this keeps the compiler's order)
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ inline double block_sum_f64(double v, double* red) {
   // deterministic: fixed shuffle tree per wave, then waves summed in order
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -413,8 +438,8 @@ hipError_t launch_pad_msa(const uint8_t* msa, int32_t B, int32_t N, int32_t q, u
                           int32_t B_pad, int32_t N_pad, int32_t* flag_dev, hipStream_t st);
 hipError_t launch_transpose_msa(const uint8_t* msa_cm, int32_t B_pad, int32_t N_pad, uint8_t* msaT,
                                 hipStream_t st);
-hipError_t launch_chunk_sort(const uint8_t* msa_cm, int32_t B3, int32_t B_pad, int32_t N, int32_t q,
-                             uint16_t* sorted, hipStream_t st);
+// finite check of the weights (bit 2 of *flag) and the exponent of the largest
+hipError_t launch_weight_exponent(const double* w, int32_t B, int32_t* wexp, int32_t* flag, hipStream_t st);
 int32_t forward_tile_seqs(int32_t nb);
 // f64: 0 FP32 accumulation, 1 FP64 (the precise path), 2 FP64 reading the
 // low-order words of the point as well (EvalArgs.h_lo, J_lo)
@@ -423,9 +448,6 @@ int32_t forward_resident_blocks(int32_t nb, int32_t f64);
 // residuals out as two int8 digit sets; its own tile of forward_f64_tile_seqs rows)
 hipError_t launch_forward(const BatchArgs& b, int32_t nb, int32_t nblocks, int32_t f64, hipStream_t st);
 int32_t forward_f64_tile_seqs();
-int32_t backward_blocks_per_site(int32_t N);
-int32_t backward_resident_blocks();
-hipError_t launch_backward(const BatchArgs& b, int32_t nblocks, hipStream_t st);
 int32_t mfma_forward_tile_seqs();
 int32_t mfma_backward_blocks_per_site(int32_t N, int32_t q);
 int32_t mfma_resident_blocks(int32_t kind, int32_t npieces);
@@ -450,9 +472,10 @@ hipError_t launch_jquant(const BatchArgs& b, int32_t total_sites, hipStream_t st
 hipError_t launch_fwd_i8(const BatchArgs& b, int32_t nblocks, hipStream_t st);
 // grouped int8 fixed-point MFMA gradient (three sites per item, R as digits)
 int32_t i8_backward_blocks_per_site(int32_t N, int32_t q);
-int32_t i8_resident_blocks();
+// digits: 3 (paths 5 to 7) or 4 (path 0)
+int32_t i8_resident_blocks(int32_t digits);
 // lo: the second pass of the precise path (the remainder digits, added in)
-hipError_t launch_backward_i8(const BatchArgs& b, int32_t nblocks, int32_t lo, hipStream_t st);
+hipError_t launch_backward_i8(const BatchArgs& b, int32_t digits, int32_t nblocks, int32_t lo, hipStream_t st);
 hipError_t launch_forward_mfma(const BatchArgs& b, int32_t npieces, int32_t nblocks, hipStream_t st);
 hipError_t launch_backward_mfma(const BatchArgs& b, int32_t npieces, int32_t f16, int32_t nblocks,
                                 hipStream_t st);
@@ -491,7 +514,8 @@ hipError_t launch_score_ex(const float* J, int32_t N, int32_t q, const ScoreOpts
                            const double* freq, double* raw, double* cor, hipStream_t st);
 hipError_t launch_frequencies(const uint8_t* msa, int32_t B, int32_t N, int32_t q, const double* w,
                               const double* beff, double* f, hipStream_t st);
-hipError_t launch_objgrad_final(const FinalArgs& a, int32_t nsites, hipStream_t st);
+// check (nullable): flag word raised for non-finite h, J or grad_scale of the listed sites
+hipError_t launch_objgrad_final(const FinalArgs& a, int32_t nsites, int32_t* check, hipStream_t st);
 hipError_t launch_check_f32(const float* p, size_t n, int32_t* flag, hipStream_t st);
 hipError_t launch_probe(const ProbeArgs& p, hipStream_t st);
 hipError_t launch_check_f64(const double* p, size_t n, int32_t* flag, hipStream_t st);

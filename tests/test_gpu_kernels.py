@@ -72,3 +72,41 @@ def test_frequencies_sizes(plm, B, N, q):
     w = rng.uniform(0.01, 1.0, size=B)
     f = plm.frequencies(_to(msa), _to(w), _to(np.array([w.sum()])), q)
     np.testing.assert_allclose(f.cpu().numpy(), sv.frequencies(msa, w, float(w.sum()), q), rtol=1e-12, atol=1e-15)
+
+
+# the four-digit gradient of path 0: one and two row groups per chunk, three-site groups with
+# remainders, weights above one and over eight decades, all-zero weights
+@pytest.mark.parametrize("B,N,q,wexp", [(1, 2, 2, 0), (255, 4, 21, 0), (257, 25, 21, 3), (513, 24, 5, -4),
+                                        (3100, 49, 21, 0), (700, 31, 21, 12), (300, 7, 21, None)])
+def test_path0_gradient_digits(plm, B, N, q, wexp):
+    from tests.helpers import random_params
+    print(f"path 0 gradient B={B} N={N} q={q} wexp={wexp}", flush=True)
+    rng = np.random.default_rng(B + N)
+    msa = rng.integers(0, q, size=(B, N), dtype=np.uint8)
+    w = np.zeros(B) if wexp is None else 2.0 ** wexp * 10.0 ** rng.uniform(-8 if wexp == 12 else -1, 0, size=B)
+    beff = max(float(w.sum()), 1.0)
+    h, J = random_params(B + N, N, q, 0.3, 0.2)
+    h, J = h.astype(np.float32), J.astype(np.float32)
+    f, gh, gJ = plm.objgrad(_to(msa), _to(w), _to(np.array([beff])), _to(h), _to(J), path=0)
+    plm.sync(DEV)
+    fo, gho, gJo = oracle.objgrad(msa, w, beff, h.astype(np.float64), J.astype(np.float64))
+    # FP32 energies: each probability is off by about sqrt(N) 2^-24 max|E|; the digits by 2^-31 max w per
+    # sequence, the result by its FP32 rounding: the bounds the FP32 paths are held to
+    assert np.max(np.abs(f.cpu().numpy() - fo)) <= 1e-5 * max(1.0, np.max(np.abs(fo)))
+    assert np.max(np.abs(gh.cpu().numpy() - gho)) <= 2e-6 * beff
+    assert np.max(np.abs(gJ.cpu().numpy() - gJo)) <= 2e-6 * beff
+
+
+def test_path0_gradient_carries_nan(plm):
+    """Energies that overflow give a NaN objective and a NaN gradient, not the digits of one."""
+    print("path 0 gradient NaN", flush=True)
+    rng = np.random.default_rng(3)
+    B, N, q = 90, 5, 21
+    msa = rng.integers(0, q, size=(B, N), dtype=np.uint8)
+    J = np.zeros((N, N, q, q), dtype=np.float32)
+    J[2] = 3e38
+    h = np.zeros((N, q), dtype=np.float32)
+    f, gh, gJ = plm.objgrad(_to(msa), _to(np.ones(B)), _to(np.array([float(B)])), _to(h), _to(J), path=0)
+    torch.cuda.synchronize()
+    assert torch.isnan(f[2]) and torch.isnan(gh[2]).any() and torch.isnan(gJ[2, 0]).any()
+    assert torch.isfinite(f[0]) and torch.isfinite(gJ[0]).all()
