@@ -110,3 +110,21 @@ def test_path0_gradient_carries_nan(plm):
     torch.cuda.synchronize()
     assert torch.isnan(f[2]) and torch.isnan(gh[2]).any() and torch.isnan(gJ[2, 0]).any()
     assert torch.isfinite(f[0]) and torch.isfinite(gJ[0]).all()
+
+
+# block sweep of 1, 2, 3, 5 and 11 units of 64 indices (a last pivot block of one unit and of two), and more
+# sequences of one state than a wave takes at once
+@pytest.mark.parametrize("N,B,q", [(3, 2000, 21), (6, 900, 21), (9, 700, 21), (16, 400, 21), (35, 260, 21), (90, 300, 6)])
+def test_mean_field_block_sweep(plm, N, B, q):
+    from oracle import meanfield
+    print(f"mean field N={N} B={B} q={q}", flush=True)
+    rng = np.random.default_rng(N)
+    msa = rng.integers(0, q, size=(B, N), dtype=np.uint8)
+    msa[:, 1] = np.where(rng.uniform(size=B) < 0.5, msa[:, 0], msa[:, 1])
+    w = rng.uniform(0.1, 1.0, size=B)
+    beff = float(w.sum())
+    h, J = plm.mf_init(_to(msa), _to(w), _to(np.array([beff])), q=q)
+    h_o, J_o = meanfield.couplings(msa, w, beff, q=q, lam=0.5)
+    # FP64 throughout, results rounded to FP32
+    assert np.max(np.abs(J.cpu().numpy() - J_o)) <= 1e-6 * max(1.0, np.max(np.abs(J_o)))
+    assert np.max(np.abs(h.cpu().numpy() - h_o)) <= 1e-6 * max(1.0, np.max(np.abs(h_o)))
