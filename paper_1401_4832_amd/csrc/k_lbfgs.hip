@@ -548,51 +548,63 @@ __global__ __launch_bounds__(256) void lbfgs_coef_kernel(BatchArgs b) {
   const auto YG = SG + M;                                           // [M] y_k . G by slot
   const int nv = 4 + 2 * stored;
   for (int k = tid; k < nv; k += nth) {
-    double t = 0.0;
-    for (int c = 0; c < kLbChunks; ++c) t += site_part(a, r, c)[k];
+    const auto p = gmem(site_part(a, r, 0)) + k;
+    double v[kLbChunks], t = 0.0;
+#pragma unroll
+    for (int c = 0; c < kLbChunks; ++c) v[c] = p[c * kLbPartW];
+#pragma unroll
+    for (int c = 0; c < kLbChunks; ++c) t += v[c];
     sh.vals[k] = t;
   }
   __syncthreads();
   double gamma = S->gamma;
-  if (tid == 0) {
+  if (tid < 64) {
     const double sy = sh.vals[0], yy = sh.vals[1];
+    const bool keep = sy > 0.0 && yy > 0.0;
     // S^T g and Y^T g at the new point: the stored products moved by the
-    // candidate's y (G changes by y whether or not the pair is kept)
-    for (int j = 0; j < stored; ++j) {
-      const int k = (head - 1 - j + 2 * M) % M;
-      const double pg1 = SG[k] + sh.vals[4 + 2 * j], pg2 = YG[k] + sh.vals[5 + 2 * j];
+    // candidate's y (G changes by y whether or not the pair is kept); lane j
+    // takes stored pair j (newest first)
+    double pg1 = 0.0, pg2 = 0.0;
+    const int k = (head - 1 - tid + 2 * M) % M;  // (stored <= m <= 32 lanes)
+    if (tid < stored) {
+      pg1 = SG[k] + sh.vals[4 + 2 * tid];
+      pg2 = YG[k] + sh.vals[5 + 2 * tid];
       SG[k] = pg1;
       YG[k] = pg2;
-      sh.p1[j] = pg1;
-      sh.p2[j] = pg2;
     }
-    if (sy > 0.0 && yy > 0.0) {
+    if (keep) {
       // keep the candidate: its column of S^T Y and its row/column of Y^T Y;
       // it becomes the newest pair (index 0 of the newest-first lists)
       const int c = head;
-      for (int j = 0; j < stored; ++j) {
-        const int k = (head - 1 - j + 2 * M) % M;
-        StY[k * M + c] = sh.vals[4 + 2 * j];
-        YtY[k * M + c] = sh.vals[5 + 2 * j];
-        YtY[c * M + k] = sh.vals[5 + 2 * j];
+      if (tid < stored) {
+        StY[k * M + c] = sh.vals[4 + 2 * tid];
+        YtY[k * M + c] = sh.vals[5 + 2 * tid];
+        YtY[c * M + k] = sh.vals[5 + 2 * tid];
+        if (tid + 1 < m) {
+          sh.p1[tid + 1] = pg1;
+          sh.p2[tid + 1] = pg2;
+        }
       }
-      StY[c * M + c] = sy;
-      YtY[c * M + c] = yy;
-      for (int j = min(stored, m - 1); j > 0; --j) {
-        sh.p1[j] = sh.p1[j - 1];
-        sh.p2[j] = sh.p2[j - 1];
+      if (tid == 0) {
+        StY[c * M + c] = sy;
+        YtY[c * M + c] = yy;
+        sh.p1[0] = sh.vals[2];
+        sh.p2[0] = sh.vals[3];
+        SG[c] = sh.vals[2];
+        YG[c] = sh.vals[3];
       }
-      sh.p1[0] = sh.vals[2];
-      sh.p2[0] = sh.vals[3];
-      SG[c] = sh.vals[2];
-      YG[c] = sh.vals[3];
       gamma = sy / yy;
       head = (head + 1) % M;
       if (stored < m) ++stored;
+    } else if (tid < stored) {
+      sh.p1[tid] = pg1;
+      sh.p2[tid] = pg2;
     }
-    sh.gamma = gamma;
-    sh.head = head;
-    sh.stored = stored;
+    if (tid == 0) {
+      sh.gamma = gamma;
+      sh.head = head;
+      sh.stored = stored;
+    }
   }
   __syncthreads();
   head = __builtin_amdgcn_readfirstlane(sh.head);
@@ -621,27 +633,7 @@ __global__ __launch_bounds__(256) void lbfgs_coef_kernel(BatchArgs b) {
     sh.YYm[e] = YtY[sh.ord[i] * M + sh.ord[j]];
   }
   __syncthreads();
-  if (tid == 0) {
-    // R t = S^T g (back substitution); p1, p2 are newest first
-    for (int i = n - 1; i >= 0; --i) {
-      double x = sh.p1[n - 1 - i];
-      for (int l = i + 1; l < n; ++l) x -= sh.Rm[i * n + l] * sh.tv[l];
-      sh.tv[i] = x / sh.Rm[i * n + i];
-    }
-    // R^T q1 = D t + gamma Y^T Y t - gamma Y^T g (forward substitution), q1 in cs
-    for (int i = 0; i < n; ++i) {
-      double yyt = 0.0;
-      for (int l = 0; l < n; ++l) yyt += sh.YYm[i * n + l] * sh.tv[l];
-      double x = sh.Rm[i * n + i] * sh.tv[i] + gamma * (yyt - sh.p2[n - 1 - i]);
-      for (int l = 0; l < i; ++l) x -= sh.Rm[l * n + i] * sh.cs[l];
-      sh.cs[i] = x / sh.Rm[i * n + i];
-    }
-    // d = -gamma g - S q1 + gamma Y t
-    for (int i = 0; i < n; ++i) {
-      sh.cs[i] = -sh.cs[i];
-      sh.cy[i] = gamma * sh.tv[i];
-    }
-  }
+  if (tid < 64) compact_solve(n, gamma, sh.Rm, sh.YYm, sh.p1, sh.p2, sh.tv, sh.cs, sh.cy);
   __syncthreads();
   DirCoef* C = a.dc + r;
   if (tid < n) {

@@ -58,8 +58,11 @@ __device__ inline void for_each_param(const SymArgs& a, F&& f) {
   }
 }
 
+// The partial sums of a block: quantity k of block b at part[k * nblk + b], so
+// that a wave adding one quantity over the blocks reads contiguously (by block,
+// the solve kernel's single CU fetched a cache line per value).
 template <int NV>
-__device__ inline void block_partials(double (&v)[NV], double* red, double* out) {
+__device__ inline void block_partials(double (&v)[NV], double* red, double* part, int32_t nblk) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
   for (int k = 0; k < NV; ++k)
@@ -73,17 +76,18 @@ __device__ inline void block_partials(double (&v)[NV], double* red, double* out)
   if (threadIdx.x < NV) {
     double t = 0.0;
     for (int w = 0; w < nw; ++w) t += red[w * NV + threadIdx.x];
-    out[threadIdx.x] = t;
+    part[(size_t)threadIdx.x * nblk + blockIdx.x] = t;
   }
 }
 
-// Sum of base[k * stride], k < count, over one wavefront: lane l takes
+// Sum of base[k], k < count, over one wavefront: lane l takes
 // k = l, l + 64, ...; the lanes are combined in a fixed tree.  The value of
 // lane 0 is the result (the other lanes may differ in the last bits).
-__device__ inline double wave_sum_strided(const double* base, int count, int stride) {
+__device__ inline double wave_sum(const double* base, int count) {
   const int lane = threadIdx.x & 63;
   double t = 0.0;
-  for (int k = lane; k < count; k += 64) t += base[(size_t)k * stride];
+#pragma unroll 8
+  for (int k = lane; k < count; k += 64) t += base[k];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
   return t;
@@ -125,7 +129,7 @@ __global__ __launch_bounds__(kSymThreads) void sym_eval_kernel(SymArgs a) {
   });
   const size_t nf = (size_t)a.tiles * a.N, step = (size_t)gridDim.x * blockDim.x;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < nf; e += step) v[2] += a.f_part[e];
-  block_partials(v, red, a.part + (size_t)blockIdx.x * kSymPart);
+  block_partials(v, red, a.part, a.nblk);
 }
 
 __global__ __launch_bounds__(kSymThreads) void sym_decide_kernel(SymArgs a) {
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(kSymThreads) void sym_decide_kernel(SymArgs a) {
   if (S->phase == PH_DONE) return;
   const int wid = threadIdx.x >> 6;
   if (wid < 3) {
-    const double t = wave_sum_strided(a.part + wid, a.nblk, kSymPart);
+    const double t = wave_sum(a.part + (size_t)wid * a.nblk, a.nblk);
     if ((threadIdx.x & 63) == 0) tot[wid] = t;
   }
   __syncthreads();
@@ -261,7 +265,7 @@ __global__ __launch_bounds__(kSymThreads) void sym_accept_kernel(SymArgs a) {
   };
   if (pair) with_count<0, kSymGroup>(nA, pass);
   else pass(std::integral_constant<int, 0>{});
-  block_partials(v, red, a.part + (size_t)blockIdx.x * kSymPart);
+  block_partials(v, red, a.part, a.nblk);
 }
 
 // dot products of stored pairs group*4 .. group*4+3 with the candidate y and the new g
@@ -300,100 +304,117 @@ __global__ __launch_bounds__(kSymThreads) void sym_group_kernel(SymArgs a, int32
       }
     });
   });
-  block_partials(v, red, a.part + ((size_t)(1 + group) * a.nblk + blockIdx.x) * kSymPart);
+  block_partials(v, red, a.part + (size_t)(1 + group) * a.nblk * kSymPart, a.nblk);
 }
 
-// Curvature test, small-matrix update and the compact-form coefficients
-// (block sums in parallel, the rest on one thread; n <= 32).
-__global__ __launch_bounds__(kSymThreads) void sym_solve_kernel(SymArgs a) {
+// Curvature test, small-matrix update and the compact-form coefficients: block
+// sums by the waves, the rest by one wave from LDS (one thread on global memory
+// took 72 us of a 640 us iteration at N = 120; 12 us now, with the block sums stored by quantity).
+constexpr int kSolveThreads = 1024;
+__global__ __launch_bounds__(kSolveThreads) void sym_solve_kernel(SymArgs a) {
   __shared__ double tot[4 + 4 * kMMax];
-  __shared__ double t[kMMax];
+  __shared__ double tv[kMMax], cs[kMMax], cy[kMMax], p1[kMMax + 1], p2[kMMax + 1];
+  __shared__ double Rm[kMMax * kMMax], YYm[kMMax * kMMax];
+  __shared__ int32_t ord[kMMax];
   SymState* S = a.st;
   if (!S->accept) return;
+  const int tid = threadIdx.x;
   const int m = a.m, M = m + 1;
   SymCoef* C = a.coef;
   double* StY = a.small;
   double* YtY = a.small + (size_t)M * M;
   int stored = S->stored, head = S->head;
-  if (S->pair) {
+  const bool pair = S->pair;
+  double gamma = S->gamma;
+  if (pair) {
     // block sums of the candidate's dot products (quantity 0..3) and of the
     // stored pairs' (4 + 4 j + k, newest first), one wavefront per quantity
     const int nq = 4 + 4 * stored;
-    for (int qi = threadIdx.x >> 6; qi < nq; qi += kSymThreads / 64) {
+    for (int qi = tid >> 6; qi < nq; qi += kSolveThreads / 64) {
       const double* base;
       if (qi < 4 + 4 * kSymGroup) {
-        base = a.part + qi;
+        base = a.part + (size_t)qi * a.nblk;
       } else {
         const int j = (qi - 4) >> 2, k = (qi - 4) & 3;
         const int grp = 1 + (j - kSymGroup) / kSymGroup, p = (j - kSymGroup) % kSymGroup;
-        base = a.part + (size_t)grp * a.nblk * kSymPart + 4 * p + k;
+        base = a.part + ((size_t)grp * kSymPart + 4 * p + k) * a.nblk;
       }
-      const double v = wave_sum_strided(base, a.nblk, kSymPart);
-      if ((threadIdx.x & 63) == 0) tot[qi] = v;
+      const double v = wave_sum(base, a.nblk);
+      if ((tid & 63) == 0) tot[qi] = v;
     }
-    __syncthreads();
   }
-  if (threadIdx.x != 0) return;
-  if (S->pair) {
-    for (int j = 0; j < stored; ++j) {
-      C->colS[j] = tot[4 + 4 * j];
-      C->colY[j] = tot[5 + 4 * j];
-      C->p1[j] = tot[6 + 4 * j];
-      C->p2[j] = tot[7 + 4 * j];
+  __syncthreads();
+  const int phase = S->phase;
+  // the lists p1, p2 (S^T g, Y^T g, newest first) live in C between accepted points without a pair
+  if (tid < stored) {
+    p1[tid] = pair ? tot[6 + 4 * tid] : C->p1[tid];
+    p2[tid] = pair ? tot[7 + 4 * tid] : C->p2[tid];
+  }
+  __syncthreads();
+  if (pair && tot[0] > 0.0 && tot[1] > 0.0) {
+    // keep the candidate: lane j puts the products with stored pair j in place
+    const double sy = tot[0], yy = tot[1];
+    const int c = head;
+    double q1 = 0.0, q2 = 0.0;
+    if (tid < stored) {
+      const int k = (head - 1 - tid + 2 * M) % M;
+      StY[k * M + c] = tot[4 + 4 * tid];
+      YtY[k * M + c] = tot[5 + 4 * tid];
+      YtY[c * M + k] = tot[5 + 4 * tid];
+      q1 = p1[tid];
+      q2 = p2[tid];
     }
-    const double cand[4] = {tot[0], tot[1], tot[2], tot[3]};
-    const double sy = cand[0], yy = cand[1];
-    if (sy > 0.0 && yy > 0.0) {
-      const int c = head;
-      for (int j = 0; j < stored; ++j) {
-        const int k = (head - 1 - j + 2 * M) % M;
-        StY[k * M + c] = C->colS[j];
-        YtY[k * M + c] = C->colY[j];
-        YtY[c * M + k] = C->colY[j];
-      }
+    if (tid == 0) {
       StY[c * M + c] = sy;
       YtY[c * M + c] = yy;
-      for (int j = min(stored, m - 1); j > 0; --j) {
-        C->p1[j] = C->p1[j - 1];
-        C->p2[j] = C->p2[j - 1];
+    }
+    __syncthreads();
+    if (tid < stored && tid + 1 < m) {
+      p1[tid + 1] = q1;
+      p2[tid + 1] = q2;
+    }
+    if (tid == 0) {
+      p1[0] = tot[2];
+      p2[0] = tot[3];
+    }
+    gamma = sy / yy;
+    head = (head + 1) % M;
+    if (stored < m) ++stored;
+  }
+  __syncthreads();  // (the block's own writes to StY, YtY are read back below)
+  if (tid < stored) {
+    C->p1[tid] = p1[tid];
+    C->p2[tid] = p2[tid];
+  }
+  const int n = stored;
+  if (phase != PH_DONE && n > 0) {
+    if (tid < n) ord[tid] = (head - n + tid + 2 * M) % M;
+    __syncthreads();
+    for (int e = tid; e < n * n; e += kSolveThreads) {
+      const int i = e / n, j = e - i * n;
+      Rm[e] = StY[ord[i] * M + ord[j]];
+      YYm[e] = YtY[ord[i] * M + ord[j]];
+    }
+    __syncthreads();
+    if (tid < 64) {
+      compact_solve(n, gamma, Rm, YYm, p1, p2, tv, cs, cy);
+      wave_sync();
+      if (tid < n) {
+        C->cs[tid] = cs[tid];
+        C->cy[tid] = cy[tid];
+        C->ord[tid] = ord[tid];
       }
-      C->p1[0] = cand[2];
-      C->p2[0] = cand[3];
-      S->gamma = sy / yy;
-      head = (head + 1) % M;
-      if (stored < m) ++stored;
     }
   }
-  S->head = head;
-  S->stored = stored;
-  if (S->phase == PH_DONE) return;
-  if (stored == 0) {
-    S->dir = SD_STEEPEST;
-    return;
+  if (tid == 0) {
+    S->head = head;
+    S->stored = n;
+    S->gamma = gamma;
+    if (phase != PH_DONE) {
+      S->dir = n > 0 ? SD_QN : SD_STEEPEST;
+      if (n > 0) C->n = n;
+    }
   }
-  S->dir = SD_QN;
-  const int n = stored;
-  const double gamma = S->gamma;
-  for (int i = 0; i < n; ++i) C->ord[i] = (head - n + i + 2 * M) % M;
-  auto R = [&](int i, int j) { return StY[C->ord[i] * M + C->ord[j]]; };
-  auto YY = [&](int i, int j) { return YtY[C->ord[i] * M + C->ord[j]]; };
-  for (int i = n - 1; i >= 0; --i) {
-    double x = C->p1[n - 1 - i];
-    for (int l = i + 1; l < n; ++l) x -= R(i, l) * t[l];
-    t[i] = x / R(i, i);
-  }
-  for (int i = 0; i < n; ++i) {
-    double yyt = 0.0;
-    for (int l = 0; l < n; ++l) yyt += YY(i, l) * t[l];
-    double x = R(i, i) * t[i] + gamma * (yyt - C->p2[n - 1 - i]);
-    for (int l = 0; l < i; ++l) x -= R(l, i) * C->cs[l];
-    C->cs[i] = x / R(i, i);
-  }
-  for (int i = 0; i < n; ++i) {
-    C->cs[i] = -C->cs[i];
-    C->cy[i] = gamma * t[i];
-  }
-  C->n = n;
 }
 
 __global__ __launch_bounds__(kSymThreads) void sym_direct_kernel(SymArgs a) {
@@ -444,13 +465,13 @@ __global__ __launch_bounds__(kSymThreads) void sym_direct_kernel(SymArgs a) {
     }
     v[0] += d * g;
   });
-  block_partials(v, red, a.part + (size_t)blockIdx.x * kSymPart);
+  block_partials(v, red, a.part, a.nblk);
 }
 
 __global__ void sym_check_kernel(SymArgs a) {
   SymState* S = a.st;
   if (S->phase == PH_DONE) return;
-  const double dgw = S->dir == SD_QN ? wave_sum_strided(a.part, a.nblk, kSymPart) : 0.0;
+  const double dgw = S->dir == SD_QN ? wave_sum(a.part, a.nblk) : 0.0;
   if (threadIdx.x != 0) return;
   if (S->dir == SD_QN) {
     const double dg = dgw;
@@ -571,7 +592,7 @@ hipError_t launch_sym_step(const SymArgs& a, const BatchArgs& b, hipStream_t st)
   hipLaunchKernelGGL(sym_accept_kernel, dim3(a.nblk), dim3(kSymThreads), 0, st, a);
   for (int g = 0; g < sym_groups(a.m); ++g)
     hipLaunchKernelGGL(sym_group_kernel, dim3(a.nblk), dim3(kSymThreads), 0, st, a, g);
-  hipLaunchKernelGGL(sym_solve_kernel, dim3(1), dim3(kSymThreads), 0, st, a);
+  hipLaunchKernelGGL(sym_solve_kernel, dim3(1), dim3(kSolveThreads), 0, st, a);
   hipLaunchKernelGGL(sym_direct_kernel, dim3(a.nblk), dim3(kSymThreads), 0, st, a);
   hipLaunchKernelGGL(sym_check_kernel, dim3(1), dim3(64), 0, st, a);
   hipLaunchKernelGGL(sym_move_kernel, dim3(a.nblk), dim3(kSymThreads), 0, st, a);

@@ -431,6 +431,44 @@ __device__ inline double block_sum_f64(double v, double* red) {
   return t;
 }
 
+// The direction coefficients of the compact form (see k_lbfgs.hip), by one
+// wave, from LDS: n pairs in chronological order, Rm and YYm [n][n] (S^T Y, upper
+// triangle, and Y^T Y), p1 and p2 (S^T g, Y^T g) newest first:
+//   R t = S^T g,   R^T q1 = (D + gamma Y^T Y) t - gamma Y^T g,
+//   cs = -q1, cy = gamma t.
+// Each sum runs over l in ascending order, as one thread would take it: the
+// back substitution on every lane alike (its order leaves nothing to share),
+// the products Y^T Y t and the forward substitution with one lane per row.
+// tv, cs, cy: [n] in LDS.
+__device__ inline void compact_solve(int n, double gamma, const double* Rm, const double* YYm, const double* p1,
+                                     const double* p2, double* tv, double* cs, double* cy) {
+  const int lane = threadIdx.x & 63;
+  for (int i = n - 1; i >= 0; --i) {
+    double x = p1[n - 1 - i];
+#pragma unroll 4
+    for (int l = i + 1; l < n; ++l) x -= Rm[i * n + l] * tv[l];
+    x = x / Rm[i * n + i];
+    if (lane == 0) tv[i] = x;
+    wave_sync();
+  }
+  const int i = lane < n ? lane : 0;
+  const double ti = tv[i], rii = Rm[i * n + i];
+  double yyt = 0.0;
+#pragma unroll 4
+  for (int l = 0; l < n; ++l) yyt += YYm[i * n + l] * tv[l];
+  double x = rii * ti + gamma * (yyt - p2[n - 1 - i]);
+  double q = 0.0;
+  for (int l = 0; l < n; ++l) {
+    const double c = __shfl(x / rii, l, 64);
+    if (lane == l) q = c;
+    if (lane > l) x -= Rm[l * n + i] * c;
+  }
+  if (lane < n) {
+    cs[lane] = -q;
+    cy[lane] = gamma * ti;
+  }
+}
+
 // Host-side launchers -------------------------------------------------------
 // The evaluation and optimiser kernels are persistent / per-site over a batch;
 // nblocks is the grid (resident blocks for the persistent kernels).
