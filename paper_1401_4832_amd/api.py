@@ -108,9 +108,11 @@ def objgrad(msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, sites=None, grad=T
         _dev_tensor(grad_scale, torch.float64, dev, "grad_scale")
         if grad_scale.numel() != N:
             raise ValueError("grad_scale must have N entries")
-    f = torch.zeros(N, dtype=torch.float64, device=dev)
-    gh = torch.zeros(N, q, dtype=torch.float32, device=dev) if grad else None
-    gJ = torch.zeros(N, N, q, q, dtype=torch.float32, device=dev) if grad else None
+    # with every site listed the library writes every entry
+    new = torch.empty if sites is None else torch.zeros
+    f = new(N, dtype=torch.float64, device=dev)
+    gh = new(N, q, dtype=torch.float32, device=dev) if grad else None
+    gJ = new(N, N, q, q, dtype=torch.float32, device=dev) if grad else None
     nbytes = L.lib().plm_objgrad_workspace_bytes(B, N, q, path)
     ws = workspace(nbytes, dev)
     ctx = context(dev)

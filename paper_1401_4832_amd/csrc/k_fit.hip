@@ -33,25 +33,6 @@ __global__ void init_fit_kernel(int32_t N, int32_t q, float* Xh, float* XJ, floa
   }
 }
 
-// Work-item offsets of every alignment from the active-list runs in b.seg
-// (an item covers kind_group consecutive sites of a run), and cleared queue
-// counters (one block; after the runs are written).
-__device__ inline void finish_tables(const BatchArgs& b) {
-  __syncthreads();
-  if (threadIdx.x < 2 * kQueues) b.ctr[threadIdx.x] = 0u;
-  if (threadIdx.x < 2) {
-    const int kind = threadIdx.x;
-    int32_t* off = b.item_off + kind * (b.n_msas + 1);
-    const int32_t grp = kind_group(b, kind);
-    int32_t acc = 0;
-    for (int m = 0; m < b.n_msas; ++m) {
-      off[m] = acc;
-      acc += (b.seg[m + 1] - b.seg[m] + grp - 1) / grp * b.nsub[kind * b.n_msas + m];
-    }
-    off[b.n_msas] = acc;
-  }
-}
-
 // Active list = sites not done, in global order, with the run of each
 // alignment and the work-item tables for the next evaluation; the count also
 // goes to pinned host memory, and the running total of site evaluations (the
@@ -106,25 +87,8 @@ hipError_t launch_reset_queues(const BatchArgs& b, int32_t kind, hipStream_t st)
   return hipGetLastError();
 }
 
-// Tables of a one-alignment batch over an explicit site list (list[j], or
-// first + j when list is null).  Site indices outside [0, N) are replaced by
-// 0 and raise bit 4 of *flag.
-__global__ void list_tables_kernel(BatchArgs b, const int32_t* list, int32_t first, int32_t n,
-                                   int32_t* flag) {
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    int32_t v = list ? list[j] : first + j;
-    if (v < 0 || v >= b.total_sites) {
-      if (flag) atomicOr(flag, 4);
-      v = 0;
-    }
-    b.active[j] = v;
-  }
-  if (threadIdx.x == 0) {
-    *b.n_active = n;
-    b.seg[0] = 0;
-    b.seg[1] = n;
-  }
-  finish_tables(b);
+__global__ void list_tables_kernel(BatchArgs b, const int32_t* list, int32_t first, int32_t n, int32_t* flag) {
+  list_tables(b, list, first, n, flag);
 }
 
 // Objective and gradient of one listed site (blockIdx.x): the l2 terms added
@@ -239,39 +203,6 @@ hipError_t launch_check_f64(const double* p, size_t n, int32_t* flag, hipStream_
   size_t blocks = (n + 255) / 256;
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL(nonfinite_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, st, p, n, flag);
-  return hipGetLastError();
-}
-
-// One block: raises bit 2 of *flag for a non-finite weight, and writes the
-// smallest exponent e with every |w_b| <= 2^e (0 for all-zero weights).
-__global__ __launch_bounds__(1024) void weight_exponent_kernel(const double* __restrict__ w, int32_t B, int32_t* wexp,
-                                                               int32_t* flag) {
-  __shared__ double red[16];
-  double mx = 0.0;
-  bool bad = false;
-#pragma unroll 8
-  for (int b = threadIdx.x; b < B; b += 1024) {
-    const double v = fabs(w[b]);
-    bad |= !isfinite(v);
-    mx = fmax(mx, v);
-  }
-  if (bad && flag) atomicOr(flag, 2);
-  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < 16; ++k) mx = fmax(mx, red[k]);
-    int e = 0;
-    if (mx > 0.0 && isfinite(mx)) {
-      const double m = frexp(mx, &e);  // m in [0.5, 1)
-      if (m == 0.5) --e;
-    }
-    *wexp = e;
-  }
-}
-
-hipError_t launch_weight_exponent(const double* w, int32_t B, int32_t* wexp, int32_t* flag, hipStream_t st) {
-  hipLaunchKernelGGL(weight_exponent_kernel, dim3(1), dim3(1024), 0, st, w, B, wexp, flag);
   return hipGetLastError();
 }
 

@@ -150,30 +150,6 @@ __global__ __launch_bounds__(256) void jquant_kernel(BatchArgs b) {
   }
 }
 
-// ---- symbols of position triples ---------------------------------------------
-__global__ void sym3_kernel(const uint8_t* __restrict__ msa_cm, int32_t B_pad, int32_t N, int32_t NG,
-                            uint32_t* __restrict__ sym3) {
-  const size_t total = (size_t)NG * B_pad;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-    const int G = (int)(e / B_pad), b = (int)(e - (size_t)G * B_pad);
-    uint32_t v = 0;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      const int i = 3 * G + p;
-      if (i < N) v |= (uint32_t)msa_cm[((size_t)(i >> 4) * B_pad + b) * 16 + (i & 15)] << (8 * p);
-    }
-    sym3[e] = v;
-  }
-}
-
-hipError_t launch_sym3(const uint8_t* msa_cm, int32_t B_pad, int32_t N, int32_t NG, uint32_t* sym3, hipStream_t st) {
-  const size_t total = (size_t)NG * B_pad;
-  int blocks = (int)((total + 255) / 256);
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(sym3_kernel, dim3(blocks), dim3(256), 0, st, msa_cm, B_pad, N, NG, sym3);
-  return hipGetLastError();
-}
-
 // 16 bytes, byte j = bit j of bits (one multiply per 4 bits)
 __device__ inline uint4 spread16(uint32_t bits) {
   uint32_t w[4];

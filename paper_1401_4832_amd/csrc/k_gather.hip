@@ -18,39 +18,6 @@
 
 namespace plm {
 
-// Padded copy of the alignment in chunk-major order: symbol (b, i) at byte
-// ((i / 16) * B_pad + b) * 16 + i % 16, so that the sixteen columns of a chunk
-// for a run of rows are one contiguous block.  Symbols >= q raise the flag.
-__global__ void pad_msa_kernel(const uint8_t* __restrict__ msa, int32_t B, int32_t N, int32_t q,
-                               uint8_t* __restrict__ out, int32_t B_pad, int32_t N_pad,
-                               int32_t* flag) {
-  const size_t total = (size_t)B_pad * N_pad;
-  const size_t per_chunk = (size_t)B_pad * kFwdChunk;
-  int bad = 0;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total;
-       e += (size_t)gridDim.x * blockDim.x) {
-    const size_t c = e / per_chunk, rem = e - c * per_chunk;
-    const int32_t b = (int32_t)(rem / kFwdChunk), i = (int32_t)(c * kFwdChunk + rem % kFwdChunk);
-    uint8_t v = 0;
-    if (b < B && i < N) {
-      v = msa[(size_t)b * N + i];
-      if (v >= q) { bad = 1; v = 0; }
-    }
-    out[e] = v;
-  }
-  if (bad && flag) atomicOr(flag, 1);
-}
-
-hipError_t launch_pad_msa(const uint8_t* msa, int32_t B, int32_t N, int32_t q, uint8_t* msa_cm,
-                          int32_t B_pad, int32_t N_pad, int32_t* flag_dev, hipStream_t st) {
-  const size_t total = (size_t)B_pad * N_pad;
-  int blocks = (int)((total + 255) / 256);
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(pad_msa_kernel, dim3(blocks), dim3(256), 0, st, msa, B, N, q, msa_cm, B_pad,
-                     N_pad, flag_dev);
-  return hipGetLastError();
-}
-
 int32_t forward_tile_seqs(int32_t nb) { return kFwdWaves * kSlots * nb; }
 
 // J chunk of the gather forward: kFwdPos columns of kQMax rows of 64 floats;

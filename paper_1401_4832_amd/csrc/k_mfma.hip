@@ -79,37 +79,6 @@ __device__ inline uint4 onehot8_x2(uint2 s8, uint32_t kk) {
 
 constexpr double kOneHotUnscale = 0.5;  // the one-hot value is 2
 
-// Position-major copy of the padded alignment: msaT[i * B_pad + b].
-__global__ void transpose_msa_kernel(const uint8_t* __restrict__ msa_cm, int32_t B_pad,
-                                     int32_t N_pad, uint8_t* __restrict__ msaT) {
-  const size_t groups = (size_t)B_pad / 16;
-  const size_t total = (size_t)N_pad * groups;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total;
-       e += (size_t)gridDim.x * blockDim.x) {
-    const int32_t i = (int32_t)(e / groups);
-    const size_t b0 = (e - (size_t)i * groups) * 16;
-    const uint8_t* src = msa_cm + ((size_t)(i / kFwdChunk) * B_pad + b0) * kFwdChunk + i % kFwdChunk;
-    uint32_t w[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      w[t] = (uint32_t)src[(4 * t) * kFwdChunk] | ((uint32_t)src[(4 * t + 1) * kFwdChunk] << 8) |
-             ((uint32_t)src[(4 * t + 2) * kFwdChunk] << 16) |
-             ((uint32_t)src[(4 * t + 3) * kFwdChunk] << 24);
-    }
-    *reinterpret_cast<uint4*>(msaT + (size_t)i * B_pad + b0) = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-}
-
-hipError_t launch_transpose_msa(const uint8_t* msa_cm, int32_t B_pad, int32_t N_pad, uint8_t* msaT,
-                                hipStream_t st) {
-  const size_t total = (size_t)N_pad * (B_pad / 16);
-  int blocks = (int)((total + 255) / 256);
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(transpose_msa_kernel, dim3(blocks), dim3(256), 0, st, msa_cm, B_pad, N_pad,
-                     msaT);
-  return hipGetLastError();
-}
-
 // One backward work item: site r x column block cb.  Bf: B fragments of the
 // residual pieces, [buffer][piece][step][half][column][8 sequences]; sig:
 // symbols of the block's columns, [buffer][column][sequence].
@@ -704,28 +673,6 @@ __global__ __launch_bounds__(kGThreads) void bwd_g3_kernel(BatchArgs b) {
     g3_item(b, a, it, Rf0, Rf1, sig0, sig1);
     __syncthreads();
   }
-}
-
-__global__ void rfrag_tail_zero_kernel(uint4* R, int32_t N, int32_t nch_site, int32_t c0, int32_t c1,
-                                       int32_t chunk16) {
-  const int64_t per = (int64_t)(c1 - c0) * chunk16;
-  const int64_t total = per * N;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = e / per, k = e - r * per;
-    R[(r * nch_site + c0) * chunk16 + k] = make_uint4(0, 0, 0, 0);
-  }
-}
-
-hipError_t launch_rfrag_tail_zero(float* R, int32_t N, int32_t B, int32_t B3, int32_t B_pad, int32_t chunk_bytes,
-                                  hipStream_t st) {
-  const int32_t c0 = B >> 8, c1 = (B3 + 255) >> 8;
-  if (c0 >= c1) return hipSuccess;
-  const int32_t chunk16 = chunk_bytes / 16;
-  const int64_t total = (int64_t)(c1 - c0) * chunk16 * N;
-  const int blocks = (int)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
-  hipLaunchKernelGGL(rfrag_tail_zero_kernel, dim3(blocks), dim3(256), 0, st, reinterpret_cast<uint4*>(R), N,
-                     B_pad >> 8, c0, c1, chunk16);
-  return hipGetLastError();
 }
 
 int32_t g3_backward_blocks_per_site(int32_t N, int32_t q) {

@@ -337,28 +337,28 @@ int32_t eval_bwd_blocks(const PathSpec& p, int32_t N, int32_t q) {
   return mfma_backward_blocks_per_site(N, q);
 }
 
-// Once per alignment, before the first forward: the int8 forward's packed
-// symbols, and (backward = true) the gradient path's symbol copy and, for the
-// grouped gradient, the residual rows no forward tile writes.
-hipError_t eval_prepare(const PathSpec& p, const EvalArgs& a, uint8_t* msaT, hipStream_t st, bool backward = true) {
-  if (!backward)
-    return p.fwd_i8 ? launch_sym3(a.msa_cm, a.B_pad, a.N, a.NG, const_cast<uint32_t*>(a.sym3), st)
-                    : hipSuccess;
-  if (p.bwd_g3 || p.bwd_i8) {
-    hipError_t e =
-        launch_rfrag_tail_zero(a.R, a.N, a.B, a.B3, a.B_pad,
-                               p.bwd_i8 == 4 ? kR4ChunkBytes : p.bwd_i8 ? kRiChunkBytes : kRfChunkBytes, st);
-    if (e == hipSuccess && p.f64)  // the remainder digits
-      e = launch_rfrag_tail_zero(reinterpret_cast<float*>(reinterpret_cast<char*>(a.R) +
-                                                          (size_t)a.N * (a.B_pad >> 8) * kRiChunkBytes),
-                                 a.N, a.B, a.B3, a.B_pad, kRiChunkBytes, st);
-    if (e != hipSuccess) return e;
-  }
-  if (p.fwd_i8) {
-    const hipError_t e = launch_sym3(a.msa_cm, a.B_pad, a.N, a.NG, const_cast<uint32_t*>(a.sym3), st);
-    if (e != hipSuccess) return e;
-  }
-  return launch_transpose_msa(a.msa_cm, a.B_pad, a.N_pad, msaT, st);
+// Once per alignment, before the first forward: the internal copies of the
+// alignment the path reads (backward = false: the forward's only), the zeroed
+// residual rows of a grouped gradient, the check of the weights.
+PrepArgs prep_args(const PathSpec& p, const EvalBufs& e, const uint8_t* msa, const double* w, int32_t B, int32_t N,
+                   int32_t q, int32_t* flag, bool backward = true) {
+  PrepArgs a;
+  a.msa = msa; a.B = B; a.N = N; a.q = q; a.B_pad = e.B_pad; a.N_pad = e.N_pad; a.NG = e.NG;
+  a.msa_cm = e.msa_cm;
+  a.msaT = backward ? e.msaT : nullptr;
+  a.sym3 = p.fwd_i8 ? e.sym3 : nullptr;
+  a.w = w;
+  a.wexp = p.bwd_i8 == 4 ? e.jexp : nullptr;  // (path 0 has no coupling digits)
+  const bool grouped = p.bwd_g3 || p.bwd_i8;
+  const int32_t chunk = p.bwd_i8 == 4 ? kR4ChunkBytes : p.bwd_i8 ? kRiChunkBytes : kRfChunkBytes;
+  a.zero0 = backward && grouped ? reinterpret_cast<uint4*>(e.R) : nullptr;
+  a.chunk16 = chunk / 16;
+  a.zc0 = B >> 8;
+  a.zc1 = (e.B3 + 255) >> 8;
+  // the remainder digits of the precise path
+  a.zero1 = a.zero0 && p.f64 ? a.zero0 + (size_t)N * (e.B_pad >> 8) * a.chunk16 : nullptr;
+  a.flag = flag;
+  return a;
 }
 
 // persistent grids: resident blocks of each kernel on the whole device
@@ -426,12 +426,6 @@ EvalArgs eval_args(const EvalBufs& e, const uint8_t* msa_unused, int32_t B, int3
   a.h_lo = nullptr;
   a.J_lo = nullptr;
   return a;
-}
-
-// finite check of the weights, and for path 0 the scale of its residual digits
-hipError_t check_weights(const PathSpec& p, const double* w, int32_t B, const EvalBufs& e, int32_t* flag,
-                         hipStream_t st) {
-  return p.bwd_i8 == 4 ? launch_weight_exponent(w, B, e.jexp, flag, st) : launch_check_f64(w, (size_t)B, flag, st);
 }
 
 int flags_status(plm_ctx* c) {
@@ -577,21 +571,19 @@ int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
   Tables t;
   layout_tables(bp, 1, N, false, t);
   const BatchArgs b = batch_args(t, 1, N, bwd_group(ps), fwd_group(ps));
-  HIPCHK(c, check_weights(ps, w, B, e, c->pin_dev, c->stream));
   // with every site listed the last kernel, which reads h and J anyway, checks them
   if (sites) {
     HIPCHK(c, launch_check_f32(h, (size_t)N * q, c->pin_dev, c->stream));
     HIPCHK(c, launch_check_f32(J, (size_t)N * N * q * q, c->pin_dev, c->stream));
     if (grad_scale) HIPCHK(c, launch_check_f64(grad_scale, (size_t)N, c->pin_dev, c->stream));
   }
-  HIPCHK(c, launch_pad_msa(msa, B, N, q, e.msa_cm, e.B_pad, e.N_pad, c->pin_dev, c->stream));
   const int32_t nb = pick_nb(N, B, c->ncu, 0);
   const EvalArgs a = eval_args(e, msa, B, N, q, w, h, J, eval_tiles(ps, B, nb), ps);
-  HIPCHK(c, launch_setup_msa(b, 0, a, nullptr, 0, N, a.tiles, eval_bwd_blocks(ps, N, q), nullptr,
-                             c->stream));
-  HIPCHK(c, launch_list_tables(b, sites, 0, n_sites, c->pin_dev, c->stream));
+  TableArgs ta;
+  ta.b = b; ta.e = a; ta.sites = sites; ta.n_sites = n_sites;
+  ta.nsub_f = a.tiles; ta.nsub_b = eval_bwd_blocks(ps, N, q);
+  HIPCHK(c, launch_prepare(prep_args(ps, e, msa, w, B, N, q, c->pin_dev, gJ_out != nullptr), &ta, c->stream));
   const Grids g = eval_grids(c, ps, nb);
-  HIPCHK(c, eval_prepare(ps, a, e.msaT, c->stream, gJ_out != nullptr));
   HIPCHK(c, eval_forward(ps, b, nb, g, c->stream));
   if (gJ_out) HIPCHK(c, eval_backward(ps, b, g, c->stream));
   FinalArgs fa;
@@ -772,13 +764,11 @@ int prepare_fit(plm_ctx* c, const plm_msa_desc* d, int32_t n, int32_t q, const p
     const plm_msa_desc& m = d[ord[k]];
     const FitBufs& f = fb[k];
     base[k + 1] = base[k] + m.N;
-    HIPCHK(c, check_weights(ps, m.w, m.B, f.ev, c->pin_dev, st));
     HIPCHK(c, launch_check_f32(m.h_io, (size_t)m.N * q, c->pin_dev, st));
-    HIPCHK(c, launch_pad_msa(m.msa, m.B, m.N, q, f.ev.msa_cm, f.ev.B_pad, f.ev.N_pad, c->pin_dev, st));
+    HIPCHK(c, launch_prepare(prep_args(ps, f.ev, m.msa, m.w, m.B, m.N, q, c->pin_dev), nullptr, st));
     HIPCHK(c, launch_init_fit(m.N, q, m.h_io, m.J_io, f.Th, f.TJ, t.st + base[k], phase_host_dev + base[k], st));
     HIPCHK(c, launch_check_f32(m.J_io, (size_t)m.N * m.N * q * q, c->pin_dev, st));
     const EvalArgs a = eval_args(f.ev, m.msa, m.B, m.N, q, m.w, f.Th, f.TJ, eval_tiles(ps, m.B, nb), ps);
-    HIPCHK(c, eval_prepare(ps, a, f.ev.msaT, st));
     LbfgsArgs L;
     L.N = m.N; L.q = q; L.m = o->lbfgs_m; L.max_iter = o->max_iter; L.max_ls = o->max_linesearch;
     L.tiles = a.tiles; L.tol = o->tol; L.lambda_h = o->lambda_h; L.lambda_Jp = 0.5 * o->lambda_J;
@@ -1245,20 +1235,18 @@ int run_sym_once(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
 
   const int32_t nb = pick_nb(N, B, c->ncu, o->tile_seqs);
   const BatchArgs b = batch_args(f.t, 1, N, bwd_group(ps), fwd_group(ps));
-  HIPCHK(c, check_weights(ps, w, B, f.ev, c->pin_dev, st));
   HIPCHK(c, launch_check_f32(h_io, (size_t)N * q, c->pin_dev, st));
   HIPCHK(c, launch_check_f32(J_io, (size_t)N * N * q * q, c->pin_dev, st));
   if (lo) {
     HIPCHK(c, launch_check_f32(h_lo_io, (size_t)N * q, c->pin_dev, st));
     HIPCHK(c, launch_check_f32(J_lo_io, (size_t)N * N * q * q, c->pin_dev, st));
   }
-  HIPCHK(c, launch_pad_msa(msa, B, N, q, f.ev.msa_cm, f.ev.B_pad, f.ev.N_pad, c->pin_dev, st));
+  HIPCHK(c, launch_prepare(prep_args(ps, f.ev, msa, w, B, N, q, c->pin_dev), nullptr, st));
   EvalArgs a = eval_args(f.ev, msa, B, N, q, w, f.Th, f.TJ, eval_tiles(ps, B, nb), ps);
   if (ps.f64 == 2) {
     a.h_lo = f.Thl;
     a.J_lo = f.TJl;
   }
-  HIPCHK(c, eval_prepare(ps, a, f.ev.msaT, st));
   HIPCHK(c, launch_setup_msa(b, 0, a, nullptr, 0, N, a.tiles, eval_bwd_blocks(ps, N, q), nullptr, st));
   HIPCHK(c, launch_list_tables(b, nullptr, 0, N, nullptr, st));
 

@@ -410,6 +410,29 @@ struct ScoreOpts {
   int32_t exclude_gap, correction;
 };
 
+// What the evaluation of one alignment needs before its first forward (k_prep.hip).
+struct PrepArgs {
+  const uint8_t* msa;   // uint8[B][N], the caller's
+  int32_t B, N, q, B_pad, N_pad, NG;
+  uint8_t* msa_cm;
+  uint8_t* msaT;        // null: not needed
+  uint32_t* sym3;       // null: not needed
+  const double* w;      // [B], checked
+  int32_t* wexp;        // null: not needed
+  uint4* zero0;         // residual buffer of a grouped gradient whose tail chunks [zc0, zc1) are zeroed, or null
+  uint4* zero1;         // a second digit set, or null
+  int32_t chunk16, zc0, zc1;  // 16-byte words per chunk and site
+  int32_t* flag;
+};
+
+// The work tables of a standalone evaluation of one alignment.
+struct TableArgs {
+  BatchArgs b;
+  EvalArgs e;
+  const int32_t* sites;  // device list, or null: all N
+  int32_t n_sites, nsub_f, nsub_b;
+};
+
 // Device helpers ----------------------------------------------------------
 // orders a wave's LDS accesses (they execute in program order; this keeps the compiler's order)
 __device__ inline void wave_sync() {
@@ -469,15 +492,67 @@ __device__ inline void compact_solve(int n, double gamma, const double* Rm, cons
   }
 }
 
+// Work-item offsets of every alignment from the active-list runs in b.seg
+// (an item covers kind_group consecutive sites of a run), and cleared queue
+// counters (one block; after the runs are written).
+__device__ inline void finish_tables(const BatchArgs& b) {
+  __syncthreads();
+  if (threadIdx.x < 2 * kQueues) b.ctr[threadIdx.x] = 0u;
+  if (threadIdx.x < 2) {
+    const int kind = threadIdx.x;
+    int32_t* off = b.item_off + kind * (b.n_msas + 1);
+    const int32_t grp = kind_group(b, kind);
+    int32_t acc = 0;
+    for (int m = 0; m < b.n_msas; ++m) {
+      off[m] = acc;
+      acc += (b.seg[m + 1] - b.seg[m] + grp - 1) / grp * b.nsub[kind * b.n_msas + m];
+    }
+    off[b.n_msas] = acc;
+  }
+}
+
+// The active list of a one-alignment batch from an explicit site list (list[j],
+// or first + j when list is null) and its work items.  Site indices outside
+// [0, N) are replaced by 0 and raise bit 4 of *flag.
+__device__ inline void list_tables(const BatchArgs& b, const int32_t* list, int32_t first, int32_t n, int32_t* flag) {
+  for (int j = threadIdx.x; j < n; j += blockDim.x) {
+    int32_t v = list ? list[j] : first + j;
+    if (v < 0 || v >= b.total_sites) {
+      if (flag) atomicOr(flag, 4);
+      v = 0;
+    }
+    b.active[j] = v;
+  }
+  if (threadIdx.x == 0) {
+    *b.n_active = n;
+    b.seg[0] = 0;
+    b.seg[1] = n;
+  }
+  finish_tables(b);
+}
+
+// Every table of a standalone evaluation (one block): the descriptor, the
+// site map and the active list.
+__device__ inline void write_eval_tables(const TableArgs& t, int32_t* flag) {
+  const BatchArgs& b = t.b;
+  for (int j = threadIdx.x; j < b.total_sites; j += blockDim.x) const_cast<int32_t*>(b.msa_of)[j] = 0;
+  if (threadIdx.x == 0) {
+    const_cast<EvalArgs*>(b.ev)[0] = t.e;
+    int32_t* sb = const_cast<int32_t*>(b.site_base);
+    sb[0] = 0;
+    sb[1] = b.total_sites;
+    int32_t* ns = const_cast<int32_t*>(b.nsub);
+    ns[KIND_FWD] = t.nsub_f;
+    ns[KIND_BWD] = t.nsub_b;
+  }
+  list_tables(b, t.sites, 0, t.n_sites, flag);
+}
+
 // Host-side launchers -------------------------------------------------------
 // The evaluation and optimiser kernels are persistent / per-site over a batch;
 // nblocks is the grid (resident blocks for the persistent kernels).
-hipError_t launch_pad_msa(const uint8_t* msa, int32_t B, int32_t N, int32_t q, uint8_t* msa_cm,
-                          int32_t B_pad, int32_t N_pad, int32_t* flag_dev, hipStream_t st);
-hipError_t launch_transpose_msa(const uint8_t* msa_cm, int32_t B_pad, int32_t N_pad, uint8_t* msaT,
-                                hipStream_t st);
-// finite check of the weights (bit 2 of *flag) and the exponent of the largest
-hipError_t launch_weight_exponent(const double* w, int32_t B, int32_t* wexp, int32_t* flag, hipStream_t st);
+// everything before the first forward; t (or null): the tables of a standalone evaluation too
+hipError_t launch_prepare(const PrepArgs& a, const TableArgs* t, hipStream_t st);
 int32_t forward_tile_seqs(int32_t nb);
 // f64: 0 FP32 accumulation, 1 FP64 (the precise path), 2 FP64 reading the
 // low-order words of the point as well (EvalArgs.h_lo, J_lo)
@@ -494,17 +569,11 @@ constexpr int kG3Sites = 3;
 int32_t g3_backward_blocks_per_site(int32_t N, int32_t q);
 int32_t g3_resident_blocks();
 hipError_t launch_backward_g3(const BatchArgs& b, int32_t nblocks, hipStream_t st);
-// zero the fragment-order residual rows [B rounded down to 256, B3 rounded up
-// to 256) of every site: the forward writes only the rows of its tiles, and the
-// last gradient chunk may reach past them
-hipError_t launch_rfrag_tail_zero(float* R, int32_t N, int32_t B, int32_t B3, int32_t B_pad, int32_t chunk_bytes,
-                                  hipStream_t st);
 // int8 fixed-point MFMA forward (three sites per item; path 6)
 constexpr int kWqGroupBytes = 3 * 2 * 2 * kSlot * 16;      // 4032 per (site, position triple)
 constexpr int kJParts = 16;                                 // blocks per site of the coupling quantisation
 int32_t fwd_i8_tile_seqs();
 int32_t fwd_i8_resident_blocks();
-hipError_t launch_sym3(const uint8_t* msa_cm, int32_t B_pad, int32_t N, int32_t NG, uint32_t* sym3, hipStream_t st);
 // couplings of every active site to digits (jmax_kernel, jquant_kernel), then the int8 forward
 hipError_t launch_jquant(const BatchArgs& b, int32_t total_sites, hipStream_t st);
 hipError_t launch_fwd_i8(const BatchArgs& b, int32_t nblocks, hipStream_t st);
