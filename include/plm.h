@@ -149,6 +149,22 @@ int plm_objgrad(plm_ctx *ctx, const uint8_t *msa, int32_t B, int32_t N, int32_t 
                 int32_t path, void *workspace, size_t workspace_bytes,
                 const double *grad_scale, double *f_out, float *gh_out, float *gJ_out);
 
+/* The two halves of plm_objgrad over all sites, for callers that learn only
+ * after the objective whether and with which multipliers they need the gradient
+ * (automatic differentiation).  plm_objgrad_begin writes f_out and leaves the
+ * residuals in the workspace; plm_objgrad_finish, given the same sizes, inputs,
+ * path and the same workspace contents (possibly copied to another address),
+ * writes the gradient without evaluating the energies again.  It may be called
+ * more than once.  Results equal those of plm_objgrad bit for bit. */
+int plm_objgrad_begin(plm_ctx *ctx, const uint8_t *msa, int32_t B, int32_t N, int32_t q,
+                      const double *w, const double *beff, const float *h, const float *J,
+                      double lambda_h, double lambda_J, int32_t path, void *workspace,
+                      size_t workspace_bytes, double *f_out);
+int plm_objgrad_finish(plm_ctx *ctx, int32_t B, int32_t N, int32_t q, const double *w,
+                       const double *beff, const float *h, const float *J, double lambda_h,
+                       double lambda_J, int32_t path, void *workspace, size_t workspace_bytes,
+                       const double *grad_scale, float *gh_out, float *gJ_out);
+
 /* ---- Objective and gradient without a workspace ----------------------------
  * For callers that cannot allocate device memory: code under HIP graph
  * capture, serving loops, harnesses that forbid allocation.  plm_objgrad

@@ -153,6 +153,8 @@ def lib():
             "plm_objgrad_workspace_bytes": (SZ, [I32, I32, I32, I32]),
             "plm_objgrad": (ctypes.c_int, [P, P, I32, I32, I32, P, P, P, P, D, D, P, I32, I32, P, SZ,
                                            P, P, P, P]),
+            "plm_objgrad_begin": (ctypes.c_int, [P, P, I32, I32, I32, P, P, P, P, D, D, I32, P, SZ, P]),
+            "plm_objgrad_finish": (ctypes.c_int, [P, I32, I32, I32, P, P, P, P, D, D, I32, P, SZ, P, P, P]),
             "plm_objgrad_static": (ctypes.c_int, [P, P, I32, I32, I32, P, P, P, P, D, D, P, I32, I32, P, P, P, P]),
             "plm_fit_opts_default": (None, [ctypes.POINTER(FitOpts)]),
             "plm_fit_opts_size": (SZ, []),
@@ -192,7 +194,7 @@ def exported_symbols():
     """Names declared in include/plm.h that the ABI tests check for."""
     return ["plm_ctx_create", "plm_ctx_destroy", "plm_last_error", "plm_status_string", "plm_sync",
             "plm_reweight", "plm_objgrad_workspace_bytes", "plm_objgrad", "plm_fit_opts_default",
-            "plm_fit_opts_size", "plm_objgrad_static",
+            "plm_fit_opts_size", "plm_objgrad_static", "plm_objgrad_begin", "plm_objgrad_finish",
             "plm_fit_workspace_bytes", "plm_fit", "plm_score", "plm_fit_last_timing",
             "plm_fit_batch_workspace_bytes", "plm_fit_batch", "plm_tune", "plm_score_opts_default",
             "plm_frequencies", "plm_score_ex", "plm_contact_tpr", "plm_parse_alignment",

@@ -122,6 +122,50 @@ def objgrad(msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, sites=None, grad=T
     return f, gh, gJ
 
 
+def _objgrad_inputs(msa, w, beff, h, J):
+    dev = msa.device
+    _dev_tensor(msa, torch.uint8, dev, "msa")
+    B, N = msa.shape
+    q = h.shape[1]
+    _dev_tensor(w, torch.float64, dev, "w")
+    _dev_tensor(beff, torch.float64, dev, "beff")
+    _dev_tensor(h, torch.float32, dev, "h")
+    _dev_tensor(J, torch.float32, dev, "J")
+    if tuple(J.shape) != (N, N, q, q) or tuple(h.shape) != (N, q) or w.numel() != B:
+        raise ValueError("shape mismatch between msa, w, h and J")
+    return dev, B, N, q
+
+
+def objgrad_begin(msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_GATHER_FP32):
+    """(f, workspace): the objectives of all sites, and the workspace that holds
+    their residuals for objgrad_finish()."""
+    dev, B, N, q = _objgrad_inputs(msa, w, beff, h, J)
+    f = torch.empty(N, dtype=torch.float64, device=dev)
+    ws = workspace(L.lib().plm_objgrad_workspace_bytes(B, N, q, path), dev)
+    ctx = context(dev)
+    _check(L.lib().plm_objgrad_begin(ctx, _ptr(msa), B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J),
+                                     float(lambda_h), float(lambda_J), path, _ptr(ws), ws.numel(), _ptr(f)), ctx)
+    return f, ws
+
+
+def objgrad_finish(ws, msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_GATHER_FP32, grad_scale=None):
+    """(gh, gJ) of the evaluation that objgrad_begin(), with the same arguments,
+    left in ws (or in a copy of it)."""
+    dev, B, N, q = _objgrad_inputs(msa, w, beff, h, J)
+    _dev_tensor(ws, torch.uint8, dev, "ws")
+    if grad_scale is not None:
+        _dev_tensor(grad_scale, torch.float64, dev, "grad_scale")
+        if grad_scale.numel() != N:
+            raise ValueError("grad_scale must have N entries")
+    gh = torch.empty(N, q, dtype=torch.float32, device=dev)
+    gJ = torch.empty(N, N, q, q, dtype=torch.float32, device=dev)
+    ctx = context(dev)
+    _check(L.lib().plm_objgrad_finish(ctx, B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J), float(lambda_h),
+                                      float(lambda_J), path, _ptr(ws), ws.numel(), _ptr(grad_scale), _ptr(gh),
+                                      _ptr(gJ)), ctx)
+    return gh, gJ
+
+
 def objgrad_static(msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, sites=None, grad=True,
                    path=L.PATH_GATHER_FP32, grad_scale=None, out=None):
     """objgrad() through plm_objgrad_static: no workspace, the library's fixed

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(kFinThreads) void objgrad_final_kernel(FinalArgs a,
       }
     }
     reg = block_sum_f64(reg, red);
-    if (tid == 0) a.f_out[r] = fd_s + beff * reg;
+    if (tid == 0 && a.f_out) a.f_out[r] = fd_s + beff * reg;
   }
   bad |= !isfinite(sc);
   if (check && bad) atomicOr(check, 2);

@@ -151,7 +151,7 @@ hipError_t launch_prepare(const PrepArgs& a, const TableArgs* t, hipStream_t st)
   const int col_tiles = (a.N_pad + kPrCols - 1) / kPrCols;
   const int64_t tiles = (int64_t)(a.B_pad / kPrRows) * col_tiles;
   const int nzero = a.zero0 && a.zc0 < a.zc1 ? kPrZeroBlocks : 0;
-  const int64_t grid = tiles + nzero + 1 + (t ? 1 : 0);
+  const int64_t grid = a.tables_only ? 1 : tiles + nzero + 1 + (t ? 1 : 0);
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL(prep_kernel, dim3((unsigned)grid), dim3(kPrThreads), 0, st, a, t ? *t : TableArgs{}, t ? 1 : 0,
                      nzero, col_tiles);

@@ -358,6 +358,7 @@ PrepArgs prep_args(const PathSpec& p, const EvalBufs& e, const uint8_t* msa, con
   // the remainder digits of the precise path
   a.zero1 = a.zero0 && p.f64 ? a.zero0 + (size_t)N * (e.B_pad >> 8) * a.chunk16 : nullptr;
   a.flag = flag;
+  a.tables_only = 0;
   return a;
 }
 
@@ -545,13 +546,17 @@ size_t plm_objgrad_workspace_bytes(int32_t B, int32_t N, int32_t q, int32_t path
 
 namespace {
 
-// plm_objgrad on the given scratch (a caller's workspace or the static array)
+// plm_objgrad on the given scratch (a caller's workspace or the static array),
+// whole, or its two halves: EV_BEGIN leaves in the scratch everything the
+// gradient needs, EV_FINISH takes it up there.
+enum { EV_WHOLE = 0, EV_BEGIN = 1, EV_FINISH = 2 };
 int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q, const double* w,
                  const double* beff, const float* h, const float* J, double lambda_h,
                  double lambda_J, const int32_t* sites, int32_t n_sites, int32_t path, void* ws,
                  size_t ws_bytes, const double* grad_scale, double* f_out, float* gh_out,
-                 float* gJ_out) {
-  if (!msa || !w || !beff || !h || !J || !f_out) return set_err(c, PLM_E_INVALID, "null pointer");
+                 float* gJ_out, int stage = EV_WHOLE) {
+  if (!w || !beff || !h || !J) return set_err(c, PLM_E_INVALID, "null pointer");
+  if (stage == EV_FINISH ? !gh_out || !gJ_out : !msa || !f_out) return set_err(c, PLM_E_INVALID, "null pointer");
   int rc = check_sizes(c, B, N, q);
   if (rc) return rc;
   if (!(lambda_h >= 0.0) || !(lambda_J >= 0.0)) return set_err(c, PLM_E_INVALID, "negative lambda");
@@ -582,9 +587,12 @@ int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
   TableArgs ta;
   ta.b = b; ta.e = a; ta.sites = sites; ta.n_sites = n_sites;
   ta.nsub_f = a.tiles; ta.nsub_b = eval_bwd_blocks(ps, N, q);
-  HIPCHK(c, launch_prepare(prep_args(ps, e, msa, w, B, N, q, c->pin_dev, gJ_out != nullptr), &ta, c->stream));
+  // (the tables hold addresses in the scratch, which may have moved since EV_BEGIN: written again)
+  PrepArgs pa = prep_args(ps, e, msa, w, B, N, q, c->pin_dev, gJ_out != nullptr || stage == EV_BEGIN);
+  pa.tables_only = stage == EV_FINISH;
+  HIPCHK(c, launch_prepare(pa, &ta, c->stream));
   const Grids g = eval_grids(c, ps, nb);
-  HIPCHK(c, eval_forward(ps, b, nb, g, c->stream));
+  if (stage != EV_FINISH) HIPCHK(c, eval_forward(ps, b, nb, g, c->stream));
   if (gJ_out) HIPCHK(c, eval_backward(ps, b, g, c->stream));
   FinalArgs fa;
   fa.N = N; fa.q = q; fa.tiles = a.tiles; fa.lambda_h = lambda_h; fa.lambda_Jp = 0.5 * lambda_J;
@@ -607,6 +615,22 @@ int plm_objgrad(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q,
   if (!c) return PLM_E_INVALID;
   return objgrad_impl(c, msa, B, N, q, w, beff, h, J, lambda_h, lambda_J, sites, n_sites, path, ws,
                       ws_bytes, grad_scale, f_out, gh_out, gJ_out);
+}
+
+int plm_objgrad_begin(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q, const double* w,
+                      const double* beff, const float* h, const float* J, double lambda_h, double lambda_J,
+                      int32_t path, void* ws, size_t ws_bytes, double* f_out) {
+  if (!c) return PLM_E_INVALID;
+  return objgrad_impl(c, msa, B, N, q, w, beff, h, J, lambda_h, lambda_J, nullptr, N, path, ws, ws_bytes, nullptr,
+                      f_out, nullptr, nullptr, EV_BEGIN);
+}
+
+int plm_objgrad_finish(plm_ctx* c, int32_t B, int32_t N, int32_t q, const double* w, const double* beff,
+                       const float* h, const float* J, double lambda_h, double lambda_J, int32_t path, void* ws,
+                       size_t ws_bytes, const double* grad_scale, float* gh_out, float* gJ_out) {
+  if (!c) return PLM_E_INVALID;
+  return objgrad_impl(c, nullptr, B, N, q, w, beff, h, J, lambda_h, lambda_J, nullptr, N, path, ws, ws_bytes,
+                      grad_scale, nullptr, gh_out, gJ_out, EV_FINISH);
 }
 
 int plm_objgrad_static(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q,

@@ -422,6 +422,7 @@ struct PrepArgs {
   uint4* zero0;         // residual buffer of a grouped gradient whose tail chunks [zc0, zc1) are zeroed, or null
   uint4* zero1;         // a second digit set, or null
   int32_t chunk16, zc0, zc1;  // 16-byte words per chunk and site
+  int32_t tables_only;  // the rest is in place (the second half of an evaluation)
   int32_t* flag;
 };
 

@@ -128,3 +128,52 @@ def test_mean_field_block_sweep(plm, N, B, q):
     # FP64 throughout, results rounded to FP32
     assert np.max(np.abs(J.cpu().numpy() - J_o)) <= 1e-6 * max(1.0, np.max(np.abs(J_o)))
     assert np.max(np.abs(h.cpu().numpy() - h_o)) <= 1e-6 * max(1.0, np.max(np.abs(h_o)))
+
+
+def _autograd_case(plm, B=700, N=13):
+    rng = np.random.default_rng(B)
+    msa = _to(rng.integers(0, 21, size=(B, N), dtype=np.uint8))
+    _, w, beff = plm.reweight(msa, theta=0.8)
+    h = _to((0.2 * rng.standard_normal((N, 21))).astype(np.float32))
+    J = _to((0.1 * rng.standard_normal((N, N, 21, 21))).astype(np.float32))
+    return msa, w, beff, h, J, _to(rng.uniform(0.5, 1.5, size=N))
+
+
+@pytest.mark.parametrize("path", [0, 1, 2, 3, 4, 5, 6, 7])
+def test_objgrad_halves_equal_the_whole(plm, path):
+    from paper_1401_4832_amd import api
+    print(f"objgrad halves path={path}", flush=True)
+    msa, w, beff, h, J, sc = _autograd_case(plm, B=1031)
+    f, gh, gJ = plm.objgrad(msa, w, beff, h, J, path=path, grad_scale=sc)
+    f2, ws = api.objgrad_begin(msa, w, beff, h, J, path=path)
+    moved = ws.clone()  # the contents may be used from another address
+    ws.zero_()
+    for _ in range(2):  # and more than once
+        gh2, gJ2 = api.objgrad_finish(moved, msa, w, beff, h, J, path=path, grad_scale=sc)
+        plm.sync(DEV)
+        assert torch.equal(f, f2) and torch.equal(gh, gh2) and torch.equal(gJ, gJ2)
+
+
+def test_autograd_kept_residuals_equal_recomputed_ones(plm, monkeypatch):
+    from paper_1401_4832_amd import autograd
+    print("autograd kept residuals", flush=True)
+    msa, w, beff, h, J, sc = _autograd_case(plm)
+    grads = []
+    for keep, hooks in ((1 << 30, False), (0, False), (1 << 30, True)):
+        monkeypatch.setattr(autograd, "KEEP_BYTES", keep)
+        hh, JJ = h.clone().requires_grad_(True), J.clone().requires_grad_(True)
+
+        def odd(t):  # hands every tensor back at another place, bytes at an odd address
+            if t.dtype != torch.uint8:
+                return t.clone()
+            return torch.cat([t.new_zeros(1), t.reshape(-1)])[1:].view(t.shape)
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t, odd if hooks else (lambda t: t)):
+            f = plm.plm_objective(hh, JJ, msa, w, beff)
+        (f * sc).sum().backward(retain_graph=True)
+        (f * sc).sum().backward()
+        grads.append((f.detach(), hh.grad, JJ.grad))
+    for g in grads[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(grads[0], g))
+    # no graph, nothing kept
+    with torch.no_grad():
+        assert not plm.plm_objective(h, J, msa, w, beff).requires_grad
