@@ -704,20 +704,27 @@ hipError_t launch_backward_g3(const BatchArgs& b, int32_t nblocks, hipStream_t s
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
 constexpr int kISteps = kMChunk / 32;                 // MFMA steps per chunk
-// Digit planes per pass over the sequences: three (paths 5 to 7: R * 2^22), or
-// two (path 0: the four digits of R * 2^30 in two passes, so that the
-// accumulators of a pass leave registers for the operands in flight).
+// Digit planes of the residuals: three (paths 5 to 7: R * 2^22), two row blocks
+// per wave; or four (path 0: R * 2^30), one row block per wave, so that the
+// accumulators stay at 128 registers and one pass over the sequences takes all.
 template <int ND>
 struct I8Shape {
-  static constexpr int kPassBytes = ND * kRiDigitBytes;                   // copied per site, chunk and pass
-  static constexpr int kChunkBytes = ND == 2 ? kR4ChunkBytes : kRiChunkBytes;
-  static constexpr int kPasses = kChunkBytes / kPassBytes;
-  static constexpr int kSiteStride = kPassBytes + 80;                     // bank-disjoint site runs, as above
-  static constexpr int kBufBytes = 2 * kSiteStride + kPassBytes;
-  static constexpr int kCopies = (kPassBytes + 1023) / 1024;              // wave copies of 1 KB per site and chunk
+  static constexpr int kRB = ND == 4 ? 1 : 2;                              // 32-row blocks per wave
+  static constexpr int kRows = kGWaves * kRB * 32;                         // rows (i, k) per block
+  static constexpr int kChunkBytes = ND * kRiDigitBytes;                   // per site
+  static constexpr int kSiteStride = kChunkBytes + 80;                     // bank-disjoint site runs, as above
+  static constexpr int kBufBytes = 2 * kSiteStride + kChunkBytes;
+  static constexpr int kCopies = (kChunkBytes + 1023) / 1024;              // wave copies of 1 KB per site and chunk
   static constexpr int kCopiesWave = (kG3Sites * kCopies + kGWaves - 1) / kGWaves;
   static_assert((kSiteStride / 16 - kSlot) % 8 == 0 && kSiteStride % 16 == 0, "bank-disjoint site runs");
 };
+static_assert(I8Shape<3>::kChunkBytes == kRiChunkBytes && I8Shape<4>::kChunkBytes == kR4ChunkBytes, "chunk layouts");
+// alignment columns per block
+template <int ND>
+__host__ __device__ inline int32_t i8_block_positions(int32_t q) {
+  const int32_t p = I8Shape<ND>::kRows / q;
+  return p < kGPosMax ? p : kGPosMax;
+}
 
 // One-hot of 16 symbols against k as sixteen int8 values (1 where sigma == k):
 // a byte of x = sigma ^ k is below 32, so x + 0x7f keeps bit 7 clear exactly
@@ -750,16 +757,18 @@ __device__ inline uint4 onehot16_neg(uint4 s16, uint32_t nkk) {
 // ND = 3, LO = false: the residual digits of round(R * 2^22), written to the
 // gradient data part; LO = true (second pass of the precise path): the digits
 // of the remainder, round((R * 2^22 - v) * 2^22), added to it scaled by 2^-44.
-// ND = 2 (path 0): the four digits of round(R * 2^(30 - e)), e = *a.wexp, in
-// two passes over the sequences, the high two first; every pass is cut into
-// segments of kI8SegChunks chunks, so that the int32 sums are exact for any
-// number of sequences, and each pass and segment after the first adds its
+// ND = 4 (path 0): the four digits of round(R * 2^(30 - e)), e = *a.wexp; the
+// sequences are taken in segments of kI8SegChunks chunks, so that the int32 sums
+// are exact for any number of them, and each segment after the first adds its
 // FP64 value to the one stored (exact while the sums stay below 2^53 2^-30,
 // 2^23 sequences).  Bound: the int8 product, four digit planes against three
-// (10.9 ms at the products' measured rate for N = 500, B = 50 000); it took
-// the place of a scatter of FP32 residuals in symbol order through LDS, 85 ->
-// 16 ms there and 1776 -> 426 us at N = 150, B = 8000, with a gradient error
-// against FP64 of 3.0e-8 where the scatter's was 4.9e-8 (N = 40, B = 500).
+// (10.9 ms at the products' measured rate for N = 500, B = 50 000), and LDS,
+// one B fragment per product; it took the place of a scatter of FP32 residuals
+// in symbol order through LDS, 85 -> 16 ms there, 1776 -> 347 us at N = 150,
+// B = 8000 and 52 -> 28 us at N = 40, B = 500, with a gradient error against FP64
+// of 3.0e-8 where the scatter's was 4.9e-8 (N = 40).  Two planes and two row
+// blocks per wave, in two passes whose second reads back and adds to the
+// first's values, took 16 ms, 433 us and 48 us.
 // NEG: the one-hot operand holds -128 for a one (alignments of fewer than
 // kNegSeqMax padded sequences), and the epilogue divides it out exactly.
 constexpr int kI8SegChunks = (1 << 16) - 1;
@@ -767,7 +776,8 @@ template <int ND, bool LO, bool NEG>
 __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Item& it, int8_t* Rb0, int8_t* Rb1,
                                uint8_t* sig0, uint8_t* sig1) {
   using Sh = I8Shape<ND>;
-  const int npos_blk = g3_block_positions(a.q);
+  constexpr int RB = Sh::kRB;
+  const int npos_blk = i8_block_positions<ND>(a.q);
   const int q = a.q, N = a.N, qq = q * q;
   const int i0 = it.sub * npos_blk;
   const int npos = min(npos_blk, N - i0);
@@ -781,17 +791,17 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
   for (int g = 0; g < kG3Sites; ++g)
     rs[g] = __builtin_amdgcn_readfirstlane(g < cnt ? bt.active[it.first + g] - bt.site_base[it.m] : it.r);
 
-  int arow_off[kGRB];
-  uint32_t arow_kk[kGRB];
+  int arow_off[RB];
+  uint32_t arow_kk[RB];
 #pragma unroll
-  for (int m = 0; m < kGRB; ++m) {
-    const int rho = (wid * kGRB + m) * 32 + l32;
+  for (int m = 0; m < RB; ++m) {
+    const int rho = (wid * RB + m) * 32 + l32;
     const bool ok = rho < nrows;
     arow_off[m] = ok ? (rho / q) * kSigPitch : 0;
     arow_kk[m] = (ok ? (uint32_t)(rho % q) : 31u) * 0x01010101u;
     if (NEG) arow_kk[m] = ~arow_kk[m];
   }
-  const bool wave_live = wid * kGRB * 32 < nrows;
+  const bool wave_live = wid * RB * 32 < nrows;
   uint32_t boff[kGT];
 #pragma unroll
   for (int T = 0; T < kGT; ++T) {
@@ -803,7 +813,7 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
   const int nchunks = (a.B3 + kMChunk - 1) / kMChunk;
   const int nch_site = a.B_pad >> 8;
   const int nsig = npos_blk * (kMChunk / 16);
-  // a site's pass over a chunk is 15.75 (10.5) KB: wave copies of 1 KB, the
+  // a site's chunk is 15.75 (21) KB: wave copies of 1 KB, the
   // last one moved back to end at its end (it re-copies bytes with the same
   // values); the LDS destination of a copy is uniform over the wave
   // with three sites, each wave's copies are set up once per item
@@ -814,29 +824,27 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
   for (int j = 0; j < kCW; ++j) {
     const int k = min(wid + kGWaves * j, kG3Sites * kCopies - 1);
     const int g = k / kCopies, part = k - g * kCopies;
-    const int off = min(part * 1024, Sh::kPassBytes - 1024);
+    const int off = min(part * 1024, Sh::kChunkBytes - 1024);
     const int rg = g == 0 ? rs[0] : (g == 1 ? rs[1] : rs[2]);
     rsrc[j] = reinterpret_cast<const char*>(a.R) + (LO ? (size_t)N * nch_site * kRiChunkBytes : 0) +
               (size_t)rg * nch_site * Sh::kChunkBytes + off;
     rdst[j] = (uint32_t)(g * Sh::kSiteStride + off);
   }
-  int poff = 0;  // byte offset of the pass within a chunk
   auto fetch_r = [&](int c, int8_t* dst) {
     if (cnt == kG3Sites) {
 #pragma unroll
       for (int j = 0; j < kCW; ++j)
         if (wid + kGWaves * j < kG3Sites * kCopies)
-          copy16_to_lds(rsrc[j] + (size_t)c * Sh::kChunkBytes + (Sh::kPasses > 1 ? poff : 0),
-                        reinterpret_cast<char*>(dst) + rdst[j], lane);
+          copy16_to_lds(rsrc[j] + (size_t)c * Sh::kChunkBytes, reinterpret_cast<char*>(dst) + rdst[j], lane);
       return;
     }
     const int ninst = cnt * kCopies;
     for (int k = wid; k < ninst; k += kGWaves) {
       const int g = k / kCopies, part = k - g * kCopies;
-      const int off = min(part * 1024, Sh::kPassBytes - 1024);
+      const int off = min(part * 1024, Sh::kChunkBytes - 1024);
       const int rg = g == 0 ? rs[0] : (g == 1 ? rs[1] : rs[2]);
       const char* src = reinterpret_cast<const char*>(a.R) + (LO ? (size_t)N * nch_site * kRiChunkBytes : 0) +
-                        ((size_t)rg * nch_site + c) * Sh::kChunkBytes + (Sh::kPasses > 1 ? poff : 0) + off;
+                        ((size_t)rg * nch_site + c) * Sh::kChunkBytes + off;
       copy16_to_lds(src, reinterpret_cast<char*>(dst) + g * Sh::kSiteStride + off, lane);
     }
   };
@@ -851,7 +859,7 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
     if (tid < nsig) *reinterpret_cast<uint4*>(dst + (tid >> 4) * kSigPitch + (tid & 15) * 16) = sv;
   };
 
-  i32x16 acc[ND][kGRB][kGT];
+  i32x16 acc[ND][RB][kGT];
   int cend = nchunks;  // end of the segment
 
   auto chunk = [&](int c, const int8_t* cur, int8_t* nxt, const uint8_t* scur, uint8_t* snxt) {
@@ -863,7 +871,7 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
     if (wave_live) {
       const char* rb = reinterpret_cast<const char*>(cur);
       const uint8_t* sgb = scur + half * 16;
-      static_assert(kGRB == 2 && kGT == 2, "two row blocks, two column tiles");
+      static_assert(RB <= 2 && kGT == 2, "one or two row blocks, two column tiles");
       auto ldsym = [&](int m, int t) { return *reinterpret_cast<const uint4*>(sgb + arow_off[m] + t * 32); };
       auto onehot = [&](uint4 s16, int m) {
         return NEG ? onehot16_neg(s16, arow_kk[m]) : onehot16_i8(s16, arow_kk[m]);
@@ -889,7 +897,8 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
         // one-hot operand; then each product pair followed by the read of the
         // fragment two ahead (an LDS wait then covers only the reads a product
         // needs)
-        const uint4 s1 = ldsym(1, t);
+        uint4 s1;
+        if constexpr (RB == 2) s1 = ldsym(1, t);
         uint4 bq[2 * ND];
         bq[0] = ldb(0);
         bq[1] = ldb(1);
@@ -900,13 +909,16 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
         s0 = ldsym(0, min(t + 1, kISteps - 1));
         bq[2] = ldb(2);
         __builtin_amdgcn_sched_barrier(0);
-        const uint4 av1 = onehot(s1, 1);
-        prod(0, 1, av1, bq[0]);
-        __builtin_amdgcn_sched_barrier(0);
+        uint4 av1;
+        if constexpr (RB == 2) {
+          av1 = onehot(s1, 1);
+          prod(0, 1, av1, bq[0]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int f = 1; f < 2 * ND; ++f) {
           prod(f, 0, av0, bq[f]);
-          prod(f, 1, av1, bq[f]);
+          if constexpr (RB == 2) prod(f, 1, av1, bq[f]);
           __builtin_amdgcn_sched_barrier(0);
           if (f + 2 < 2 * ND) bq[f + 2] = ldb(f + 2);
           __builtin_amdgcn_sched_barrier(0);
@@ -922,7 +934,7 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
 #pragma unroll
     for (int d = 0; d < ND; ++d)
 #pragma unroll
-      for (int m = 0; m < kGRB; ++m)
+      for (int m = 0; m < RB; ++m)
 #pragma unroll
         for (int T = 0; T < kGT; ++T) acc[d][m][T] = i32x16{};
     fetch_r(cb, Rb0);
@@ -952,8 +964,8 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
       auto out = gmem_w(a.gJ) + ((size_t)rg * N + i0) * qq + sidx;
       const int self0 = (rg - i0) * q;  // rows of the site's own column
 #pragma unroll
-      for (int m = 0; m < kGRB; ++m) {
-        const int row0 = (wv * kGRB + m) * 32 + 4 * hi32;
+      for (int m = 0; m < RB; ++m) {
+        const int row0 = (wv * RB + m) * 32 + 4 * hi32;
         // the stored values of a few rows are read together, as many as registers allow
         constexpr int kOld = ND == 3 ? 4 : 16;
         double old[kOld];
@@ -968,10 +980,10 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
           }
           const int row = row0 + 8 * (j >> 2) + (j & 3);
           if (row < nrows) {
-            // exact: every digit sum is an integer below 2^31
-            const double v = ND == 3 ? (double)acc[0][m][T][j] * 65536.0 + (double)acc[1][m][T][j] * 256.0 +
-                                           (double)acc[ND - 1][m][T][j]
-                                     : (double)acc[0][m][T][j] * 256.0 + (double)acc[1][m][T][j];
+            // exact: every digit sum is an integer below 2^31, the whole below 2^53
+            double v = (double)acc[0][m][T][j];
+#pragma unroll
+            for (int d = 1; d < ND; ++d) v = v * 256.0 + (double)acc[d][m][T][j];
             out[row * q] = (unsigned)(row - self0) < (unsigned)q ? 0.0 : old[j % kOld] + v * scale;
           }
         }
@@ -987,13 +999,10 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
           LO);
   } else {
     const double unit = ldexp(kNeg, __builtin_amdgcn_readfirstlane(*a.wexp) - kR4ScaleLog2);
-    for (int pass = 0; pass < Sh::kPasses; ++pass) {
-      poff = pass * Sh::kPassBytes;
-      for (int cb = 0; cb < nchunks; cb += kI8SegChunks) {
-        cend = min(nchunks, cb + kI8SegChunks);
-        accumulate(cb);
-        if (wave_live) flush(pass == 0 ? unit * 65536.0 : unit, pass > 0 || cb > 0);
-      }
+    for (int cb = 0; cb < nchunks; cb += kI8SegChunks) {
+      cend = min(nchunks, cb + kI8SegChunks);
+      accumulate(cb);
+      if (wave_live) flush(unit, cb > 0);
     }
   }
 }
@@ -1020,18 +1029,21 @@ __global__ __launch_bounds__(kGThreads) void bwd_i8_kernel(BatchArgs b) {
   }
 }
 
-int32_t i8_backward_blocks_per_site(int32_t N, int32_t q) { return g3_backward_blocks_per_site(N, q); }
+int32_t i8_backward_blocks_per_site(int32_t N, int32_t q, int32_t digits) {
+  const int32_t p = digits == 4 ? i8_block_positions<4>(q) : i8_block_positions<3>(q);
+  return (N + p - 1) / p;
+}
 
 int32_t i8_resident_blocks(int32_t digits) {
   int per = 0;
   const hipError_t e =
-      digits == 4 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bwd_i8_kernel<2, false>, kGThreads, 0)
+      digits == 4 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bwd_i8_kernel<4, false>, kGThreads, 0)
                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bwd_i8_kernel<3, false>, kGThreads, 0);
   return (e == hipSuccess && per > 0) ? per : 1;
 }
 
 hipError_t launch_backward_i8(const BatchArgs& b, int32_t digits, int32_t nblocks, int32_t lo, hipStream_t st) {
-  if (digits == 4) hipLaunchKernelGGL((bwd_i8_kernel<2, false>), dim3(nblocks), dim3(kGThreads), 0, st, b);
+  if (digits == 4) hipLaunchKernelGGL((bwd_i8_kernel<4, false>), dim3(nblocks), dim3(kGThreads), 0, st, b);
   else if (lo) hipLaunchKernelGGL((bwd_i8_kernel<3, true>), dim3(nblocks), dim3(kGThreads), 0, st, b);
   else hipLaunchKernelGGL((bwd_i8_kernel<3, false>), dim3(nblocks), dim3(kGThreads), 0, st, b);
   return hipGetLastError();

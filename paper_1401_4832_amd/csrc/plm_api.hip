@@ -333,7 +333,7 @@ int32_t eval_tiles(const PathSpec& p, int32_t B, int32_t nb) {
 
 int32_t eval_bwd_blocks(const PathSpec& p, int32_t N, int32_t q) {
   if (p.bwd_g3) return g3_backward_blocks_per_site(N, q);
-  if (p.bwd_i8) return i8_backward_blocks_per_site(N, q);
+  if (p.bwd_i8) return i8_backward_blocks_per_site(N, q, p.bwd_i8);
   return mfma_backward_blocks_per_site(N, q);
 }
 

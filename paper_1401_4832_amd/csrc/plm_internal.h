@@ -579,8 +579,8 @@ int32_t fwd_i8_resident_blocks();
 hipError_t launch_jquant(const BatchArgs& b, int32_t total_sites, hipStream_t st);
 hipError_t launch_fwd_i8(const BatchArgs& b, int32_t nblocks, hipStream_t st);
 // grouped int8 fixed-point MFMA gradient (three sites per item, R as digits)
-int32_t i8_backward_blocks_per_site(int32_t N, int32_t q);
 // digits: 3 (paths 5 to 7) or 4 (path 0)
+int32_t i8_backward_blocks_per_site(int32_t N, int32_t q, int32_t digits);
 int32_t i8_resident_blocks(int32_t digits);
 // lo: the second pass of the precise path (the remainder digits, added in)
 hipError_t launch_backward_i8(const BatchArgs& b, int32_t digits, int32_t nblocks, int32_t lo, hipStream_t st);

@@ -74,10 +74,11 @@ def test_frequencies_sizes(plm, B, N, q):
     np.testing.assert_allclose(f.cpu().numpy(), sv.frequencies(msa, w, float(w.sum()), q), rtol=1e-12, atol=1e-15)
 
 
-# the four-digit gradient of path 0: one and two row groups per chunk, three-site groups with
-# remainders, weights above one and over eight decades, all-zero weights
+# the four-digit gradient of path 0: one and two row groups per chunk, whole and begun row blocks,
+# three-site groups with remainders, weights above one and over eight decades, all-zero weights
 @pytest.mark.parametrize("B,N,q,wexp", [(1, 2, 2, 0), (255, 4, 21, 0), (257, 25, 21, 3), (513, 24, 5, -4),
-                                        (3100, 49, 21, 0), (700, 31, 21, 12), (300, 7, 21, None)])
+                                        (3100, 49, 21, 0), (700, 31, 21, 12), (300, 7, 21, None),
+                                        (256, 12, 21, 0), (129, 13, 21, 0), (300, 33, 5, 1)])
 def test_path0_gradient_digits(plm, B, N, q, wexp):
     from tests.helpers import random_params
     print(f"path 0 gradient B={B} N={N} q={q} wexp={wexp}", flush=True)
