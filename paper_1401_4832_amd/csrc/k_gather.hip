@@ -13,7 +13,9 @@
 // with the symbols 25.  Measured, all sites at N = 500, B = 50 000: 24 -> 19 ms
 // (the softmax over 21 lanes by shuffles, a row at a time with its loads inside
 // the loop and byte stores of the digits, took a third of it), N = 150,
-// B = 8000: 830 -> 457 us, N = 40, B = 500: 66 -> 23 us.
+// B = 8000: 830 -> 425 us, N = 40, B = 500: 66 -> 22 us.  A wave's read and its
+// two vector instructions take 2.7 clocks a CU at best (a read alone 2.2); the
+// loop takes 2.8 at N = 500.
 #include "plm_internal.h"
 
 namespace plm {
@@ -56,9 +58,17 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
   const int slot = lane / kSlot, s = lane - slot * kSlot;
   const int slotA = slot < kSlots ? slot : kSlots - 1;  // lane 63 shadows slot 2 for addressing
   const bool act = (slot < kSlots) && (s < q);
-  const int tile0 = tile * tileSeq;
-  const int tw = wid * (NB * kSlots) + slotA;  // tile row of row j: tw + 3j
-  const int bw = tile0 + tw;
+  // the alignment's groups of 48 rows, divided evenly over the tiles; a tile's
+  // groups go to its waves in turn, so that tiles and waves are equally loaded
+  // (whole tiles first left the last one nearly empty: with N = 120, B = 5000,
+  // 3.3 tiles a site, 178 -> 156 us; N = 150, B = 8000 476 -> 425 us with the rows
+  // per tile chosen for it)
+  const int ngroups = (a.B3 + kParkRows - 1) / kParkRows, tgroups = (ngroups + a.tiles - 1) / a.tiles;
+  const int tile0 = tile * tgroups * kParkRows;
+  const int tgr = min(tgroups, ngroups - tile * tgroups);  // this tile's groups with rows (none: not positive)
+  const int ng = __builtin_amdgcn_readfirstlane(max(0, min(NB / 16, (tgr - wid + kFwdWaves - 1) / kFwdWaves)));  // this wave's
+  const int tw = wid * kParkRows + slotA;  // the tile row of the wave's row j: tw + trow(j)
+  constexpr auto trow = [](int j) { return (j / 16) * (kFwdWaves * kParkRows) + (j % 16) * kSlots; };
 
   AT E[NB];
   AT hv = act ? (AT)gmem(a.h)[r * q + s] : (AT)0;
@@ -68,10 +78,9 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
 
   const size_t Jr = (size_t)r * N * qq;
   const int nchunks = (N + kFwdPos - 1) / kFwdPos;
-  // a wave whose rows all lie past the alignment's (padded to three) has
-  // nothing to gather: no row of it is read by the gradient (the rows of the
-  // last gradient chunk past the alignment are zeroed once per alignment)
-  const bool live = tile0 + wid * (NB * kSlots) < a.B3;
+  // groups that lie past the alignment's rows (padded to three) are left out:
+  // no row of them is read by the gradient (the rows of the last gradient chunk
+  // past the alignment are zeroed once per alignment)
   const char* L = reinterpret_cast<const char*>(lds);
   // LDS byte address of row (p, sigma), this lane's word: p * kPosBytes (an
   // immediate offset) + sigma * 256 + 4 * lane, where the last two are one
@@ -104,7 +113,8 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
 #pragma unroll
     for (int k = 0; k < kSPer; ++k) {
       const int e = tid + k * kFwdThreads;
-      if (e < tileSeq)
+      sv[k] = uint2{0, 0};
+      if (e < tgr * kParkRows)
         sv[k] = gload_u2(a.msa_cm + ((size_t)(c >> 1) * a.B_pad + tile0 + e) * kFwdChunk + 8 * (c & 1));
     }
   };
@@ -141,7 +151,7 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
     store();
     __syncthreads();
     if (c + 1 < nchunks) load(c + 1);
-    if (!live) continue;
+    if (ng == 0) continue;
     // row j + 1's words are read while row j's are added, and its symbols one
     // row earlier still: one row at a time left the LDS idle between a row's
     // reads and its sums
@@ -162,24 +172,30 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
       }
     };
     gather(sgl[tw], v[0]);
-    uint2 sn = sgl[tw + 3];
+    uint2 sn = sgl[tw + kSlots];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const uint2 sc = sn;
-      if (j + 2 < NB) sn = sgl[tw + 3 * (j + 2)];
-      if (j + 1 < NB) gather(sc, v[(j + 1) & 1]);
-      __builtin_amdgcn_sched_barrier(0);
-      // two accumulation chains (even and odd columns)
-      const AT(&d)[kFwdPos] = v[j & 1];
-      AT acc0 = E[j], acc1 = d[1];
+    for (int g = 0; g < NB / 16; ++g) {
+      if (g >= ng) continue;
 #pragma unroll
-      for (int p = 0; p < kFwdPos; ++p) {
-        if (p == 1) continue;
-        if (p & 1) acc1 += d[p];
-        else acc0 += d[p];
+      for (int jj = 0; jj < 16; ++jj) {
+        const int j = 16 * g + jj;
+        const uint2 sc = sn;
+        // (past the wave's last group these reads are of rows that are not used, inside the tile's arrays)
+        if (j + 2 < NB) sn = sgl[tw + trow(j + 2)];
+        if (j + 1 < NB) gather(sc, v[(j + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        // two accumulation chains (even and odd columns)
+        const AT(&d)[kFwdPos] = v[j & 1];
+        AT acc0 = E[j], acc1 = d[1];
+#pragma unroll
+        for (int p = 0; p < kFwdPos; ++p) {
+          if (p == 1) continue;
+          if (p & 1) acc1 += d[p];
+          else acc0 += d[p];
+        }
+        E[j] = acc0 + acc1;
+        __builtin_amdgcn_sched_barrier(0);
       }
-      E[j] = acc0 + acc1;
-      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
@@ -193,8 +209,8 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
   __syncthreads();  // every wave is done with the last chunk
   AT* park = reinterpret_cast<AT*>(lds) + wid * (kParkRows * kSlot);
 #pragma unroll 1
-  for (int g = 0; live && g < NB / 16; ++g) {
-    const int b0 = tile0 + wid * (NB * kSlots) + g * kParkRows;  // the first of the 48 rows
+  for (int g = 0; g < ng; ++g) {
+    const int b0 = tile0 + (g * kFwdWaves + wid) * kParkRows;  // the first of the 48 rows
     // this lane's row: its symbol at the site and its weight
     const int b = b0 + min(lane, kParkRows - 1);
     const int sr = gmem(a.msa_cm)[((size_t)(r / kFwdChunk) * a.B_pad + b) * kFwdChunk + r % kFwdChunk];

@@ -267,21 +267,23 @@ int ensure_pin(plm_ctx* c, size_t words) {
   return PLM_OK;
 }
 
-// Rows per wave of the gather forward's tile: a compute unit works through its
-// items one after the other, so the rule takes the tile with the least
-// (items per unit, rounded up) x (rows + 4), where 4 rows' worth is what
-// staging the couplings costs an item.  Measured, forward and gradient of
-// path 5 with 16 / 32 / 64 rows: N = 40, B = 500 52 / 58 / 80 us; N = 120,
-// B = 5000 324 / 319 / 290 us; N = 150, B = 8000 684 / 673 / 780 us; N = 500,
-// B = 50 000 32.9 / 31.4 / 29.4 ms.
+// Rows per wave of the gather forward's tile at most.  A site's 48-row groups
+// are divided evenly over its tiles, two rows a wave for each, and the items of
+// a compute unit share its LDS, so the rule takes the tile with the least
+// (items per unit, rounded up, + 1/2) x (rows + 8): the half is what the last
+// item loses without a second one beside it, the eight rows' worth what staging
+// the couplings costs an item.  Measured, forward alone with 16 / 32 / 64 rows:
+// N = 40, B = 500 34 / 41 / 42 us; N = 100, B = 3000 135 / 115 / 123 us;
+// N = 120, B = 5000 249 / 225 / 177 us; N = 150, B = 8000 429 / 427 / 399 us;
+// N = 150, B = 16 000 791 / 751 / 780 us; N = 300, B = 20 000 3.55 / 3.33 / 3.16 ms.
 int32_t pick_nb(int32_t N, int32_t B, int32_t ncu, int32_t tile_seqs) {
   if (tile_seqs == 16 || tile_seqs == 32 || tile_seqs == 64) return tile_seqs;
   int32_t best = 16;
   int64_t cost = 0;
   for (int32_t nb : {64, 32, 16}) {
-    const int32_t t = forward_tile_seqs(nb);
-    const int64_t items = (int64_t)N * ((B + t - 1) / t);
-    const int64_t k = (items + ncu - 1) / ncu * (nb + 4);
+    const int32_t t = forward_tile_seqs(nb), tiles = (B + t - 1) / t;
+    const int32_t rows = 2 * (((B + 47) / 48 + tiles - 1) / tiles);
+    const int64_t k = (2 * (((int64_t)N * tiles + ncu - 1) / ncu) + 1) * (rows + 8);
     if (cost == 0 || k < cost) {
       cost = k;
       best = nb;

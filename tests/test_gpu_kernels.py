@@ -98,6 +98,27 @@ def test_path0_gradient_digits(plm, B, N, q, wexp):
     assert np.max(np.abs(gJ.cpu().numpy() - gJo)) <= 2e-6 * beff
 
 
+@pytest.mark.parametrize("path", [0, 7])
+@pytest.mark.parametrize("B,N,q", [(47, 3, 4), (49, 3, 21), (385, 9, 21), (1153, 2, 21), (3000, 100, 5), (5000, 120, 3)])
+def test_gather_forward_even_tiles(plm, path, B, N, q):
+    """48-row groups divided over tiles and waves: begun groups, waves with none, each tile size."""
+    from tests.helpers import random_params
+    print(f"gather forward path={path} B={B} N={N} q={q}", flush=True)
+    rng = np.random.default_rng(B)
+    msa = rng.integers(0, q, size=(B, N), dtype=np.uint8)
+    w = rng.uniform(0.1, 1.0, size=B)
+    beff = float(w.sum())
+    h, J = random_params(B + N, N, q, 0.3, 0.2 / np.sqrt(N))
+    h, J = h.astype(np.float32), J.astype(np.float32)
+    f, gh, gJ = plm.objgrad(_to(msa), _to(w), _to(np.array([beff])), _to(h), _to(J), path=path)
+    plm.sync(DEV)
+    fo, gho, gJo = oracle.objgrad(msa, w, beff, h.astype(np.float64), J.astype(np.float64))
+    # a row left out or taken twice moves f by some log q / B >= 2e-4; the FP32 paths' own bounds
+    assert np.max(np.abs(f.cpu().numpy() - fo)) <= 1e-5 * max(1.0, np.max(np.abs(fo)))
+    assert np.max(np.abs(gh.cpu().numpy() - gho)) <= 2e-6 * beff
+    assert np.max(np.abs(gJ.cpu().numpy() - gJo)) <= 2e-6 * beff
+
+
 def test_path0_gradient_carries_nan(plm):
     """Energies that overflow give a NaN objective and a NaN gradient, not the digits of one."""
     print("path 0 gradient NaN", flush=True)
