@@ -63,15 +63,12 @@ __device__ inline void for_each_param(const SymArgs& a, F&& f) {
 // the solve kernel's single CU fetched a cache line per value).
 template <int NV>
 __device__ inline void block_partials(double (&v)[NV], double* red, double* part, int32_t nblk) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-  for (int k = 0; k < NV; ++k)
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+  const int wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  static_assert(NV <= 32, "one value a lane after the tree's fifth level");
+  int ix = 0, cnt = NV;
+  wave_sum_vec<NV>(v, ix, cnt);
   __syncthreads();
-  if (lane == 0)
-#pragma unroll
-    for (int k = 0; k < NV; ++k) red[wid * NV + k] = v[k];
+  if (cnt > 0) red[wid * NV + ix] = v[0];
   __syncthreads();
   if (threadIdx.x < NV) {
     double t = 0.0;
