@@ -62,10 +62,10 @@ MFMA_BF16_PEAK = 2.5e15
 MFMA_I8_PEAK = 5.0e15
 PATH_NAMES = {0: "gather_fp32", 1: "mfma_bf16x2", 2: "gather_mfma_fp32", 3: "mfma_fp32",
               4: "gather_mfma_f16x2", 5: "gather_mfma_i8x3", 6: "mfma_i8x3", 7: "gather64_mfma_i8x6"}
-# 16-bit pieces (or int8 digits) of the non-one-hot operand, per path: (forward, backward); 0 = LDS gather/scatter
-PATH_PIECES = {0: (0, 0), 1: (2, 2), 2: (0, 3), 3: (3, 3), 4: (0, 2), 5: (0, 3), 6: (3, 3), 7: (0, 6)}
+# 16-bit pieces (or int8 digits) of the non-one-hot operand, per path: (forward, backward); 0 = LDS gather
+PATH_PIECES = {0: (0, 4), 1: (2, 2), 2: (0, 3), 3: (3, 3), 4: (0, 2), 5: (0, 3), 6: (3, 3), 7: (0, 6)}
 # the int8 matrix-core kernels (path, direction)
-INT8_KERNELS = {(5, "backward"), (6, "backward"), (6, "forward"), (7, "backward")}
+INT8_KERNELS = {(0, "backward"), (5, "backward"), (6, "backward"), (6, "forward"), (7, "backward")}
 # kernels on the 4:2 structured-sparse matrix-core product (one instruction slot
 # covers two dense-equivalent operations)
 SPARSE_KERNELS = {(6, "forward")}
@@ -417,7 +417,7 @@ def main():
             active = units_launch / (s0.B * s0.N * Q)
             alg_bytes = None if (ragged or symmetric) else active * s0.N * Q * Q * 4 + s0.B * s0.N
             if npc:
-                kname = {4: "backward_g3", 5: "backward_i8", 6: "backward_i8"}.get(path, "backward_mfma") \
+                kname = {0: "backward_i8x4", 4: "backward_g3", 5: "backward_i8", 6: "backward_i8"}.get(path, "backward_mfma") \
                     if dom == "backward" else ("forward_i8" if path == 6 else "forward_mfma")
                 int8 = (path, dom) in INT8_KERNELS
                 peak = MFMA_I8_PEAK if int8 else MFMA_BF16_PEAK

@@ -50,8 +50,9 @@ __global__ __launch_bounds__(64 * kScWaves) void pair_score_kernel(const float* 
   __shared__ double mean[kScWaves][kQMax];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < N; k += gridDim.x * blockDim.x) raw[(size_t)k * N + k] = 0.0;
-  const int p0 = (blockIdx.x * kScWaves + wid) * per, p1 = min(npairs, p0 + per);
-  if (p0 >= p1) return;
+  const int64_t lo = (int64_t)(blockIdx.x * kScWaves + wid) * per;
+  if (lo >= npairs) return;
+  const int p0 = (int)lo, p1 = (int)min((int64_t)npairs, lo + per);
   // row i of pair p0: the last i whose first pair i (2 N - 1 - i) / 2 is <= p0
   int i, j;
   {
