@@ -268,10 +268,8 @@ __device__ inline void sweep_unit(double* M, double (*col)[2][kGjTile], bool& ba
 // Bound: the chain of 32 steps per unit (barrier, LDS, two reciprocals); 44 us for
 // two units.  All 128 indices in registers took 80 us (four rows a thread) and
 // 104 us (one row a thread, one index a step): LDS reads and spills.
-__global__ __launch_bounds__(kMfThreads) void gj_pivot_kernel(double* A, int64_t ld, int32_t u0, int32_t nu,
-                                                              int32_t* flag) {
-  __shared__ double M[kPv * kPvPitch];
-  __shared__ __attribute__((aligned(16))) double col[2][2][kGjTile];
+__device__ __forceinline__ void pivot_block(double* A, int64_t ld, int32_t u0, int32_t nu, int32_t* flag, double* M,
+                                   double (&col)[2][2][kGjTile]) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, l16 = lane & 15, lk = lane >> 4;
   const size_t o = (size_t)u0 * kGjTile;
   const int w = nu * kGjTile;
@@ -450,21 +448,13 @@ __global__ __launch_bounds__(kMfThreads, 2) void gj_panel_kernel(double* A, int6
   }
 }
 
-// Update of the tiles outside the pivot block: A_ij -= W_i X_j^T, one block
-// per 2 x 2 units (a, b), a >= b, one unit per wave (64 x 64 in registers, sixteen
+// Update of the tiles outside pivot block ps: A_ij -= W_i X_j^T, tile t a 2 x 2 of
+// units (a, b), a >= b, one unit per wave (64 x 64 in registers, sixteen
 // FP64 products per four panel indices); chunks of kGjK panel indices are
 // double-buffered in LDS, each wave staging one of the block's four panel units.
-// The blocks are dealt to the XCDs in runs, so that a run's panels stay in one L2.
-// Bound: the FP64 matrix cores (38 TFLOP/s of the 69 they reach alone) and the
-// last round of blocks, a part of the chip's; n = 6000: 117 us per 128 indices,
-// where 64-index updates of both triangles in vector FP64 took 328 us each.
-__global__ __launch_bounds__(kMfThreads, 2) void gj_update_kernel(double* A, int64_t ld, int32_t nt, int32_t ps,
-                                                                  int32_t u0, int32_t nu, int32_t nblk) {
-  __shared__ __attribute__((aligned(16))) double L[2][2][kGjK * kGjPitch];
-  // block -> pair (a, b) of pivot-block-sized units, a >= b, both outside ps
-  const int per = (nblk + kQueues - 1) / kQueues;
-  const int t = (blockIdx.x % kQueues) * per + blockIdx.x / kQueues;
-  if (t >= nblk) return;
+using UpdateLds = double[2][2][kGjK * kGjPitch];
+__device__ __forceinline__ void update_tile(double* A, int64_t ld, int32_t nt, int32_t ps, int32_t u0, int32_t nu, int32_t t,
+                                   UpdateLds& L) {
   int a = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
   while (a * (a + 1) / 2 > t) --a;
   while ((a + 1) * (a + 2) / 2 <= t) ++a;
@@ -550,6 +540,49 @@ __global__ __launch_bounds__(kMfThreads, 2) void gj_update_kernel(double* A, int
       for (int n = 0; n < 4; ++n)
 #pragma unroll
         for (int r = 0; r < 4; ++r) C[(size_t)(16 * m + 4 * r) * ld + 16 * n] = acc[m][n][r];
+}
+
+// Whole rounds of the update's tiles over the chip, dealt to the XCDs in runs, so
+// that a run's panels stay in one L2.  The tile that holds the next pivot block
+// (index tp) is one of them: it takes the place of the last.
+// Bound: the FP64 matrix cores (43 TFLOP/s of the 69 they reach alone); n = 6000:
+// 50 us a round of 512 blocks, where 64-index updates of both triangles in vector
+// FP64 took 328 us each.
+__global__ __launch_bounds__(kMfThreads, 2) void gj_update_kernel(double* A, int64_t ld, int32_t nt, int32_t ps,
+                                                                  int32_t u0, int32_t nu, int32_t ntile, int32_t tp) {
+  __shared__ __attribute__((aligned(16))) UpdateLds L;
+  const int per = (ntile + kQueues - 1) / kQueues;
+  int t = (blockIdx.x % kQueues) * per + blockIdx.x / kQueues;
+  if (t >= ntile) return;
+  if (t == ntile - 1 && tp >= ntile) t = tp;
+  update_tile(A, ld, nt, ps, u0, nu, t, L);
+}
+
+// The rest of the tiles, from first on, beside the sweep of the next pivot block
+// (block 0), which took 44 us alone after an update whose last round left most of
+// the chip idle: n = 6000, 117 + 44 -> 100 + 45 us (with one or two tiles for
+// every other unit here, 96 + 48 and 73 + 73 us).  With no whole round (first = 0)
+// block 0 updates its own tile (index tp) before the sweep.
+// Bound: the sweep's chain, or with few blocks a tile's.
+__global__ __launch_bounds__(kMfThreads) void gj_sweep_kernel(double* A, int64_t ld, int32_t nt, int32_t ps, int32_t u0,
+                                                              int32_t nu, int32_t first, int32_t tp, int32_t un,
+                                                              int32_t nun, int32_t* flag) {
+  __shared__ __attribute__((aligned(16))) double M[kPv * kPvPitch];
+  __shared__ __attribute__((aligned(16))) double col[2][2][kGjTile];
+  static_assert(sizeof(UpdateLds) <= sizeof(M), "a tile's panels take the pivot block's place");
+  UpdateLds& L = *reinterpret_cast<UpdateLds*>(M);
+  if (blockIdx.x > 0) {
+    int t = first + (int)blockIdx.x - 1;
+    if (first == 0) t += t >= tp;                       // tp is block 0's
+    else if (t == tp) t = first - 1;                    // tp took the place of this one
+    update_tile(A, ld, nt, ps, u0, nu, t, L);
+    return;
+  }
+  if (first == 0 && tp >= 0) {
+    update_tile(A, ld, nt, ps, u0, nu, tp, L);
+    __syncthreads();  // the tile is written, its panels are done with
+  }
+  pivot_block(A, ld, un, nun, flag, M, col);
 }
 
 // ---- output ------------------------------------------------------------------
@@ -647,22 +680,29 @@ hipError_t launch_mf_correlation(const uint8_t* msa, const int32_t* order, const
   return hipGetLastError();
 }
 
-hipError_t launch_mf_invert(double* C, int32_t n_pad, int32_t* flag, hipStream_t st) {
+hipError_t launch_mf_invert(double* C, int32_t n_pad, int32_t ncu, int32_t* flag, hipStream_t st) {
   const int nt = n_pad / kGjTile, ns = (nt + 1) / 2;  // units, pivot blocks
   const int64_t ld = n_pad;
-  for (int p = 0; p < ns; ++p) {
-    const int u0 = 2 * p, nu = nt - u0 < 2 ? nt - u0 : 2;
-    hipLaunchKernelGGL(gj_pivot_kernel, dim3(1), dim3(kMfThreads), 0, st, C, ld, u0, nu, flag);
-    if (nt > nu) {
-      hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (nt - nu)), dim3(kMfThreads), 0, st, C, ld, u0, nu);
-      const int nblk = (ns - 1) * ns / 2;  // pairs a >= b of the other blocks
-      const int grid = (nblk + kQueues - 1) / kQueues * kQueues;
-      hipLaunchKernelGGL(gj_update_kernel, dim3(grid), dim3(kMfThreads), 0, st, C, ld, nt, p, u0, nu, nblk);
-    }
+  const int nblk = (ns - 1) * ns / 2;  // pairs a >= b of the blocks besides the pivot
+  auto units = [&](int p) { return nt - 2 * p < 2 ? nt - 2 * p : 2; };
+  hipLaunchKernelGGL(gj_sweep_kernel, dim3(1), dim3(kMfThreads), 0, st, C, ld, nt, 0, 0, 0, 0, -1, 0, units(0), flag);
+  for (int p = 0; p < ns && ns > 1; ++p) {
+    const int u0 = 2 * p, nu = units(p);
+    hipLaunchKernelGGL(gj_panel_kernel, dim3(2 * (nt - nu)), dim3(kMfThreads), 0, st, C, ld, u0, nu);
+    // the next pivot block is pair (p, p) of the others; the last update is followed by no sweep
+    const bool last = p + 1 == ns;
+    const int tp = last ? -1 : p * (p + 1) / 2 + p;
+    const int whole = last ? nblk : nblk / (2 * ncu) * (2 * ncu);  // rounds of two blocks per compute unit
+    if (whole > 0)
+      hipLaunchKernelGGL(gj_update_kernel, dim3((whole + kQueues - 1) / kQueues * kQueues), dim3(kMfThreads), 0, st, C,
+                         ld, nt, p, u0, nu, whole, tp);
+    if (!last)
+      hipLaunchKernelGGL(gj_sweep_kernel, dim3(1 + nblk - (whole > 0 ? whole : 1)), dim3(kMfThreads), 0, st, C, ld, nt,
+                         p, u0, nu, whole, tp, u0 + 2, units(p + 1), flag);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  return hipGetLastError();
 }
 
 hipError_t launch_mf_output(const double* Cinv, int32_t n_pad, const double* fi, int32_t N, int32_t q, float* h,

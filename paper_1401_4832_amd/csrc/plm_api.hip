@@ -1193,7 +1193,7 @@ int plm_mf_init(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q,
   HIPCHK(c, launch_check_f64(w, (size_t)B, c->pin_dev, st));
   HIPCHK(c, launch_mf_frequencies(msa, B, N, q, w, beff, pseudocount, order, start, fi, c->pin_dev, st));
   HIPCHK(c, launch_mf_correlation(msa, order, start, w, beff, fi, B, N, q, pseudocount, C, n_pad, st));
-  HIPCHK(c, launch_mf_invert(C, n_pad, c->pin_dev, st));
+  HIPCHK(c, launch_mf_invert(C, n_pad, c->ncu, c->pin_dev, st));
   HIPCHK(c, launch_mf_output(C, n_pad, fi, N, q, h_out, J_out, c->pin_dev, st));
   HIPCHK(c, hipStreamSynchronize(st));
   return flags_status(c);

@@ -640,7 +640,7 @@ hipError_t launch_mf_frequencies(const uint8_t* msa, int32_t B, int32_t N, int32
 hipError_t launch_mf_correlation(const uint8_t* msa, const int32_t* order, const int32_t* start, const double* w,
                                  const double* beff, const double* fi, int32_t B, int32_t N, int32_t q,
                                  double lam, double* C, int32_t n_pad, hipStream_t st);
-hipError_t launch_mf_invert(double* C, int32_t n_pad, int32_t* flag, hipStream_t st);
+hipError_t launch_mf_invert(double* C, int32_t n_pad, int32_t ncu, int32_t* flag, hipStream_t st);
 hipError_t launch_mf_output(const double* Cinv, int32_t n_pad, const double* fi, int32_t N, int32_t q, float* h,
                             float* J, int32_t* flag, hipStream_t st);
 hipError_t launch_reweight(const uint8_t* msa, int32_t B, int32_t N, int32_t q, double theta,

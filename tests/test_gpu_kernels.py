@@ -136,7 +136,8 @@ def test_path0_gradient_carries_nan(plm):
 
 # block sweep of 1, 2, 3, 5 and 11 units of 64 indices (a last pivot block of one unit and of two), and more
 # sequences of one state than a wave takes at once
-@pytest.mark.parametrize("N,B,q", [(3, 2000, 21), (6, 900, 21), (9, 700, 21), (16, 400, 21), (35, 260, 21), (90, 300, 6)])
+@pytest.mark.parametrize("N,B,q", [(3, 2000, 21), (6, 900, 21), (9, 700, 21), (16, 400, 21), (35, 260, 21), (90, 300, 6),
+                                   (214, 300, 21)])
 def test_mean_field_block_sweep(plm, N, B, q):
     from oracle import meanfield
     print(f"mean field N={N} B={B} q={q}", flush=True)
