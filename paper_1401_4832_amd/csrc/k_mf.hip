@@ -560,8 +560,8 @@ __global__ __launch_bounds__(kMfThreads, 2) void gj_update_kernel(double* A, int
 
 // The rest of the tiles, from first on, beside the sweep of the next pivot block
 // (block 0), which took 44 us alone after an update whose last round left most of
-// the chip idle: n = 6000, 117 + 44 -> 100 + 45 us (with one or two tiles for
-// every other unit here, 96 + 48 and 73 + 73 us).  With no whole round (first = 0)
+// the chip idle: n = 6000, 117 + 44 -> 100 + 45 us (with 255 or 510 of
+// its 1081 tiles here instead of what whole rounds leave, 96 + 48 and 73 + 73 us).  With no whole round (first = 0)
 // block 0 updates its own tile (index tp) before the sweep.
 // Bound: the sweep's chain, or with few blocks a tile's.
 __global__ __launch_bounds__(kMfThreads) void gj_sweep_kernel(double* A, int64_t ld, int32_t nt, int32_t ps, int32_t u0,
