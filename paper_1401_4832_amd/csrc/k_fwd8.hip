@@ -293,10 +293,15 @@ __device__ inline void fwd_i8_item(const BatchArgs& bt, const EvalArgs* ea, cons
       // expcnt left at their maxima, so the stage copies stay in flight): the
       // one-hot operands are then built while the first B operands are read
       __builtin_amdgcn_s_waitcnt(0xc07f);
+      // (at a raised priority, so that the wave that builds operands is not held up by
+      // the other one's products: all sites at N = 500, B = 50 000 8.68 -> 8.59 ms)
+      __builtin_amdgcn_s_setprio(1);
       fi32x8 bq0 = ldb(0), bq1 = ldb(1);
 #pragma unroll
       for (int m = 0; m < kFIRB; ++m) onehot_sparse(s3n[m], shA, oA, oB, av[m], ap[m]);
       load_s3(Sc, min(kg + 1, ng - 1), s3n);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(0);
 #pragma unroll
       for (int f = 0; f < 6; ++f) {
         fi32x8 bq2 = bq1;
@@ -308,11 +313,8 @@ __device__ inline void fwd_i8_item(const BatchArgs& bt, const EvalArgs* ea, cons
         bq0 = bq1;
         bq1 = bq2;
       }
-      // issue order: the first two B operands, the one-hot operands and the next
-      // symbols, then each pair of products followed by the reads of the B
-      // operand two ahead
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, 80, 0);
+      // issue order after the one-hot operands and the next symbols: each pair of
+      // products followed by the reads of the B operand two ahead
 #pragma unroll
       for (int f = 0; f < 6; ++f) {
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
