@@ -79,14 +79,14 @@ __device__ inline uint4 onehot8_x2(uint2 s8, uint32_t kk) {
 
 constexpr double kOneHotUnscale = 0.5;  // the one-hot value is 2
 
-// One backward work item: site r x column block cb.  Bf: B fragments of the
-// residual pieces, [buffer][piece][step][half][column][8 sequences]; sig:
-// symbols of the block's columns, [buffer][column][sequence].
+// One backward work item: site r x column block cb.  Bf0, Bf1: B fragments of the
+// residual pieces, two buffers of [piece][step][half][column][8 sequences]; sig0,
+// sig1: symbols of the block's columns, [column][sequence].
 // F16: FP16 hi/lo pieces of R * 2^12 (v_mfma_f32_32x32x16_f16) instead of
 // BF16 pieces (v_mfma_f32_32x32x16_bf16).
 template <int NP, bool F16>
-__device__ inline void bwd_mfma_item(const EvalArgs& a, int r, int cb, uint16_t (*Bf)[NP * kBfPiece],
-                                     uint8_t (*sig)[kMPosMax * kSigPitch]) {
+__device__ inline void bwd_mfma_item(const EvalArgs& a, int r, int cb, uint16_t* Bf0, uint16_t* Bf1, uint8_t* sig0,
+                                     uint8_t* sig1) {
   const int npos_blk = mfma_block_positions(a.q);
   const int q = a.q, N = a.N, qq = q * q;
   const int i0 = cb * npos_blk;
@@ -108,8 +108,10 @@ __device__ inline void bwd_mfma_item(const EvalArgs& a, int r, int cb, uint16_t 
   }
   const bool wave_live = wid * kMRB * 32 < nrows;
 
-  for (int e = tid; e < 2 * NP * kBfPiece / 8; e += kMThreads)
-    reinterpret_cast<uint4*>(&Bf[0][0])[e] = make_uint4(0, 0, 0, 0);
+  for (int e = tid; e < NP * kBfPiece / 8; e += kMThreads) {
+    reinterpret_cast<uint4*>(Bf0)[e] = make_uint4(0, 0, 0, 0);
+    reinterpret_cast<uint4*>(Bf1)[e] = make_uint4(0, 0, 0, 0);
+  }
 
   const auto Rr = gmem(a.R + (size_t)r * a.B3 * kSlot);
   const int nchunks = (a.B3 + kMChunk - 1) / kMChunk;
@@ -136,6 +138,8 @@ __device__ inline void bwd_mfma_item(const EvalArgs& a, int r, int cb, uint16_t 
     }
   };
   auto store = [&](int buf) {
+    uint16_t* Bf = buf ? Bf1 : Bf0;
+    uint8_t* sig = buf ? sig1 : sig0;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int u = tid + k * kMThreads;
@@ -167,12 +171,12 @@ __device__ inline void bwd_mfma_item(const EvalArgs& a, int r, int cb, uint16_t 
         }
 #pragma unroll
         for (int p = 0; p < NP; ++p)
-          *reinterpret_cast<uint4*>(&Bf[buf][p * kBfPiece + (g * 32 + s) * 8]) =
+          *reinterpret_cast<uint4*>(&Bf[p * kBfPiece + (g * 32 + s) * 8]) =
               make_uint4(hw[p][0], hw[p][1], hw[p][2], hw[p][3]);
       }
       const int e = tid + k * kMThreads;
       if (e < nsig)
-        *reinterpret_cast<uint4*>(&sig[buf][(e >> 4) * kSigPitch + (e & 15) * 16]) = sv[k];
+        *reinterpret_cast<uint4*>(&sig[(e >> 4) * kSigPitch + (e & 15) * 16]) = sv[k];
     }
   };
 
@@ -194,8 +198,8 @@ __device__ inline void bwd_mfma_item(const EvalArgs& a, int r, int cb, uint16_t 
   for (int c = 0; c < nchunks; ++c) {
     const int buf = c & 1;
     if (wave_live) {
-      const uint16_t* bfb = &Bf[buf][((half * 32) + l32) * 8];
-      const uint8_t* sgb = &sig[buf][half * 8];
+      const uint16_t* bfb = (buf ? Bf1 : Bf0) + ((half * 32) + l32) * 8;
+      const uint8_t* sgb = (buf ? sig1 : sig0) + half * 8;
 #pragma unroll 2
       for (int t = 0; t < kMSteps; ++t) {
         uint4 bp[NP];
@@ -468,7 +472,7 @@ __global__ __launch_bounds__(kMThreads) void bwd_mfma_kernel(BatchArgs b) {
     if (t < 0) break;
     const Item it = decode_item(b, KIND_BWD, t);
     const EvalArgs a = load_uniform(b.ev + it.m);
-    bwd_mfma_item<NP, F16>(a, it.r, it.sub, Bf, sig);
+    bwd_mfma_item<NP, F16>(a, it.r, it.sub, Bf[0], Bf[1], sig[0], sig[1]);
     __syncthreads();
   }
 }
@@ -757,7 +761,7 @@ __device__ inline uint4 onehot16_neg(uint4 s16, uint32_t nkk) {
 // ND = 3, LO = false: the residual digits of round(R * 2^22), written to the
 // gradient data part; LO = true (second pass of the precise path): the digits
 // of the remainder, round((R * 2^22 - v) * 2^22), added to it scaled by 2^-44.
-// ND = 4 (path 0): the four digits of round(R * 2^(30 - e)), e = *a.wexp; the
+// ND = 4 (path 0): the four digits of round(R * 2^(30 - e)), e = a.wexp[0]; the
 // sequences are taken in segments of kI8SegChunks chunks, so that the int32 sums
 // are exact for any number of them, and each segment after the first adds its
 // FP64 value to the one stored (exact while the sums stay below 2^53 2^-30,
@@ -1002,12 +1006,35 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
               : 1.0 / (double)(1 << kRiScaleLog2)) * kNeg,
           LO);
   } else {
-    const double unit = ldexp(kNeg, __builtin_amdgcn_readfirstlane(*a.wexp) - kR4ScaleLog2);
+    const double unit = ldexp(kNeg, __builtin_amdgcn_readfirstlane(a.wexp[0]) - kR4ScaleLog2);
     for (int cb = 0; cb < nchunks; cb += kI8SegChunks) {
       cend = min(nchunks, cb + kI8SegChunks);
       accumulate(cb);
       if (wave_live) flush(unit, cb > 0);
     }
+  }
+}
+
+// Path 0 where the weights' range is too wide for the digits (a.wexp[1]): the
+// residuals are FP32 rows, and the three-piece BF16 product takes them.  Its
+// items (a site x a block of columns) are dealt to the digit gradient's, whose
+// number the work tables hold.  Bound as bwd_mfma_kernel<3>: conversion and staging
+// of the pieces.  Whole evaluation with one weight of 1e6 among [0.1, 1] (with
+// digits): N = 40, B = 500 96 (68) us, N = 150, B = 8000 1.31 (0.77) ms, N = 500,
+// B = 50 000 55.7 (36.6) ms.
+constexpr int kWideBf = 3 * kBfPiece * 2;  // bytes of a buffer's fragments; its symbols follow them
+static_assert(kWideBf % 16 == 0 && kWideBf + kMPosMax * kSigPitch <= I8Shape<4>::kBufBytes && kMThreads == kGThreads,
+              "the three-piece product runs in the digit product's block");
+__device__ inline void wide_items(const BatchArgs& bt, const EvalArgs& a, const Item& it, char* L0, char* L1) {
+  const int first = bt.seg[it.m], n = bt.seg[it.m + 1] - first;
+  const int nsub = bt.nsub[KIND_BWD * bt.n_msas + it.m], cols = mfma_block_positions(a.q), per = (a.N + cols - 1) / cols;
+  const int items = (n + kG3Sites - 1) / kG3Sites * nsub;
+  for (int y = (it.first - first) / kG3Sites * nsub + it.sub; y < n * per; y += items) {
+    const int j = y / per;
+    const int r = __builtin_amdgcn_readfirstlane(bt.active[first + j] - bt.site_base[it.m]);
+    bwd_mfma_item<3, false>(a, r, y - j * per, reinterpret_cast<uint16_t*>(L0), reinterpret_cast<uint16_t*>(L1),
+                            reinterpret_cast<uint8_t*>(L0 + kWideBf), reinterpret_cast<uint8_t*>(L1 + kWideBf));
+    __syncthreads();
   }
 }
 
@@ -1027,8 +1054,13 @@ __global__ __launch_bounds__(kGThreads) void bwd_i8_kernel(BatchArgs b) {
     if (t < 0) break;
     const Item it = decode_item(b, KIND_BWD, t);
     const EvalArgs a = load_uniform(b.ev + it.m);
-    if (a.B_pad < kNegSeqMax) i8_item<ND, LO, true>(b, a, it, Rb0, Rb1, sig0, sig1);
-    else i8_item<ND, LO, false>(b, a, it, Rb0, Rb1, sig0, sig1);
+    if (ND == 4 && __builtin_amdgcn_readfirstlane(a.wexp[1])) {
+      wide_items(b, a, it, reinterpret_cast<char*>(Rb0), reinterpret_cast<char*>(Rb1));
+    } else if (a.B_pad < kNegSeqMax) {
+      i8_item<ND, LO, true>(b, a, it, Rb0, Rb1, sig0, sig1);
+    } else {
+      i8_item<ND, LO, false>(b, a, it, Rb0, Rb1, sig0, sig1);
+    }
     __syncthreads();
   }
 }

@@ -94,30 +94,42 @@ __device__ inline void prep_zero(const PrepArgs& a, int blk) {
 }
 
 // Raises bit 2 of *flag for a non-finite weight; wexp (if any) receives the
-// smallest exponent e with every |w_b| <= 2^e (0 for all-zero weights).
+// smallest exponent e with every |w_b| <= 2^e (0 for all-zero weights), and
+// whether a weight that is not zero lies below 2^(e - kR4RangeLog2).
 __device__ inline void prep_weights(const PrepArgs& a) {
-  __shared__ double red[kPrThreads / 64];
-  double mx = 0.0;
+  __shared__ double red[2][kPrThreads / 64];
+  double mx = 0.0, mn = INFINITY;
   bool bad = false;
 #pragma unroll 16
   for (int b = threadIdx.x; b < a.B; b += kPrThreads) {
     const double v = fabs(a.w[b]);
     bad |= !isfinite(v);
     mx = fmax(mx, v);
+    mn = fmin(mn, v > 0.0 ? v : INFINITY);
   }
   if (bad && a.flag) atomicOr(a.flag, 2);
   if (!a.wexp) return;
-  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  for (int o = 32; o > 0; o >>= 1) {
+    mx = fmax(mx, __shfl_xor(mx, o, 64));
+    mn = fmin(mn, __shfl_xor(mn, o, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = mx;
+    red[1][threadIdx.x >> 6] = mn;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int k = 1; k < kPrThreads / 64; ++k) mx = fmax(mx, red[k]);
+    for (int k = 1; k < kPrThreads / 64; ++k) {
+      mx = fmax(mx, red[0][k]);
+      mn = fmin(mn, red[1][k]);
+    }
     int e = 0;
     if (mx > 0.0 && isfinite(mx)) {
       const double m = frexp(mx, &e);  // m in [0.5, 1)
       if (m == 0.5) --e;
     }
-    *a.wexp = e;
+    a.wexp[0] = e;
+    a.wexp[1] = mn < ldexp(1.0, e - kR4RangeLog2);
   }
 }
 

@@ -81,7 +81,8 @@ struct EvalArgs {
   int32_t rfrag;           // R in gradient-fragment order: 1 FP16 hi/lo pieces, 2 int8 digits, 3 two int8 digit
                            // sets (R and its remainder; the second set after N * B_pad/256 chunks), 4 four
                            // int8 digits (see below)
-  const int32_t* wexp;     // path 0: exponent e with every |w_b| <= 2^e (the residual digits' scale)
+  const int32_t* wexp;     // path 0: [0] exponent e with every |w_b| <= 2^e (the residual digits' scale),
+                           // [1] not zero: some weight is too small for the digits (see below)
   // int8 forward (path 6): couplings as fixed-point digits, symbols by position triple
   int8_t* Wq;              // [N][NG][3 digits][2 steps][2 halves][21 states][16] bytes
   int32_t* jexp;           // [N] scale exponent: digits of round(J * 2^jexp); then [N][kJParts] partial maxima
@@ -124,7 +125,15 @@ __device__ inline size_t rifrag_index(int32_t r, int32_t nch, int32_t b, int32_t
 // Path 0 (rfrag = 4): v = round(R_b(s) * 2^(30 - e)) with |R| <= |w_b| <= 2^e,
 // so |v| <= 2^30: 32 bits, as four signed int8 digits, in chunks of 256
 // sequences as above with four digit planes (21504 bytes per chunk and site).
+// The step is the same for every row, so rows of small weight are held more
+// coarsely than FP32 would: an alignment with a weight (not zero) below
+// 2^(e - kR4RangeLog2) has FP32 residual rows (as rfrag = 0) and the three-piece
+// BF16 product instead.  Error of a gradient entry over the weights it sums, one
+// row of weight 1 among rows of weight 1 / ratio (900 rows, 30 sites, against 64
+// bits; median / root mean square, in 1e-9): digits 0.9 / 1.4 at ratio 16, 1.2 / 1.9
+// at 32, 1.9 / 2.9 at 64, 6.9 / 11 at 256, 3.6e4 at 1e6; FP32 1.3 / 2.3 to 3.0 throughout.
 constexpr int kR4ScaleLog2 = 30;
+constexpr int kR4RangeLog2 = 5;
 constexpr int kR4ChunkBytes = 4 * kRiDigitBytes;            // 21504
 __device__ inline size_t r4frag_index(int32_t r, int32_t nch, int32_t b, int32_t s) {
   const size_t c = (size_t)r * nch + (b >> 8);

@@ -200,3 +200,48 @@ def test_autograd_kept_residuals_equal_recomputed_ones(plm, monkeypatch):
     # no graph, nothing kept
     with torch.no_grad():
         assert not plm.plm_objective(h, J, msa, w, beff).requires_grad
+
+
+# path 0 holds every row's residuals to its own weight, whatever the others weigh: the rule's two sides (a lowest
+# weight of 1/32 and below it), one row that outweighs all others, a large family beside a single row, most rows weightless
+@pytest.mark.parametrize("case,B,N,q", [("lowest32", 300, 13, 21), ("lowest33", 300, 13, 21), ("heavy", 900, 13, 21),
+                                        ("heavy", 500, 40, 21), ("heavy", 700, 5, 3), ("family", 60001, 5, 21),
+                                        ("zeros", 1031, 7, 21), ("tiny", 400, 38, 20)])
+def test_path0_gradient_every_weight(plm, case, B, N, q):
+    from tests.helpers import random_params
+    print(f"path 0 gradient weights {case} B={B} N={N} q={q}", flush=True)
+    rng = np.random.default_rng(B + N)
+    msa = rng.integers(0, q, size=(B, N), dtype=np.uint8)
+    w = rng.uniform(0.1, 1.0, size=B)
+    if case.startswith("lowest"):
+        w[:] = 1.0 / float(case[6:])
+        w[3] = 1.0
+    elif case == "heavy":
+        w[B // 2] = 1e6
+    elif case == "family":
+        msa[1:] = msa[1]
+        w[0], w[1:] = 1.0, 1.0 / (B - 1)
+    elif case == "zeros":
+        w[rng.uniform(size=B) < 0.9] = 0.0
+        w[5] = 3e4
+    else:
+        w *= 1e-20
+        w[7] = 1.0
+    beff = float(w.sum())
+    h, J = random_params(B + N, N, q, 0.3, 0.2)
+    h, J = h.astype(np.float32), J.astype(np.float32)
+    f, gh, gJ = plm.objgrad(_to(msa), _to(w), _to(np.array([beff])), _to(h), _to(J), lambda_h=0.0, lambda_J=0.0, path=0)
+    plm.sync(DEV)
+    fo, gho, gJo = oracle.objgrad(msa, w, beff, h.astype(np.float64), J.astype(np.float64), lambda_h=0.0, lambda_J=0.0)
+    assert np.max(np.abs(f.cpu().numpy() - fo)) <= 1e-5 * max(1.0, np.max(np.abs(fo)))
+    # A row's residual over its weight: energies of N terms are off by at most N big 2^-25 (big: the largest sum), a
+    # probability by at most half of that (P (1 - P) <= 1/4, either sign), and the softmax rounds some 16 times; an entry
+    # adds its rows in FP32 by runs of 256 (at most 64 sums each) and is rounded once.  So it is held to this times the
+    # weights it adds.
+    big = N * float(np.abs(J).max()) + float(np.abs(h).max())
+    tol = (N * big / 4.0 + 16 + 64) * 2.0 ** -24
+    W = np.zeros((N, q))
+    for i in range(N):
+        W[i] = np.bincount(msa[:, i], weights=w, minlength=q)[:q]
+    err = np.abs(gJ.cpu().numpy().astype(np.float64) - gJo)
+    assert np.all(err <= tol * W[None, :, :, None] + 1e-37)
