@@ -71,11 +71,11 @@ extern "C" {
 #define PLM_PATH_GATHER_FP32 0 /* energies by LDS gather, FP32 arithmetic; coupling gradient as an
                                   int8 MFMA product with the FP32 residuals in 32-bit fixed point,
                                   round(R * 2^(30 - e)) with max |w_b| <= 2^e, as four signed int8
-                                  digits, accumulated exactly (|dR_b| <= 2^-31 2^e).  That holds for
-                                  weights whose smallest (zeros aside) is at least 2^(e - 5), so that
-                                  |dR_b| <= 2^-26 |w_b|; for others the gradient is that of path 2
-                                  (FP32 residuals as three BF16 pieces): every row keeps the FP32
-                                  precision of its own weight */
+                                  digits, accumulated exactly over each 2^23 sequences
+                                  (|dR_b| <= 2^-31 2^e).  That holds for weights whose smallest
+                                  (zeros aside) is at least 2^(e - 5), so that |dR_b| <= 2^-26 |w_b|;
+                                  for others the gradient is that of path 2 (FP32 residuals as three
+                                  BF16 pieces): every row keeps the FP32 precision of its own weight */
 #define PLM_PATH_MFMA_BF16X2 1 /* both directions as MFMA products with hi/lo (two-piece)
                                   operands: 16 significant bits, relative error <= 2^-16 per
                                   coupling and residual (precision/speed trade-off) */

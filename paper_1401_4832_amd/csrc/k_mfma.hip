@@ -762,10 +762,9 @@ __device__ inline uint4 onehot16_neg(uint4 s16, uint32_t nkk) {
 // gradient data part; LO = true (second pass of the precise path): the digits
 // of the remainder, round((R * 2^22 - v) * 2^22), added to it scaled by 2^-44.
 // ND = 4 (path 0): the four digits of round(R * 2^(30 - e)), e = a.wexp[0]; the
-// sequences are taken in segments of kI8SegChunks chunks, so that the int32 sums
-// are exact for any number of them, and each segment after the first adds its
-// FP64 value to the one stored (exact while the sums stay below 2^53 2^-30,
-// 2^23 sequences).  Bound: the int8 product, four digit planes against three
+// sequences are taken in segments of kI8SegChunks chunks, whose int32 sums and
+// their combination in FP64 are exact, and each segment after the first adds its
+// value to the one stored (one FP64 rounding).  Bound: the int8 product, four digit planes against three
 // (10.9 ms at the products' measured rate for N = 500, B = 50 000), and LDS,
 // one B fragment per product; it took the place of a scatter of FP32 residuals
 // in symbol order through LDS, 85 -> 16 ms there, 1776 -> 347 us at N = 150,
@@ -775,7 +774,7 @@ __device__ inline uint4 onehot16_neg(uint4 s16, uint32_t nkk) {
 // first's values, took 16 ms, 433 us and 48 us.
 // NEG: the one-hot operand holds -128 for a one (alignments of fewer than
 // kNegSeqMax padded sequences), and the epilogue divides it out exactly.
-constexpr int kI8SegChunks = (1 << 16) - 1;
+constexpr int kI8SegChunks = 1 << 15;  // 2^23 sequences: values up to 2^30 sum to at most 2^53
 template <int ND, bool LO, bool NEG>
 __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Item& it, int8_t* Rb0, int8_t* Rb1,
                                uint8_t* sig0, uint8_t* sig1) {

@@ -245,3 +245,52 @@ def test_path0_gradient_every_weight(plm, case, B, N, q):
         W[i] = np.bincount(msa[:, i], weights=w, minlength=q)[:q]
     err = np.abs(gJ.cpu().numpy().astype(np.float64) - gJo)
     assert np.all(err <= tol * W[None, :, :, None] + 1e-37)
+
+
+def test_path0_gradient_either_side_of_2e17_sequences(plm):
+    """The digit product's one-hot operand is -128 for fewer than 2^17 padded sequences and +1 from there on: one more
+    row, of weight zero, takes the alignment across and leaves every digit sum as it was."""
+    B, N, q = 42 * 3072, 5, 21
+    print(f"path 0 gradient B={B}/{B + 1}", flush=True)
+    rng = np.random.default_rng(17)
+    msa = rng.integers(0, q, size=(B + 1, N), dtype=np.uint8)
+    w = rng.uniform(0.2, 1.0, size=B + 1)
+    w[B] = 0.0
+    beff = float(w.sum())
+    h = (0.3 * rng.standard_normal((N, q))).astype(np.float32)
+    J = (0.2 * rng.standard_normal((N, N, q, q))).astype(np.float32)
+    out = [plm.objgrad(_to(msa[:n]), _to(w[:n]), _to(np.array([beff])), _to(h), _to(J), path=0) for n in (B, B + 1)]
+    plm.sync(DEV)
+    assert torch.equal(out[0][2], out[1][2])
+    fo, gho, gJo = oracle.objgrad(msa, w, beff, h.astype(np.float64), J.astype(np.float64))
+    # the bounds the FP32 paths are held to
+    assert np.max(np.abs(out[1][0].cpu().numpy() - fo)) <= 1e-5 * np.max(np.abs(fo))
+    assert np.max(np.abs(out[1][2].cpu().numpy() - gJo)) <= 2e-6 * beff
+
+
+@pytest.mark.parametrize("wide", [False, True])
+def test_path0_gradient_second_segment(plm, wide):
+    """More than 2^23 sequences: the digit product takes them in two segments, the second added to the first."""
+    B, N, q = (1 << 23) + 70001, 2, 3
+    print(f"path 0 gradient B={B} wide={wide}", flush=True)
+    rng = np.random.default_rng(23)
+    msa = rng.integers(0, q, size=(B, N), dtype=np.uint8)
+    w = rng.uniform(0.25, 1.0, size=B)
+    if wide:
+        w[7] = 100.0
+    beff = float(w.sum())
+    h = (0.3 * rng.standard_normal((N, q))).astype(np.float32)
+    J = (0.2 * rng.standard_normal((N, N, q, q))).astype(np.float32)
+    f, gh, gJ = plm.objgrad(_to(msa), _to(w), _to(np.array([beff])), _to(h), _to(J), lambda_h=0.0, lambda_J=0.0, path=0)
+    plm.sync(DEV)
+    fo, gho, gJo = oracle.objgrad(msa, w, beff, h.astype(np.float64), J.astype(np.float64), lambda_h=0.0, lambda_J=0.0)
+    assert np.max(np.abs(f.cpu().numpy() - fo)) <= 1e-5 * np.max(np.abs(fo))
+    # per row as in test_path0_gradient_every_weight: energies below 2, the softmax, runs of 256 rows in FP32
+    tol = (2 * 2.0 / 4.0 + 16 + 64) * 2.0 ** -24
+    W = np.stack([np.bincount(msa[:, i], weights=w, minlength=q) for i in range(N)])
+    err = np.abs(gJ.cpu().numpy().astype(np.float64) - gJo)
+    assert np.all(err <= tol * W[None, :, :, None])
+    # (the second segment alone moves the entries by more than ten times that)
+    fs, _, gs = oracle.objgrad(msa[1 << 23:], w[1 << 23:], 1.0, h.astype(np.float64), J.astype(np.float64),
+                               lambda_h=0.0, lambda_J=0.0)
+    assert np.max(np.abs(gs)) > 10 * tol * W.max()
