@@ -169,6 +169,23 @@ int plm_objgrad_finish(plm_ctx *ctx, int32_t B, int32_t N, int32_t q, const doub
                        double lambda_J, int32_t path, void *workspace, size_t workspace_bytes,
                        const double *grad_scale, float *gh_out, float *gJ_out);
 
+/* The halves for callers that hold many evaluations between them: what the
+ * second half reads (the residuals above all) goes to `kept`,
+ * plm_objgrad_kept_bytes large and 256-byte aligned, which plm_objgrad_finish_kept
+ * does not write.  The workspace, of plm_objgrad_workspace_bytes less
+ * plm_objgrad_kept_bytes, may be another one in each half. */
+size_t plm_objgrad_kept_bytes(int32_t B, int32_t N, int32_t q, int32_t path);
+int plm_objgrad_begin_kept(plm_ctx *ctx, const uint8_t *msa, int32_t B, int32_t N, int32_t q,
+                           const double *w, const double *beff, const float *h, const float *J,
+                           double lambda_h, double lambda_J, int32_t path, void *kept,
+                           size_t kept_bytes, void *workspace, size_t workspace_bytes,
+                           double *f_out);
+int plm_objgrad_finish_kept(plm_ctx *ctx, int32_t B, int32_t N, int32_t q, const double *w,
+                            const double *beff, const float *h, const float *J, double lambda_h,
+                            double lambda_J, int32_t path, const void *kept, size_t kept_bytes,
+                            void *workspace, size_t workspace_bytes, const double *grad_scale,
+                            float *gh_out, float *gJ_out);
+
 /* ---- Objective and gradient without a workspace ----------------------------
  * For callers that cannot allocate device memory: code under HIP graph
  * capture, serving loops, harnesses that forbid allocation.  plm_objgrad

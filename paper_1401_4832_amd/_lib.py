@@ -155,6 +155,9 @@ def lib():
                                            P, P, P, P]),
             "plm_objgrad_begin": (ctypes.c_int, [P, P, I32, I32, I32, P, P, P, P, D, D, I32, P, SZ, P]),
             "plm_objgrad_finish": (ctypes.c_int, [P, I32, I32, I32, P, P, P, P, D, D, I32, P, SZ, P, P, P]),
+            "plm_objgrad_kept_bytes": (SZ, [I32, I32, I32, I32]),
+            "plm_objgrad_begin_kept": (ctypes.c_int, [P, P, I32, I32, I32, P, P, P, P, D, D, I32, P, SZ, P, SZ, P]),
+            "plm_objgrad_finish_kept": (ctypes.c_int, [P, I32, I32, I32, P, P, P, P, D, D, I32, P, SZ, P, SZ, P, P, P]),
             "plm_objgrad_static": (ctypes.c_int, [P, P, I32, I32, I32, P, P, P, P, D, D, P, I32, I32, P, P, P, P]),
             "plm_fit_opts_default": (None, [ctypes.POINTER(FitOpts)]),
             "plm_fit_opts_size": (SZ, []),
@@ -195,6 +198,7 @@ def exported_symbols():
     return ["plm_ctx_create", "plm_ctx_destroy", "plm_last_error", "plm_status_string", "plm_sync",
             "plm_reweight", "plm_objgrad_workspace_bytes", "plm_objgrad", "plm_fit_opts_default",
             "plm_fit_opts_size", "plm_objgrad_static", "plm_objgrad_begin", "plm_objgrad_finish",
+            "plm_objgrad_kept_bytes", "plm_objgrad_begin_kept", "plm_objgrad_finish_kept",
             "plm_fit_workspace_bytes", "plm_fit", "plm_score", "plm_fit_last_timing",
             "plm_fit_batch_workspace_bytes", "plm_fit_batch", "plm_tune", "plm_score_opts_default",
             "plm_frequencies", "plm_score_ex", "plm_contact_tpr", "plm_parse_alignment",

@@ -137,32 +137,37 @@ def _objgrad_inputs(msa, w, beff, h, J):
 
 
 def objgrad_begin(msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_GATHER_FP32):
-    """(f, workspace): the objectives of all sites, and the workspace that holds
-    their residuals for objgrad_finish()."""
+    """(f, kept): the objectives of all sites, and what objgrad_finish() needs of
+    their evaluation (the residuals above all)."""
     dev, B, N, q = _objgrad_inputs(msa, w, beff, h, J)
     f = torch.empty(N, dtype=torch.float64, device=dev)
-    ws = workspace(L.lib().plm_objgrad_workspace_bytes(B, N, q, path), dev)
+    nkept = L.lib().plm_objgrad_kept_bytes(B, N, q, path)
+    kept = workspace(nkept, dev)
+    ws = workspace(L.lib().plm_objgrad_workspace_bytes(B, N, q, path) - nkept, dev)
     ctx = context(dev)
-    _check(L.lib().plm_objgrad_begin(ctx, _ptr(msa), B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J),
-                                     float(lambda_h), float(lambda_J), path, _ptr(ws), ws.numel(), _ptr(f)), ctx)
-    return f, ws
+    _check(L.lib().plm_objgrad_begin_kept(ctx, _ptr(msa), B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J),
+                                          float(lambda_h), float(lambda_J), path, _ptr(kept), kept.numel(),
+                                          _ptr(ws), ws.numel(), _ptr(f)), ctx)
+    return f, kept
 
 
-def objgrad_finish(ws, msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_GATHER_FP32, grad_scale=None):
+def objgrad_finish(kept, msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_GATHER_FP32, grad_scale=None):
     """(gh, gJ) of the evaluation that objgrad_begin(), with the same arguments,
-    left in ws (or in a copy of it)."""
+    left in kept (or in a copy of it); kept is not written."""
     dev, B, N, q = _objgrad_inputs(msa, w, beff, h, J)
-    _dev_tensor(ws, torch.uint8, dev, "ws")
+    _dev_tensor(kept, torch.uint8, dev, "kept")
     if grad_scale is not None:
         _dev_tensor(grad_scale, torch.float64, dev, "grad_scale")
         if grad_scale.numel() != N:
             raise ValueError("grad_scale must have N entries")
     gh = torch.empty(N, q, dtype=torch.float32, device=dev)
     gJ = torch.empty(N, N, q, q, dtype=torch.float32, device=dev)
+    ws = workspace(L.lib().plm_objgrad_workspace_bytes(B, N, q, path) -
+                   L.lib().plm_objgrad_kept_bytes(B, N, q, path), dev)
     ctx = context(dev)
-    _check(L.lib().plm_objgrad_finish(ctx, B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J), float(lambda_h),
-                                      float(lambda_J), path, _ptr(ws), ws.numel(), _ptr(grad_scale), _ptr(gh),
-                                      _ptr(gJ)), ctx)
+    _check(L.lib().plm_objgrad_finish_kept(ctx, B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J), float(lambda_h),
+                                           float(lambda_J), path, _ptr(kept), kept.numel(), _ptr(ws), ws.numel(),
+                                           _ptr(grad_scale), _ptr(gh), _ptr(gJ)), ctx)
     return gh, gJ
 
 

@@ -105,8 +105,10 @@ struct EvalBufs {
 constexpr int32_t kWsRows = 192;
 
 // wide: room for the precise path's two residual digit sets (126 bytes per
-// site and row instead of 21 floats)
-void layout_eval(Bump& bp, int32_t B, int32_t N, int32_t q, EvalBufs& e, bool wide = false) {
+// site and row instead of 21 floats).  kept: where what a gradient reads of its
+// forward goes (null: among the rest).
+void layout_eval(Bump& bp, int32_t B, int32_t N, int32_t q, EvalBufs& e, bool wide = false, Bump* kept = nullptr) {
+  Bump& kp = kept ? *kept : bp;
   e.B_pad = (int32_t)rup(B, kBPadUnit);
   e.N_pad = (int32_t)rup(N, kFwdChunk);
   e.B3 = (int32_t)rup(B, 3);
@@ -114,17 +116,17 @@ void layout_eval(Bump& bp, int32_t B, int32_t N, int32_t q, EvalBufs& e, bool wi
   const int32_t tmin = std::min(forward_tile_seqs(16), fwd_i8_tile_seqs());
   e.tiles_max = (B + tmin - 1) / tmin;
   e.msa_cm = bp.take<uint8_t>((size_t)e.B_pad * e.N_pad);
-  e.msaT = bp.take<uint8_t>((size_t)e.B_pad * e.N_pad);
+  e.msaT = kp.take<uint8_t>((size_t)e.B_pad * e.N_pad);
   // FP32 rows [B3][21], or the fragment-order FP16 pieces over B_pad rows
-  e.R = bp.take<float>((size_t)N * e.B_pad * (wide ? 32 : kSlot));
-  e.f_part = bp.take<double>((size_t)e.tiles_max * N);
-  e.gh_part = bp.take<double>((size_t)e.tiles_max * N * kSlot);
+  e.R = kp.take<float>((size_t)N * e.B_pad * (wide ? 32 : kSlot));
+  e.f_part = kp.take<double>((size_t)e.tiles_max * N);
+  e.gh_part = kp.take<double>((size_t)e.tiles_max * N * kSlot);
   e.gJ = bp.take<double>((size_t)N * N * q * q);
   // unused bytes: the size of a workspace is what callers have been told before
   bp.take<uint16_t>((size_t)((e.B3 + kWsRows - 1) / kWsRows) * N * kWsRows);
   e.NG = (N + 2) / 3;
   e.Wq = bp.take<int8_t>((size_t)N * e.NG * kWqGroupBytes);
-  e.jexp = bp.take<int32_t>((size_t)N * (1 + kJParts));
+  e.jexp = kp.take<int32_t>((size_t)N * (1 + kJParts));
   e.sym3 = bp.take<uint32_t>((size_t)e.NG * e.B_pad);
 }
 
@@ -534,6 +536,14 @@ int plm_reweight(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
   return PLM_OK;
 }
 
+size_t plm_objgrad_kept_bytes(int32_t B, int32_t N, int32_t q, int32_t path) {
+  if (B < 1 || N < 2 || q < 2 || q > kQMax) return 0;
+  Bump bp{nullptr, 0}, kp{nullptr, 0};
+  EvalBufs e;
+  layout_eval(bp, B, N, q, e, path == PLM_PATH_GATHER64_MFMA_I8X6, &kp);
+  return rup(kp.off, 256);
+}
+
 size_t plm_objgrad_workspace_bytes(int32_t B, int32_t N, int32_t q, int32_t path) {
   if (B < 1 || N < 2 || q < 2 || q > kQMax) return 0;
   Bump bp{nullptr, 0};
@@ -549,14 +559,14 @@ size_t plm_objgrad_workspace_bytes(int32_t B, int32_t N, int32_t q, int32_t path
 namespace {
 
 // plm_objgrad on the given scratch (a caller's workspace or the static array),
-// whole, or its two halves: EV_BEGIN leaves in the scratch everything the
-// gradient needs, EV_FINISH takes it up there.
+// whole, or its two halves: EV_BEGIN leaves in the scratch (or in kept, if that
+// is given) everything the gradient needs, EV_FINISH takes it up there.
 enum { EV_WHOLE = 0, EV_BEGIN = 1, EV_FINISH = 2 };
 int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q, const double* w,
                  const double* beff, const float* h, const float* J, double lambda_h,
                  double lambda_J, const int32_t* sites, int32_t n_sites, int32_t path, void* ws,
                  size_t ws_bytes, const double* grad_scale, double* f_out, float* gh_out,
-                 float* gJ_out, int stage = EV_WHOLE) {
+                 float* gJ_out, int stage = EV_WHOLE, void* kept = nullptr, size_t kept_bytes = 0) {
   if (!w || !beff || !h || !J) return set_err(c, PLM_E_INVALID, "null pointer");
   if (stage == EV_FINISH ? !gh_out || !gJ_out : !msa || !f_out) return set_err(c, PLM_E_INVALID, "null pointer");
   int rc = check_sizes(c, B, N, q);
@@ -568,13 +578,15 @@ int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
   if (!path_fits(ps, B)) return set_err(c, PLM_E_UNSUPPORTED, "path %d sums at most 2^24 - 1 sequences exactly", path);
   if (!sites) n_sites = N;
   if (n_sites < 1 || n_sites > N) return set_err(c, PLM_E_INVALID, "n_sites out of range");
-  const size_t need = plm_objgrad_workspace_bytes(B, N, q, path);
-  rc = check_ws(c, ws, ws_bytes, need);
+  const size_t kneed = kept ? plm_objgrad_kept_bytes(B, N, q, path) : 0;
+  rc = check_ws(c, kept, kept_bytes, kneed);
+  if (rc) return rc;
+  rc = check_ws(c, ws, ws_bytes, plm_objgrad_workspace_bytes(B, N, q, path) - kneed);
   if (rc) return rc;
   HIPCHK(c, hipSetDevice(c->device));
-  Bump bp{(char*)ws, 0};
+  Bump bp{(char*)ws, 0}, kp{(char*)kept, 0};
   EvalBufs e;
-  layout_eval(bp, B, N, q, e, path == PLM_PATH_GATHER64_MFMA_I8X6);
+  layout_eval(bp, B, N, q, e, path == PLM_PATH_GATHER64_MFMA_I8X6, kept ? &kp : nullptr);
   Tables t;
   layout_tables(bp, 1, N, false, t);
   const BatchArgs b = batch_args(t, 1, N, bwd_group(ps), fwd_group(ps));
@@ -633,6 +645,25 @@ int plm_objgrad_finish(plm_ctx* c, int32_t B, int32_t N, int32_t q, const double
   if (!c) return PLM_E_INVALID;
   return objgrad_impl(c, nullptr, B, N, q, w, beff, h, J, lambda_h, lambda_J, nullptr, N, path, ws, ws_bytes,
                       grad_scale, nullptr, gh_out, gJ_out, EV_FINISH);
+}
+
+int plm_objgrad_begin_kept(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q, const double* w,
+                           const double* beff, const float* h, const float* J, double lambda_h, double lambda_J,
+                           int32_t path, void* kept, size_t kept_bytes, void* ws, size_t ws_bytes, double* f_out) {
+  if (!c) return PLM_E_INVALID;
+  if (!kept) return set_err(c, PLM_E_INVALID, "null pointer");
+  return objgrad_impl(c, msa, B, N, q, w, beff, h, J, lambda_h, lambda_J, nullptr, N, path, ws, ws_bytes, nullptr,
+                      f_out, nullptr, nullptr, EV_BEGIN, kept, kept_bytes);
+}
+
+int plm_objgrad_finish_kept(plm_ctx* c, int32_t B, int32_t N, int32_t q, const double* w, const double* beff,
+                            const float* h, const float* J, double lambda_h, double lambda_J, int32_t path,
+                            const void* kept, size_t kept_bytes, void* ws, size_t ws_bytes, const double* grad_scale,
+                            float* gh_out, float* gJ_out) {
+  if (!c) return PLM_E_INVALID;
+  if (!kept) return set_err(c, PLM_E_INVALID, "null pointer");
+  return objgrad_impl(c, nullptr, B, N, q, w, beff, h, J, lambda_h, lambda_J, nullptr, N, path, ws, ws_bytes,
+                      grad_scale, nullptr, gh_out, gJ_out, EV_FINISH, const_cast<void*>(kept), kept_bytes);
 }
 
 int plm_objgrad_static(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q,

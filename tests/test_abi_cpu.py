@@ -76,3 +76,16 @@ def test_fit_options_layout_matches_the_library(lib):
     o = _lib.FitOpts()
     lib.plm_fit_opts_default(ctypes.byref(o))
     assert o.refine_tol == 0.0 and o.n_probe == 0 and o.history_fp64 == 0 and not o.probe_out
+
+
+def test_kept_part_of_a_workspace(lib):
+    """What the gradient's half reads is a part of the whole workspace: the residuals and little more."""
+    for B, N, q in ((500, 40, 21), (8000, 150, 21), (50000, 500, 21), (1, 2, 2)):
+        for path in range(8):
+            whole, kept = lib.plm_objgrad_workspace_bytes(B, N, q, path), lib.plm_objgrad_kept_bytes(B, N, q, path)
+            assert kept % 256 == 0 and 0 < kept < whole
+            rows = (B + 3071) // 3072 * 3072
+            per_row = 128 if path == 7 else 84
+            # symbols once, the tiles' partial sums and the scales beside the residuals
+            assert kept <= rows * N * per_row + rows * (N + 15) + (B // 384 + 1) * N * 22 * 8 + N * 68 + 8 * 256
+    assert lib.plm_objgrad_kept_bytes(500, 40, 22, 0) == 0

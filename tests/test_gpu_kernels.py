@@ -294,3 +294,85 @@ def test_path0_gradient_second_segment(plm, wide):
     fs, _, gs = oracle.objgrad(msa[1 << 23:], w[1 << 23:], 1.0, h.astype(np.float64), J.astype(np.float64),
                                lambda_h=0.0, lambda_J=0.0)
     assert np.max(np.abs(gs)) > 10 * tol * W.max()
+
+
+def test_autograd_graphs_hold_a_bounded_total(plm, monkeypatch):
+    """Any number of graphs alive together keep at most KEEP_BYTES; the others evaluate again, with the same bits; what
+    is kept is given back by the backward, by hooks that store it elsewhere and by a dropped graph."""
+    from paper_1401_4832_amd import _lib, autograd
+    print("autograd bounded total", flush=True)
+    msa, w, beff, h, J, sc = _autograd_case(plm, B=30000, N=20)
+    h.requires_grad_(True)
+    J.requires_grad_(True)
+    one = _lib.lib().plm_objgrad_kept_bytes(30000, 20, 21, 0)
+    assert one >= 84 * 30000 * 20
+    monkeypatch.setattr(autograd, "KEEP_BYTES", 2 * one + one // 2)
+
+    def held():
+        return sum(n for _, n in autograd._live.values())
+    assert held() == 0
+    plm.plm_objective(h, J, msa, w, beff)  # (the allocator's first blocks)
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated(DEV)
+    fs = [plm.plm_objective(h, J, msa, w, beff) for _ in range(6)]
+    assert held() == 2 * one
+    # the objectives of twenty sites and the kept residuals are all that is alive
+    assert torch.cuda.memory_allocated(DEV) - before <= autograd.KEEP_BYTES + 6 * 4096
+    grads = [torch.autograd.grad((f * sc).sum(), (h, J)) for f in fs]
+    for g in grads[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(grads[0], g))
+    assert held() == 0
+    f = plm.plm_objective(h, J, msa, w, beff)
+    assert held() == one
+    del f
+    assert held() == 0
+    with torch.no_grad():
+        plm.plm_objective(h, J, msa, w, beff)
+    assert held() == 0
+    with torch.autograd.graph.save_on_cpu():
+        f = plm.plm_objective(h, J, msa, w, beff)
+    assert held() == 0
+    g = torch.autograd.grad((f * sc).sum(), (h, J))
+    assert all(torch.equal(a, b) for a, b in zip(grads[0], g))
+    msa[0, 0] = 250  # the evaluation's own errors are reported as before, and leave nothing reserved
+    f = plm.plm_objective(h, J, msa, w, beff)
+    with pytest.raises(plm.PlmError):
+        plm.sync(DEV)
+    with pytest.raises(ValueError):
+        plm.plm_objective(h, J, msa, w[1:], beff)
+    del f
+    assert held() == 0
+
+
+@pytest.mark.parametrize("path", [0, 6, 7])
+def test_objgrad_halves_c_entries(plm, path):
+    """The C halves with the residuals in the workspace, and with them apart: same bits as the whole; `kept` is not
+    written by the second half, and sizes and null pointers are checked."""
+    import ctypes
+    from paper_1401_4832_amd import _lib, api
+    print(f"objgrad halves C path={path}", flush=True)
+    L = _lib.lib()
+    msa, w, beff, h, J, sc = _autograd_case(plm, B=1031)
+    B, N, q = 1031, 13, 21
+    f, gh, gJ = plm.objgrad(msa, w, beff, h, J, path=path, grad_scale=sc)
+    full, part = L.plm_objgrad_workspace_bytes(B, N, q, path), L.plm_objgrad_kept_bytes(B, N, q, path)
+    ws, kept, ws2 = (api.workspace(n, DEV) for n in (full, part, full - part))
+    ctx, p = api.context(DEV), (lambda t: ctypes.c_void_p(t.data_ptr()))
+    inp = (B, N, q, p(w), p(beff), p(h), p(J), 0.01, 0.01, path)
+    out = [(torch.empty_like(f), torch.empty_like(gh), torch.empty_like(gJ)) for _ in range(2)]
+    (f1, gh1, gJ1), (f2, gh2, gJ2) = out
+    assert L.plm_objgrad_begin(ctx, p(msa), *inp, p(ws), full, p(f1)) == 0
+    assert L.plm_objgrad_finish(ctx, *inp, p(ws), full, p(sc), p(gh1), p(gJ1)) == 0
+    assert L.plm_objgrad_begin_kept(ctx, p(msa), *inp, p(kept), part, p(ws2), full - part, p(f2)) == 0
+    ws2.fill_(0xff)
+    was = kept.clone()
+    assert L.plm_objgrad_finish_kept(ctx, *inp, p(kept), part, p(ws2), full - part, p(sc), p(gh2), p(gJ2)) == 0
+    plm.sync(DEV)
+    assert torch.equal(kept, was)
+    for o in out:
+        assert all(torch.equal(a, b) for a, b in zip((f, gh, gJ), o))
+    rest = (p(sc), p(gh2), p(gJ2))
+    assert L.plm_objgrad_finish_kept(ctx, *inp, p(kept), part - 1, p(ws2), full - part, *rest) == -4
+    assert L.plm_objgrad_finish_kept(ctx, *inp, p(kept), part, p(ws2), full - part - 1, *rest) == -4
+    assert L.plm_objgrad_finish_kept(ctx, *inp, None, part, p(ws2), full - part, *rest) == -1
+    assert L.plm_objgrad_begin_kept(ctx, p(msa), *inp, None, part, p(ws2), full - part, p(f2)) == -1
