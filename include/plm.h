@@ -195,7 +195,7 @@ int plm_objgrad_finish_kept(plm_ctx *ctx, int32_t B, int32_t N, int32_t q, const
  * process ends; the call allocates nothing.  Problems whose
  * plm_objgrad_workspace_bytes exceeds the array are rejected with
  * PLM_E_WORKSPACE (at q = 21, 64 MiB holds N = 20 with B up to 33 700,
- * N = 40 with B up to 15 300, N = 60 with B up to 8 000).  Every call on a GPU shares that GPU's
+ * N = 40 with B up to 15 300, N = 60 with B up to 9 200).  Every call on a GPU shares that GPU's
  * array: calls ordered on one stream are safe, calls that overlap on one GPU
  * (other streams or contexts, other threads) race.  The array keeps the last
  * call's contents; an evaluation writes every scratch byte before it reads it,

@@ -20,7 +20,7 @@ from ._lib import lib, PATH_GATHER_FP32
 
 # Most that the graphs alive on a device hold together between forward and
 # backward, so that a sum over any number of families needs no more memory than
-# this on top of one evaluation's.  At N = 150, B = 8000 (119 MB) a pass takes
+# this on top of one evaluation's.  At N = 150, B = 8000 (118 MB) a pass takes
 # 740 us with the residuals kept; evaluating them again would add the forward's
 # 425 us.
 KEEP_BYTES = 1 << 30

@@ -102,8 +102,6 @@ struct EvalBufs {
   int32_t NG;
 };
 
-constexpr int32_t kWsRows = 192;
-
 // wide: room for the precise path's two residual digit sets (126 bytes per
 // site and row instead of 21 floats).  kept: where what a gradient reads of its
 // forward goes (null: among the rest).
@@ -122,8 +120,6 @@ void layout_eval(Bump& bp, int32_t B, int32_t N, int32_t q, EvalBufs& e, bool wi
   e.f_part = kp.take<double>((size_t)e.tiles_max * N);
   e.gh_part = kp.take<double>((size_t)e.tiles_max * N * kSlot);
   e.gJ = bp.take<double>((size_t)N * N * q * q);
-  // unused bytes: the size of a workspace is what callers have been told before
-  bp.take<uint16_t>((size_t)((e.B3 + kWsRows - 1) / kWsRows) * N * kWsRows);
   e.NG = (N + 2) / 3;
   e.Wq = bp.take<int8_t>((size_t)N * e.NG * kWqGroupBytes);
   e.jexp = kp.take<int32_t>((size_t)N * (1 + kJParts));

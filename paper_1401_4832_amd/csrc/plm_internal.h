@@ -374,7 +374,6 @@ struct SymState {
 struct SymCoef {
   double cs[kMMax], cy[kMMax];            // direction coefficients, chronological order
   double p1[kMMax + 1], p2[kMMax + 1];    // s_j . g, y_j . g, newest first
-  double colS[kMMax + 1], colY[kMMax + 1];
   int32_t ord[kMMax];
   int32_t n;
 };
