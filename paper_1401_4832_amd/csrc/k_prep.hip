@@ -16,6 +16,7 @@ constexpr int kPrThreads = 256;
 constexpr int kPrRows = 256;            // rows of a tile: one gradient chunk
 constexpr int kPrCols = 48;             // columns: three chunks of sixteen, sixteen triples
 constexpr int kPrPitch = kPrCols + 4;   // LDS bytes per row: an odd number of words
+static_assert(kPrPitch % 4 == 0 && kFwdChunk % 4 == 0, "rows and chunks are read as words");
 constexpr int kPrZeroBlocks = 64;
 
 // The symbols of one tile, zeros past B and N; symbols >= q become zero and
@@ -137,7 +138,7 @@ __device__ inline void prep_weights(const PrepArgs& a) {
 // zeros (if there are any to write), and one per tile, columns first.
 __global__ __launch_bounds__(kPrThreads) void prep_kernel(PrepArgs a, TableArgs t, int32_t table, int32_t nzero,
                                                           int32_t col_tiles) {
-  __shared__ uint8_t sh[kPrRows * kPrPitch];
+  __shared__ __attribute__((aligned(16))) uint8_t sh[kPrRows * kPrPitch];
   int blk = blockIdx.x;
   if (table) {
     if (blk == 0) {
