@@ -274,15 +274,33 @@ int ensure_pin(plm_ctx* c, size_t words) {
 // N = 40, B = 500 34 / 41 / 42 us; N = 100, B = 3000 135 / 115 / 123 us;
 // N = 120, B = 5000 249 / 225 / 177 us; N = 150, B = 8000 429 / 427 / 399 us;
 // N = 150, B = 16 000 791 / 751 / 780 us; N = 300, B = 20 000 3.55 / 3.33 / 3.16 ms.
-int32_t pick_nb(int32_t N, int32_t B, int32_t ncu, int32_t tile_seqs) {
+// The alignments of a batch share the units, so their items count together,
+// rows + 8 as the mean over them by their columns: objective and gradient
+// (path 0) of sixteen with N = 40, B = 2000 345 / 307 / 306 us (one alone picks
+// 16), of eight with N = 60, B = 1000 225 / 205 / 175 us, of six with N = 100,
+// B = 1500 436 / 420 / 427 us.  A site list counts as all sites: the tile decides
+// the order of the objective's sums, and a listed site's objective has the same
+// bits whichever others are listed (one site of N = 150, B = 8000 takes 155 us
+// that way, 86 with 16 rows).
+struct AlignSize {
+  int32_t N, B;
+};
+int32_t pick_nb(const AlignSize* msas, int32_t n, int32_t ncu, int32_t tile_seqs) {
   if (tile_seqs == 16 || tile_seqs == 32 || tile_seqs == 64) return tile_seqs;
   int32_t best = 16;
-  int64_t cost = 0;
+  double cost = 0.0;
   for (int32_t nb : {64, 32, 16}) {
-    const int32_t t = forward_tile_seqs(nb), tiles = (B + t - 1) / t;
-    const int32_t rows = 2 * (((B + 47) / 48 + tiles - 1) / tiles);
-    const int64_t k = (2 * (((int64_t)N * tiles + ncu - 1) / ncu) + 1) * (rows + 8);
-    if (cost == 0 || k < cost) {
+    const int32_t t = forward_tile_seqs(nb);
+    int64_t items = 0;
+    double work = 0.0;
+    for (int32_t m = 0; m < n; ++m) {
+      const int32_t B = msas[m].B, tiles = (int32_t)(((int64_t)B + t - 1) / t);
+      const int32_t rows = 2 * (((B + 47) / 48 + tiles - 1) / tiles);
+      items += (int64_t)msas[m].N * tiles;
+      work += (double)msas[m].N * tiles * msas[m].N * (rows + 8);
+    }
+    const double k = (double)(2 * ((items + ncu - 1) / ncu) + 1) * (work / (double)items);
+    if (cost == 0.0 || k < cost) {
       cost = k;
       best = nb;
     }
@@ -592,7 +610,8 @@ int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
     HIPCHK(c, launch_check_f32(J, (size_t)N * N * q * q, c->pin_dev, c->stream));
     if (grad_scale) HIPCHK(c, launch_check_f64(grad_scale, (size_t)N, c->pin_dev, c->stream));
   }
-  const int32_t nb = pick_nb(N, B, c->ncu, 0);
+  const AlignSize size{N, B};
+  const int32_t nb = pick_nb(&size, 1, c->ncu, 0);
   const EvalArgs a = eval_args(e, msa, B, N, q, w, h, J, eval_tiles(ps, B, nb), ps);
   TableArgs ta;
   ta.b = b; ta.e = a; ta.sites = sites; ta.n_sites = n_sites;
@@ -811,7 +830,9 @@ int prepare_fit(plm_ctx* c, const plm_msa_desc* d, int32_t n, int32_t q, const p
   hipStream_t st = c->fit_stream;
   c->pin[1] = total;
 
-  const int32_t nb = pick_nb(d[ord[0]].N, d[ord[0]].B, c->ncu, o->tile_seqs);  // for the largest alignment
+  std::vector<AlignSize> sizes(n);
+  for (int32_t k = 0; k < n; ++k) sizes[k] = AlignSize{d[k].N, d[k].B};
+  const int32_t nb = pick_nb(sizes.data(), n, c->ncu, o->tile_seqs);
   std::vector<int32_t> base(n + 1, 0);
   for (int32_t k = 0; k < n; ++k) {
     const plm_msa_desc& m = d[ord[k]];
@@ -1286,7 +1307,8 @@ int run_sym_once(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
     for (int32_t i = r + 1; i < N; ++i) pairs.push_back(make_int2(r, i));
   HIPCHK(c, hipMemcpyAsync(f.pairs, pairs.data(), pairs.size() * sizeof(int2), hipMemcpyHostToDevice, st));
 
-  const int32_t nb = pick_nb(N, B, c->ncu, o->tile_seqs);
+  const AlignSize size{N, B};
+  const int32_t nb = pick_nb(&size, 1, c->ncu, o->tile_seqs);
   const BatchArgs b = batch_args(f.t, 1, N, bwd_group(ps), fwd_group(ps));
   HIPCHK(c, launch_check_f32(h_io, (size_t)N * q, c->pin_dev, st));
   HIPCHK(c, launch_check_f32(J_io, (size_t)N * N * q * q, c->pin_dev, st));

@@ -376,3 +376,16 @@ def test_objgrad_halves_c_entries(plm, path):
     assert L.plm_objgrad_finish_kept(ctx, *inp, p(kept), part, p(ws2), full - part - 1, *rest) == -4
     assert L.plm_objgrad_finish_kept(ctx, *inp, None, part, p(ws2), full - part, *rest) == -1
     assert L.plm_objgrad_begin_kept(ctx, p(msa), *inp, None, part, p(ws2), full - part, p(f2)) == -1
+
+
+@pytest.mark.parametrize("path", [0, 5, 6, 7])
+@pytest.mark.parametrize("B,N", [(5000, 30), (700, 45)])
+def test_listed_sites_have_the_bits_of_all_sites(plm, path, B, N):
+    """A listed site's objective and gradient do not depend on which others are listed."""
+    print(f"site list bits path={path} B={B} N={N}", flush=True)
+    msa, w, beff, h, J, _ = _autograd_case(plm, B=B, N=N)
+    whole = plm.objgrad(msa, w, beff, h, J, path=path)
+    for sites in ([N - 1], [3, 0], list(range(1, N, 2))):
+        part = plm.objgrad(msa, w, beff, h, J, path=path, sites=torch.tensor(sites, dtype=torch.int32, device=DEV))
+        plm.sync(DEV)
+        assert all(torch.equal(a[sites], b[sites]) for a, b in zip(whole, part))
