@@ -205,9 +205,7 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
   // lane 21 g + s takes state s of the rows 16 g .. 16 g + 15 to the field
   // gradient and to HBM, sixteen rows of a digit in one store.
   double facc = 0.0, ghacc = 0.0;
-  // (path 0: FP32 rows where the weights' range is too wide for its digits)
-  const int rfrag = a.rfrag == 4 && __builtin_amdgcn_readfirstlane(a.wexp[1]) ? 0 : a.rfrag;
-  const double rscale = rfrag == 4 ? ldexp(1.0, kR4ScaleLog2 - a.wexp[0]) : (double)(1 << kRiScaleLog2);
+  const double rscale = a.rfrag == 4 ? ldexp(1.0, kR4ScaleLog2 - a.wexp[0]) : (double)(1 << kRiScaleLog2);
   __syncthreads();  // every wave is done with the last chunk
   AT* park = reinterpret_cast<AT*>(lds) + wid * (kParkRows * kSlot);
 #pragma unroll 1
@@ -263,7 +261,7 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
       }
     }
     wave_sync();
-    if (rfrag == 0) {
+    if (a.rfrag == 0) {
       // FP32 rows: the 48 rows are contiguous
       auto Rr = gmem_w(a.R) + ((size_t)r * a.B3 + b0) * kSlot;
       const int n = min(kParkRows, a.B3 - b0) * kSlot;
@@ -275,10 +273,10 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
       const int bg = b0 + 16 * slot;  // sixteen rows from here
       const AT* col = park + 16 * slot * kSlot + s;
       // rows of every tile are written, zeros past B; states past q hold zeros
-      if (rfrag == 0) {
+      if (a.rfrag == 0) {
 #pragma unroll
         for (int t = 0; t < 16; ++t) ghacc += (double)col[t * kSlot];
-      } else if (rfrag == 1) {
+      } else if (a.rfrag == 1) {
         // FP16 hi/lo pieces of R * 2^12 in the grouped gradient's fragment order
         auto Rf = gmem_w(reinterpret_cast<u32x4_t*>(a.R));
 #pragma unroll
@@ -338,7 +336,7 @@ __device__ inline void fwd_item(const EvalArgs& a, int r, int tile, float* lds, 
           for (int d = 0; d < ND; ++d) Ri[(ix + (size_t)d * kRiDigitBytes) / 16] = dw[d];
         };
         constexpr std::integral_constant<int, 3> three;
-        if (rfrag == 4) {
+        if (a.rfrag == 4) {
           put(r4frag_index(r, nch, bg, s), std::integral_constant<int, 4>{}, [&](AT v) {
             ghacc += (double)v;
             return (int)rint((double)v * rscale);
@@ -392,7 +390,9 @@ __global__ __launch_bounds__(kFwdThreads, sizeof(AT) == 4 ? 4 : 2) void fwd_kern
     const int32_t t = __builtin_amdgcn_readfirstlane(item_s);
     if (t < 0) break;
     const Item it = decode_item(b, KIND_FWD, t);
-    const EvalArgs a = load_uniform(b.ev + it.m);
+    EvalArgs a = load_uniform(b.ev + it.m);
+    // path 0: FP32 rows where the weights' range is too wide for its digits
+    if (sizeof(AT) == 4 && a.rfrag == 4 && __builtin_amdgcn_readfirstlane(a.wexp[1])) a.rfrag = 0;
     fwd_item<NB, AT, LO>(a, it.r, it.sub, lds, sgl, red);
     __syncthreads();
   }
