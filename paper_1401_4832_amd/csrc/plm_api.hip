@@ -278,12 +278,11 @@ int ensure_pin(plm_ctx* c, size_t words) {
 // rows + 8 as the mean over them by their columns: objective and gradient
 // (path 0) of sixteen with N = 40, B = 2000 345 / 307 / 306 us (one alone picks
 // 16), of eight with N = 60, B = 1000 225 / 205 / 175 us, of six with N = 100,
-// B = 1500 436 / 420 / 427 us.  A site list counts as all sites: the tile decides
-// the order of the objective's sums, and a listed site's objective has the same
-// bits whichever others are listed (one site of N = 150, B = 8000 takes 155 us
-// that way, 86 with 16 rows).
+// B = 1500 436 / 420 / 427 us.  Of a site list only the listed sites count:
+// objective of one site of N = 150, B = 8000 86 / 115 / 155 us, of 64 sites
+// 251 / 230 / 232 us, of 64 sites of N = 500, B = 50 000 3.20 / 3.03 / 2.92 ms.
 struct AlignSize {
-  int32_t N, B;
+  int32_t N, B, sites;  // sites evaluated
 };
 int32_t pick_nb(const AlignSize* msas, int32_t n, int32_t ncu, int32_t tile_seqs) {
   if (tile_seqs == 16 || tile_seqs == 32 || tile_seqs == 64) return tile_seqs;
@@ -296,8 +295,8 @@ int32_t pick_nb(const AlignSize* msas, int32_t n, int32_t ncu, int32_t tile_seqs
     for (int32_t m = 0; m < n; ++m) {
       const int32_t B = msas[m].B, tiles = (int32_t)(((int64_t)B + t - 1) / t);
       const int32_t rows = 2 * (((B + 47) / 48 + tiles - 1) / tiles);
-      items += (int64_t)msas[m].N * tiles;
-      work += (double)msas[m].N * tiles * msas[m].N * (rows + 8);
+      items += (int64_t)msas[m].sites * tiles;
+      work += (double)msas[m].sites * tiles * msas[m].N * (rows + 8);
     }
     const double k = (double)(2 * ((items + ncu - 1) / ncu) + 1) * (work / (double)items);
     if (cost == 0.0 || k < cost) {
@@ -610,7 +609,7 @@ int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
     HIPCHK(c, launch_check_f32(J, (size_t)N * N * q * q, c->pin_dev, c->stream));
     if (grad_scale) HIPCHK(c, launch_check_f64(grad_scale, (size_t)N, c->pin_dev, c->stream));
   }
-  const AlignSize size{N, B};
+  const AlignSize size{N, B, n_sites};
   const int32_t nb = pick_nb(&size, 1, c->ncu, 0);
   const EvalArgs a = eval_args(e, msa, B, N, q, w, h, J, eval_tiles(ps, B, nb), ps);
   TableArgs ta;
@@ -831,7 +830,7 @@ int prepare_fit(plm_ctx* c, const plm_msa_desc* d, int32_t n, int32_t q, const p
   c->pin[1] = total;
 
   std::vector<AlignSize> sizes(n);
-  for (int32_t k = 0; k < n; ++k) sizes[k] = AlignSize{d[k].N, d[k].B};
+  for (int32_t k = 0; k < n; ++k) sizes[k] = AlignSize{d[k].N, d[k].B, d[k].N};
   const int32_t nb = pick_nb(sizes.data(), n, c->ncu, o->tile_seqs);
   std::vector<int32_t> base(n + 1, 0);
   for (int32_t k = 0; k < n; ++k) {
@@ -1307,7 +1306,7 @@ int run_sym_once(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
     for (int32_t i = r + 1; i < N; ++i) pairs.push_back(make_int2(r, i));
   HIPCHK(c, hipMemcpyAsync(f.pairs, pairs.data(), pairs.size() * sizeof(int2), hipMemcpyHostToDevice, st));
 
-  const AlignSize size{N, B};
+  const AlignSize size{N, B, N};
   const int32_t nb = pick_nb(&size, 1, c->ncu, o->tile_seqs);
   const BatchArgs b = batch_args(f.t, 1, N, bwd_group(ps), fwd_group(ps));
   HIPCHK(c, launch_check_f32(h_io, (size_t)N * q, c->pin_dev, st));
