@@ -223,6 +223,34 @@ __global__ void diag_zero_kernel(double* cfn, int32_t N) {
   if (i < N) cfn[(size_t)i * N + i] = 0.0;
 }
 
+// Row sums and correction in one block, the same sums in the same order: for few
+// positions, where the launches above take longer than the work (plm_score whole,
+// with them and so: N = 2 12.3 / 6.9 us, N = 32 13.2 / 9.3, N = 64 13.5 / 12.9, N = 80
+// 15.0 / 17.5; two launches where one for both, one thread a row, took 9.6 and 15.5 us).
+constexpr int kCorSmall = 64;
+__global__ __launch_bounds__(1024) void correct_small_kernel(const double* __restrict__ fn, int32_t N, int32_t mode,
+                                                             double* __restrict__ cfn) {
+  __shared__ double rs[kCorSmall], red[16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid >> 6; i < N; i += 16) {
+    double s = 0.0;
+    for (int j = lane; j < N; j += 64) s += fn[(size_t)i * N + j];
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+    if (lane == 0) rs[i] = s;
+  }
+  __syncthreads();
+  const double all = block_sum_f64(tid < N ? rs[tid] : 0.0, red) / ((double)N * (double)N);
+  for (int e = tid; e < N * N; e += blockDim.x) {
+    const int i = e / N, j = e - i * N;
+    const double ri = rs[i] / (double)N, rj = rs[j] / (double)N;
+    cfn[e] = i == j                   ? 0.0
+             : mode == PLM_CORR_NONE ? fn[e]
+             : mode == PLM_CORR_ASC  ? fn[e] - ri - rj + all
+             : all == 0.0            ? 0.0
+                                     : fn[e] - ri * rj / all;
+  }
+}
+
 constexpr int kScResident = 256 * 6 * kScWaves;  // waves: six blocks (LDS) on each CU
 
 hipError_t launch_score_ex(const float* J, int32_t N, int32_t q, const ScoreOpts& o,
@@ -244,6 +272,10 @@ hipError_t launch_score_ex(const float* J, int32_t N, int32_t q, const ScoreOpts
   };
   if (o.combine == PLM_COMBINE_AVG) launch_norm(std::true_type{});
   else launch_norm(std::false_type{});
+  if (N <= kCorSmall) {
+    hipLaunchKernelGGL(correct_small_kernel, dim3(1), dim3(1024), 0, st, raw, N, o.correction, cor);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(rowsum_kernel, dim3(N), dim3(64), 0, st, raw, N, cor);
   hipLaunchKernelGGL(correct_kernel, dim3((N + kCorRows - 1) / kCorRows), dim3(256), 0, st, raw, N, o.correction, cor);
   hipLaunchKernelGGL(diag_zero_kernel, dim3((N + 255) / 256), dim3(256), 0, st, cor, N);
