@@ -8,6 +8,7 @@ device the calls raise.
 from __future__ import annotations
 
 import ctypes
+import functools
 from dataclasses import dataclass, field
 
 import torch
@@ -136,14 +137,20 @@ def _objgrad_inputs(msa, w, beff, h, J):
     return dev, B, N, q
 
 
+@functools.lru_cache(maxsize=256)
+def objgrad_half_sizes(B, N, q, path):
+    """Bytes of what objgrad_begin() keeps, and of the scratch either half needs beside it."""
+    kept = L.lib().plm_objgrad_kept_bytes(B, N, q, path)
+    return kept, L.lib().plm_objgrad_workspace_bytes(B, N, q, path) - kept
+
+
 def objgrad_begin(msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_GATHER_FP32):
     """(f, kept): the objectives of all sites, and what objgrad_finish() needs of
     their evaluation (the residuals above all)."""
     dev, B, N, q = _objgrad_inputs(msa, w, beff, h, J)
     f = torch.empty(N, dtype=torch.float64, device=dev)
-    nkept = L.lib().plm_objgrad_kept_bytes(B, N, q, path)
-    kept = workspace(nkept, dev)
-    ws = workspace(L.lib().plm_objgrad_workspace_bytes(B, N, q, path) - nkept, dev)
+    nkept, nws = objgrad_half_sizes(B, N, q, path)
+    kept, ws = workspace(nkept, dev), workspace(nws, dev)
     ctx = context(dev)
     _check(L.lib().plm_objgrad_begin_kept(ctx, _ptr(msa), B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J),
                                           float(lambda_h), float(lambda_J), path, _ptr(kept), kept.numel(),
@@ -162,8 +169,7 @@ def objgrad_finish(kept, msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=
             raise ValueError("grad_scale must have N entries")
     gh = torch.empty(N, q, dtype=torch.float32, device=dev)
     gJ = torch.empty(N, N, q, q, dtype=torch.float32, device=dev)
-    ws = workspace(L.lib().plm_objgrad_workspace_bytes(B, N, q, path) -
-                   L.lib().plm_objgrad_kept_bytes(B, N, q, path), dev)
+    ws = workspace(objgrad_half_sizes(B, N, q, path)[1], dev)
     ctx = context(dev)
     _check(L.lib().plm_objgrad_finish_kept(ctx, B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J), float(lambda_h),
                                            float(lambda_J), path, _ptr(kept), kept.numel(), _ptr(ws), ws.numel(),

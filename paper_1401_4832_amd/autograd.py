@@ -16,7 +16,7 @@ import weakref
 import torch
 
 from . import api
-from ._lib import lib, PATH_GATHER_FP32
+from ._lib import PATH_GATHER_FP32
 
 # Most that the graphs alive on a device hold together between forward and
 # backward, so that a sum over any number of families needs no more memory than
@@ -26,6 +26,7 @@ from ._lib import lib, PATH_GATHER_FP32
 KEEP_BYTES = 1 << 30
 
 _live: dict = {}  # token -> (device, bytes) of every evaluation kept
+_refs: dict = {}  # token -> weak reference to its tensor, which takes both entries out
 _tokens = itertools.count()
 
 
@@ -46,7 +47,7 @@ class PLMObjective(torch.autograd.Function):
         B, N = msa.shape
         token = None
         if any(ctx.needs_input_grad[:2]):
-            token = _reserve(msa.device, lib().plm_objgrad_kept_bytes(B, N, h.shape[1], PATH_GATHER_FP32))
+            token = _reserve(msa.device, api.objgrad_half_sizes(B, N, h.shape[1], PATH_GATHER_FP32)[0])
         if token is not None:
             try:
                 f, kept = api.objgrad_begin(msa, w, beff, h.detach(), J.detach(), lambda_h, lambda_J)
@@ -54,7 +55,7 @@ class PLMObjective(torch.autograd.Function):
                 _live.pop(token, None)
                 raise
             # given back when the graph, or whoever holds the tensor, lets it go
-            weakref.finalize(kept, _live.pop, token, None).atexit = False
+            _refs[token] = weakref.ref(kept, lambda _, t=token: (_live.pop(t, None), _refs.pop(t, None)))
             ctx.save_for_backward(h, J, msa, w, beff, kept)
         else:
             f, _, _ = api.objgrad(msa, w, beff, h.detach(), J.detach(), lambda_h, lambda_J, grad=False)
