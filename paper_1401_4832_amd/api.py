@@ -158,22 +158,22 @@ def objgrad_begin(msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_
     return f, kept
 
 
-def objgrad_finish(kept, msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_GATHER_FP32, grad_scale=None):
+def objgrad_finish(ws, msa, w, beff, h, J, lambda_h=0.01, lambda_J=0.01, path=L.PATH_GATHER_FP32, grad_scale=None):
     """(gh, gJ) of the evaluation that objgrad_begin(), with the same arguments,
-    left in kept (or in a copy of it); kept is not written."""
+    left in ws (or in a copy of it), which is not written."""
     dev, B, N, q = _objgrad_inputs(msa, w, beff, h, J)
-    _dev_tensor(kept, torch.uint8, dev, "kept")
+    _dev_tensor(ws, torch.uint8, dev, "ws")
     if grad_scale is not None:
         _dev_tensor(grad_scale, torch.float64, dev, "grad_scale")
         if grad_scale.numel() != N:
             raise ValueError("grad_scale must have N entries")
     gh = torch.empty(N, q, dtype=torch.float32, device=dev)
     gJ = torch.empty(N, N, q, q, dtype=torch.float32, device=dev)
-    ws = workspace(objgrad_half_sizes(B, N, q, path)[1], dev)
+    scratch = workspace(objgrad_half_sizes(B, N, q, path)[1], dev)
     ctx = context(dev)
     _check(L.lib().plm_objgrad_finish_kept(ctx, B, N, q, _ptr(w), _ptr(beff), _ptr(h), _ptr(J), float(lambda_h),
-                                           float(lambda_J), path, _ptr(kept), kept.numel(), _ptr(ws), ws.numel(),
-                                           _ptr(grad_scale), _ptr(gh), _ptr(gJ)), ctx)
+                                           float(lambda_J), path, _ptr(ws), ws.numel(), _ptr(scratch),
+                                           scratch.numel(), _ptr(grad_scale), _ptr(gh), _ptr(gJ)), ctx)
     return gh, gJ
 
 

@@ -767,7 +767,7 @@ __device__ inline uint4 onehot16_neg(uint4 s16, uint32_t nkk) {
 // value to the one stored (one FP64 rounding).  Bound: the int8 product, four digit planes against three
 // (10.9 ms at the products' measured rate for N = 500, B = 50 000), and LDS,
 // one B fragment per product; it took the place of a scatter of FP32 residuals
-// in symbol order through LDS, 85 -> 16 ms there, 1776 -> 347 us at N = 150,
+// in symbol order through LDS, 85 -> 16 ms there, 1776 -> 340 us at N = 150,
 // B = 8000 and 52 -> 28 us at N = 40, B = 500, with a gradient error against FP64
 // of 3.0e-8 where the scatter's was 4.9e-8 (N = 40).  Two planes and two row
 // blocks per wave, in two passes whose second reads back and adds to the
@@ -987,7 +987,7 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
           }
           const int row = row0 + 8 * (j >> 2) + (j & 3);
           if (row < nrows) {
-            // exact: every digit sum is an integer below 2^31, the whole below 2^53
+            // exact: every digit sum is an integer below 2^31, the whole at most 2^53
             double v = (double)acc[0][m][T][j];
 #pragma unroll
             for (int d = 1; d < ND; ++d) v = v * 256.0 + (double)acc[d][m][T][j];

@@ -448,7 +448,7 @@ struct TableArgs {
 // of 6 NV, with the same sums bit for bit.  v[0] of a lane ends as the sum of
 // value `ix`, if `cnt` > 0.  For a small site the trees are most of a pass:
 // N = 40, ten pairs, update pass 22.7 -> 15.0 us, evaluation pass 6.6 -> 5.6 us
-// (N = 500, where the passes stream the history at 6 TB/s, 1396 -> 1392 us); in
+// (N = 500, where the passes stream the history at 5 TB/s, 1396 -> 1392 us); in
 // the symmetric optimiser at N = 120, acceptance 73 -> 66 us, each further group
 // of pairs 25 -> 20 us.
 template <int NV, int O = 32>
