@@ -23,10 +23,10 @@ namespace plm {
 // the power 1/p), or the Burkoff divergence sum P ln(P / (f_i f_j)) with P
 // proportional to f_i(k) f_j(l) exp(J(k,l)) (computed with the largest
 // exponent factored out).
-// Lane 21 h + a holds the elements (state a of i, states 7 h + k of j),
-// k = 0..6, in registers: the site-i block is read straight into them (q
+// Lane 21 h + a holds the elements (state a of i, states h nc + k of j),
+// k < nc = ceil(q / 3), in registers: the site-i block is read straight into them (q
 // contiguous floats at a time), the site-j block through LDS (transposed);
-// the sums over j's states are seven adds and a sum over three lanes, those
+// the sums over j's states are nc adds and a sum over three lanes, those
 // over i's states the same on the matrix written to LDS and read with the
 // states exchanged.  Every wave uses its own LDS, so nothing waits for the
 // block; the next pair's loads are in flight while the current one is scored.  AVG: the gauge shift is linear, so the average is shifted once; the
@@ -35,7 +35,7 @@ namespace plm {
 // rate); measured there 277 -> 124 us (one wave per block, transposed
 // global reads, every sum q serial LDS reads before).
 constexpr int kScWaves = 4;
-constexpr int kScPer = 7;           // states of j per lane
+constexpr int kScPer = 7;           // states of j per lane at most
 constexpr int kScPitch = kQMax + 2;  // row pitch of the FP64 matrix in LDS (odd)
 static_assert(3 * kScPer == kQMax, "three lanes cover the states of j");
 
@@ -66,7 +66,8 @@ __global__ __launch_bounds__(64 * kScWaves) void pair_score_kernel(const float* 
     j = __builtin_amdgcn_readfirstlane(j);
   }
   const int qq = q * q, qs = o.exclude_gap ? q - 1 : q;  // states summed over
-  const int h = lane / kQMax, a = lane - h * kQMax, c0 = kScPer * h;
+  const int nc = (q + 2) / 3;  // states of j per lane
+  const int h = lane / kQMax, a = lane - h * kQMax, c0 = nc * h, cn = min(nc, q - c0);
   const bool act = h < 3 && a < q;
   // the other two lanes of this state
   const int l1 = h < 3 ? (h + 1) % 3 * kQMax + a : lane, l2 = h < 3 ? (h + 2) % 3 * kQMax + a : lane;
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(64 * kScWaves) void pair_score_kernel(const float* 
     const float* Jji = J + ((size_t)jj * N + ii) * qq;
 #pragma unroll
     for (int k = 0; k < kScPer; ++k) {
-      xi[k] = act && c0 + k < q ? Jij[(c0 + k) * q + a] : 0.f;
+      xi[k] = act && k < cn ? Jij[(c0 + k) * q + a] : 0.f;
       t[k] = lane + 64 * k < qq ? Jji[lane + 64 * k] : 0.f;
     }
   };
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(64 * kScWaves) void pair_score_kernel(const float* 
     double x[NM][kScPer];
 #pragma unroll
     for (int k = 0; k < kScPer; ++k) {
-      const double y = act && c0 + k < q ? (double)T[wid][a * q + c0 + k] : 0.0;
+      const double y = act && k < cn ? (double)T[wid][a * q + c0 + k] : 0.0;
       x[0][k] = AVG ? 0.5 * ((double)xc[k] + y) : (double)xc[k];
       if (!AVG) x[NM - 1][k] = y;
     }
@@ -112,20 +113,20 @@ __global__ __launch_bounds__(64 * kScWaves) void pair_score_kernel(const float* 
 #pragma unroll
       for (int k = 0; k < kScPer; ++k) {
         r += x[z][k];
-        if (act && c0 + k < q) M[wid][(c0 + k) * kScPitch + a] = x[z][k];
+        if (act && k < cn) M[wid][(c0 + k) * kScPitch + a] = x[z][k];
       }
       r = sum3(r) / dq;
       wave_sync();
       // here a is the state of j, c0 + k the states of i
 #pragma unroll
       for (int k = 0; k < kScPer; ++k)
-        if (act && c0 + k < q) s += M[wid][a * kScPitch + c0 + k];
+        if (act && k < cn) s += M[wid][a * kScPitch + c0 + k];
       s = sum3(s) / dq;
       if (act && h == 0) mean[wid][a] = s;
       wave_sync();
 #pragma unroll
       for (int k = 0; k < kScPer; ++k) {
-        cm[k] = c0 + k < q && h < 3 ? mean[wid][c0 + k] : 0.0;
+        cm[k] = k < cn && h < 3 ? mean[wid][c0 + k] : 0.0;
         g += cm[k];
       }
       g = sum3(g) / dq;
@@ -138,7 +139,7 @@ __global__ __launch_bounds__(64 * kScWaves) void pair_score_kernel(const float* 
     for (int k = 0; k < kScPer; ++k) {
       v[k] = AVG ? x[0][k]
                  : o.combine == PLM_COMBINE_MIN ? fmin(x[0][k], x[NM - 1][k]) : fmax(x[0][k], x[NM - 1][k]);
-      in[k] = act && a < qs && c0 + k < qs;
+      in[k] = act && a < qs && k < cn && c0 + k < qs;
     }
     double out = 0.0;
     if constexpr (NORM == PLM_NORM_BURKOFF) {
