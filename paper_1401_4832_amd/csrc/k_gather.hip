@@ -392,7 +392,7 @@ __global__ __launch_bounds__(kFwdThreads, sizeof(AT) == 4 ? 4 : 2) void fwd_kern
     const Item it = decode_item(b, KIND_FWD, t);
     EvalArgs a = load_uniform(b.ev + it.m);
     // path 0: FP32 rows where the weights' range is too wide for its digits
-    if (sizeof(AT) == 4 && a.rfrag == 4 && __builtin_amdgcn_readfirstlane(a.wexp[1])) a.rfrag = 0;
+    if (sizeof(AT) == 4 && a.rfrag == 4 && __builtin_amdgcn_readfirstlane(it.wide)) a.rfrag = 0;
     fwd_item<NB, AT, LO>(a, it.r, it.sub, lds, sgl, red);
     __syncthreads();
   }

@@ -1014,7 +1014,7 @@ __device__ inline void i8_item(const BatchArgs& bt, const EvalArgs& a, const Ite
   }
 }
 
-// Path 0 where the weights' range is too wide for the digits (a.wexp[1]): the
+// Path 0 where the weights' range is too wide for the digits (it.wide): the
 // residuals are FP32 rows, and the three-piece BF16 product takes them.  Its
 // items (a site x a block of columns) are dealt to the digit gradient's, whose
 // number the work tables hold.  Bound as bwd_mfma_kernel<3>: conversion and staging
@@ -1053,7 +1053,7 @@ __global__ __launch_bounds__(kGThreads) void bwd_i8_kernel(BatchArgs b) {
     if (t < 0) break;
     const Item it = decode_item(b, KIND_BWD, t);
     const EvalArgs a = load_uniform(b.ev + it.m);
-    if (ND == 4 && __builtin_amdgcn_readfirstlane(a.wexp[1])) {
+    if (ND == 4 && __builtin_amdgcn_readfirstlane(it.wide)) {
       wide_items(b, a, it, reinterpret_cast<char*>(Rb0), reinterpret_cast<char*>(Rb1));
     } else if (a.B_pad < kNegSeqMax) {
       i8_item<ND, LO, true>(b, a, it, Rb0, Rb1, sig0, sig1);

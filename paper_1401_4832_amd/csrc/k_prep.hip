@@ -96,7 +96,8 @@ __device__ inline void prep_zero(const PrepArgs& a, int blk) {
 
 // Raises bit 2 of *flag for a non-finite weight; wexp (if any) receives the
 // smallest exponent e with every |w_b| <= 2^e (0 for all-zero weights), and
-// whether a weight that is not zero lies below 2^(e - kR4RangeLog2).
+// whether a weight that is not zero lies below 2^(e - kR4RangeLog2), which goes
+// to *wide too.
 __device__ inline void prep_weights(const PrepArgs& a) {
   __shared__ double red[2][kPrThreads / 64];
   double mx = 0.0, mn = INFINITY;
@@ -109,7 +110,10 @@ __device__ inline void prep_weights(const PrepArgs& a) {
     mn = fmin(mn, v > 0.0 ? v : INFINITY);
   }
   if (bad && a.flag) atomicOr(a.flag, 2);
-  if (!a.wexp) return;
+  if (!a.wexp) {
+    if (threadIdx.x == 0) *a.wide = 0;
+    return;
+  }
   for (int o = 32; o > 0; o >>= 1) {
     mx = fmax(mx, __shfl_xor(mx, o, 64));
     mn = fmin(mn, __shfl_xor(mn, o, 64));
@@ -130,7 +134,7 @@ __device__ inline void prep_weights(const PrepArgs& a) {
       if (m == 0.5) --e;
     }
     a.wexp[0] = e;
-    a.wexp[1] = mn < ldexp(1.0, e - kR4RangeLog2);
+    a.wexp[1] = *a.wide = mn < ldexp(1.0, e - kR4RangeLog2);
   }
 }
 
@@ -143,6 +147,7 @@ __global__ __launch_bounds__(kPrThreads) void prep_kernel(PrepArgs a, TableArgs 
   if (table) {
     if (blk == 0) {
       write_eval_tables(t, a.flag);
+      if (a.tables_only && threadIdx.x == 0) *a.wide = a.wexp ? a.wexp[1] : 0;  // (the weights' block is not run)
       return;
     }
     --blk;

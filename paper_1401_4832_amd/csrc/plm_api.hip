@@ -162,7 +162,7 @@ void layout_fit(Bump& bp, int32_t B, int32_t N, int32_t q, int32_t m, int32_t hi
 struct Tables {
   EvalArgs* ev;
   LbfgsArgs* lb;
-  int32_t *site_base, *msa_of, *active, *n_active, *seg, *item_off, *nsub;
+  int32_t *site_base, *msa_of, *active, *n_active, *seg, *item_off, *nsub, *wide;
   uint32_t* ctr;
   SiteState* st;
   unsigned long long* site_evals;
@@ -178,6 +178,7 @@ void layout_tables(Bump& bp, int32_t n_msas, int32_t total, bool fit, Tables& t)
   t.seg = bp.take<int32_t>(n_msas + 1);
   t.item_off = bp.take<int32_t>(2 * (n_msas + 1));
   t.nsub = bp.take<int32_t>(2 * n_msas);
+  t.wide = bp.take<int32_t>(n_msas);
   t.ctr = bp.take<uint32_t>(2 * kQueues);
   t.st = fit ? bp.take<SiteState>(total) : nullptr;
   t.site_evals = bp.take<unsigned long long>(1);
@@ -196,6 +197,7 @@ BatchArgs batch_args(const Tables& t, int32_t n_msas, int32_t total, int32_t gro
   b.seg = t.seg;
   b.item_off = t.item_off;
   b.nsub = t.nsub;
+  b.wide = t.wide;
   b.ctr = t.ctr;
   b.bwd_group = group;
   b.fwd_group = fgroup;
@@ -358,7 +360,7 @@ int32_t eval_bwd_blocks(const PathSpec& p, int32_t N, int32_t q) {
 // alignment the path reads (backward = false: the forward's only), the zeroed
 // residual rows of a grouped gradient, the check of the weights.
 PrepArgs prep_args(const PathSpec& p, const EvalBufs& e, const uint8_t* msa, const double* w, int32_t B, int32_t N,
-                   int32_t q, int32_t* flag, bool backward = true) {
+                   int32_t q, int32_t* wide, int32_t* flag, bool backward = true) {
   PrepArgs a;
   a.msa = msa; a.B = B; a.N = N; a.q = q; a.B_pad = e.B_pad; a.N_pad = e.N_pad; a.NG = e.NG;
   a.msa_cm = e.msa_cm;
@@ -366,6 +368,7 @@ PrepArgs prep_args(const PathSpec& p, const EvalBufs& e, const uint8_t* msa, con
   a.sym3 = p.fwd_i8 ? e.sym3 : nullptr;
   a.w = w;
   a.wexp = p.bwd_i8 == 4 ? e.jexp : nullptr;  // (path 0 has no coupling digits)
+  a.wide = wide;
   const bool grouped = p.bwd_g3 || p.bwd_i8;
   const int32_t chunk = p.bwd_i8 == 4 ? kR4ChunkBytes : p.bwd_i8 ? kRiChunkBytes : kRfChunkBytes;
   a.zero0 = backward && grouped ? reinterpret_cast<uint4*>(e.R) : nullptr;
@@ -616,7 +619,7 @@ int objgrad_impl(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
   ta.b = b; ta.e = a; ta.sites = sites; ta.n_sites = n_sites;
   ta.nsub_f = a.tiles; ta.nsub_b = eval_bwd_blocks(ps, N, q);
   // (the tables hold addresses in the scratch, which may have moved since EV_BEGIN: written again)
-  PrepArgs pa = prep_args(ps, e, msa, w, B, N, q, c->pin_dev, gJ_out != nullptr || stage == EV_BEGIN);
+  PrepArgs pa = prep_args(ps, e, msa, w, B, N, q, t.wide, c->pin_dev, gJ_out != nullptr || stage == EV_BEGIN);
   pa.tables_only = stage == EV_FINISH;
   HIPCHK(c, launch_prepare(pa, &ta, c->stream));
   const Grids g = eval_grids(c, ps, nb);
@@ -838,7 +841,7 @@ int prepare_fit(plm_ctx* c, const plm_msa_desc* d, int32_t n, int32_t q, const p
     const FitBufs& f = fb[k];
     base[k + 1] = base[k] + m.N;
     HIPCHK(c, launch_check_f32(m.h_io, (size_t)m.N * q, c->pin_dev, st));
-    HIPCHK(c, launch_prepare(prep_args(ps, f.ev, m.msa, m.w, m.B, m.N, q, c->pin_dev), nullptr, st));
+    HIPCHK(c, launch_prepare(prep_args(ps, f.ev, m.msa, m.w, m.B, m.N, q, t.wide + k, c->pin_dev), nullptr, st));
     HIPCHK(c, launch_init_fit(m.N, q, m.h_io, m.J_io, f.Th, f.TJ, t.st + base[k], phase_host_dev + base[k], st));
     HIPCHK(c, launch_check_f32(m.J_io, (size_t)m.N * m.N * q * q, c->pin_dev, st));
     const EvalArgs a = eval_args(f.ev, m.msa, m.B, m.N, q, m.w, f.Th, f.TJ, eval_tiles(ps, m.B, nb), ps);
@@ -1315,7 +1318,7 @@ int run_sym_once(plm_ctx* c, const uint8_t* msa, int32_t B, int32_t N, int32_t q
     HIPCHK(c, launch_check_f32(h_lo_io, (size_t)N * q, c->pin_dev, st));
     HIPCHK(c, launch_check_f32(J_lo_io, (size_t)N * N * q * q, c->pin_dev, st));
   }
-  HIPCHK(c, launch_prepare(prep_args(ps, f.ev, msa, w, B, N, q, c->pin_dev), nullptr, st));
+  HIPCHK(c, launch_prepare(prep_args(ps, f.ev, msa, w, B, N, q, f.t.wide, c->pin_dev), nullptr, st));
   EvalArgs a = eval_args(f.ev, msa, B, N, q, w, f.Th, f.TJ, eval_tiles(ps, B, nb), ps);
   if (ps.f64 == 2) {
     a.h_lo = f.Thl;

@@ -207,6 +207,7 @@ struct BatchArgs {
   int32_t* item_off;         // [2][n_msas + 1] work-item offsets (forward, backward)
   const int32_t* nsub;       // [2][n_msas] work items per site (forward tiles, backward blocks)
   uint32_t* ctr;             // [2][kQueues] queue counters, cleared when the tables are built
+  const int32_t* wide;       // [n_msas] path 0: not zero where the residuals are FP32 rows (a copy of wexp[1])
   int32_t bwd_group;         // sites per gradient work item (consecutive in the active list)
   int32_t fwd_group;         // sites per forward work item
 };
@@ -219,7 +220,7 @@ __host__ __device__ inline int32_t kind_group(const BatchArgs& b, int kind) {
 // g, r: the first site of the item; first: its position in the active list;
 // cnt: the item's sites (active[first .. first + cnt), one alignment)
 struct Item {
-  int32_t m, g, r, sub, first, cnt;
+  int32_t m, g, r, sub, first, cnt, wide;
 };
 
 // Next work item of a persistent block (call from one thread; qi starts at
@@ -357,6 +358,7 @@ __device__ inline Item decode_item(const BatchArgs& b, int kind, int32_t t) {
   const int32_t loc = t - off[lo];
   const int32_t j = loc / ns;
   it.sub = loc - j * ns;
+  it.wide = b.wide[lo];  // (read beside the other tables: through the descriptor it would be one more trip an item)
   it.first = b.seg[lo] + j * grp;
   it.cnt = min(grp, b.seg[lo + 1] - it.first);
   it.g = b.active[it.first];
@@ -427,6 +429,7 @@ struct PrepArgs {
   uint32_t* sym3;       // null: not needed
   const double* w;      // [B], checked
   int32_t* wexp;        // null: not needed
+  int32_t* wide;        // the alignment's entry of BatchArgs.wide
   uint4* zero0;         // residual buffer of a grouped gradient whose tail chunks [zc0, zc1) are zeroed, or null
   uint4* zero1;         // a second digit set, or null
   int32_t chunk16, zc0, zc1;  // 16-byte words per chunk and site
